@@ -219,23 +219,21 @@ allocmoe_status allocmoe_pack_weights(const allocmoe_layer_desc* desc,
         char* out = static_cast<char*>(packed);
         const size_t dd = d, II = I, SS = Is;
         float* sc13 = at<float>(out, q.sc13);
-        ALLOCMOE_TRY(launch_pack_b_fp8(w->W1, E, d, I, out + q.q13, 2 * dd * II, 2 * dd * 32, 0, sc13,
-                                       2 * II, stream));
-        ALLOCMOE_TRY(launch_pack_b_fp8(w->W3, E, d, I, out + q.q13, 2 * dd * II, 2 * dd * 32, dd * 32,
-                                       sc13 + II, 2 * II, stream));
-        ALLOCMOE_TRY(launch_pack_b_fp8(w->W2, E, I, d, out + q.q2, II * dd, II * 32, 0,
-                                       at<float>(out, q.sc2), dd, stream));
+        float* scs13 = at<float>(out, q.scs13);
+        PackFp8Jobs jobs{};
+        jobs.job[0] = {w->W1, E, d, I, out + q.q13, 2 * dd * II, 2 * dd * 32, 0, sc13, 2 * II, 0};
+        jobs.job[1] = {w->W3, E, d, I, out + q.q13, 2 * dd * II, 2 * dd * 32, dd * 32, sc13 + II, 2 * II, 0};
+        jobs.job[2] = {w->W2, E, I, d, out + q.q2, II * dd, II * 32, 0, at<float>(out, q.sc2), dd, 0};
+        jobs.n = 3;
+        if (Is) {
+            jobs.job[3] = {w->Ws1, 1, d, Is, out + q.qs13, 2 * dd * SS, 2 * dd * 32, 0, scs13, 2 * SS, 0};
+            jobs.job[4] = {w->Ws3, 1, d, Is, out + q.qs13, 2 * dd * SS, 2 * dd * 32, dd * 32, scs13 + SS, 2 * SS, 0};
+            jobs.job[5] = {w->Ws2, 1, Is, d, out + q.qs2, SS * dd, SS * 32, 0, at<float>(out, q.scs2), dd, 0};
+            jobs.n = 6;
+        }
+        ALLOCMOE_TRY(launch_pack_fp8(jobs, stream));
         ALLOCMOE_TRY(launch_pack_gate(w->Wg, desc->shared_gate ? w->w_sg : nullptr, d, E,
                                       out + q.gate, stream));
-        if (Is) {
-            float* scs13 = at<float>(out, q.scs13);
-            ALLOCMOE_TRY(launch_pack_b_fp8(w->Ws1, 1, d, Is, out + q.qs13, 2 * dd * SS, 2 * dd * 32, 0,
-                                           scs13, 2 * SS, stream));
-            ALLOCMOE_TRY(launch_pack_b_fp8(w->Ws3, 1, d, Is, out + q.qs13, 2 * dd * SS, 2 * dd * 32,
-                                           dd * 32, scs13 + SS, 2 * SS, stream));
-            ALLOCMOE_TRY(launch_pack_b_fp8(w->Ws2, 1, Is, d, out + q.qs2, SS * dd, SS * 32, 0,
-                                           at<float>(out, q.scs2), dd, stream));
-        }
         return ALLOCMOE_OK;
     }
     const PackedLayout p = packed_of(desc);

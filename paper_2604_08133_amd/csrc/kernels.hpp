@@ -117,10 +117,22 @@ hipError_t launch_ffn_bf16_t256(bool swiglu, StreamGroup routed, StreamGroup sha
 // 32 k x 32 n: lane l holds 16 bytes, k = 32 kb + 8 (l/32) + i in bytes i = 0..7 and
 // k = 32 kb + 16 + 8 (l/32) + i in bytes 8 + i, column 32 nb + l%32.  Destination of
 // fragment (g, nb, kb): out + g*group_stride + nb*nblock_stride + base_off + kb*1024
-// (bytes).  scale_out[g*scale_stride + n].
-hipError_t launch_pack_b_fp8(const void* W, int G, int Kd, int N, void* out, size_t group_stride,
-                             size_t nblock_stride, size_t base_off, float* scale_out,
-                             size_t scale_stride, hipStream_t stream);
+// (bytes).  scale[g*scale_stride + n].
+// Up to six matrices [G][Kd][N] in one launch; Kd and N multiples of 128.
+struct PackFp8Job {
+    const void* W;
+    int G, Kd, N;
+    void* out;
+    size_t group_stride, nblock_stride, base_off;
+    float* scale;
+    size_t scale_stride;
+    int n_strips;   // filled by the launcher
+};
+struct PackFp8Jobs {
+    PackFp8Job job[6];
+    int n;
+};
+hipError_t launch_pack_fp8(PackFp8Jobs jobs, hipStream_t stream);
 hipError_t launch_pack_b(const void* W, int G, int Kd, int N, void* out,
                          size_t group_stride_elems, size_t nblock_stride_elems,
                          size_t base_off_elems, hipStream_t stream);

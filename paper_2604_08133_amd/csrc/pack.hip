@@ -7,6 +7,8 @@
 // stored as 64 lanes x 16 bytes = 1 KB.  The fragments of one column block nb
 // are contiguous along k (kb = 0 .. Kd/16-1).  Destination of fragment
 // (g, nb, kb):  out + g*group_stride + nb*nblock_stride + base_off + kb*512.
+#include <type_traits>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -45,86 +47,141 @@ __global__ __launch_bounds__(256) void pack_b_kernel(const bf16_t* __restrict__ 
 
 // E4M3 of the OCP 8-bit floating point format: sign, 4 exponent bits (bias 7), 3 mantissa
 // bits, subnormals, no infinities, largest finite magnitude 448.  Nearest code, ties to
-// the even mantissa, magnitudes above 448 saturate.
-__device__ __forceinline__ uint32_t e4m3_encode(float y) {
-    const uint32_t sign = (__float_as_uint(y) >> 24) & 0x80u;
-    const float a = fminf(fabsf(y), 448.f);
-    uint32_t code;
-    if (a < 0.015625f) {                       // below the smallest normal 2^-6: steps of 2^-9
-        code = static_cast<uint32_t>(__float2int_rn(a * 512.f));   // 8 = the smallest normal
-    } else {
-        const uint32_t u = __float_as_uint(a);
-        uint32_t e = (u >> 23) - 120u;         // biased by 7: (exponent - 127) + 7
-        uint32_t m = (u >> 20) & 7u;
-        const uint32_t rest = u & 0xFFFFFu, half = 0x80000u;
-        if (rest > half || (rest == half && (m & 1u))) ++m;
-        code = (e << 3) + m;                   // a mantissa carry moves into the exponent
-        code = min(code, 0x7Eu);
+// the even mantissa, magnitudes above 448 saturate: the conversion unit's rounding, on
+// values that were clamped before.  Byte i of the result = code of y[i].
+__device__ __forceinline__ uint32_t e4m3_encode4(const float (&y)[4]) {
+    float c[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c[i] = __builtin_amdgcn_fmed3f(y[i], -448.f, 448.f);
+    int w = __builtin_amdgcn_cvt_pk_fp8_f32(c[0], c[1], 0, false);
+    w = __builtin_amdgcn_cvt_pk_fp8_f32(c[2], c[3], w, true);
+    return static_cast<uint32_t>(w);
+}
+
+// A workgroup owns 64 columns (128 bytes of every row) of one matrix.  Lane 16 g + t of wave
+// w loads columns 4 t .. + 3 of the 32 rows of k block 4 w + g, i.e. the 16 waves hold 2048
+// rows of the strip in registers: the matrix is read once, the column maxima are formed
+// from the registers (lanes, then LDS), and the codes leave as whole 16-byte pieces of the
+// fragments.  Longer columns are read twice, in chunks of 2048 rows.  All six matrices of a
+// layer go in one launch, so that the shared expert's few strips fill up the others' last
+// round.  Bound by HBM: 64 experts of 2048 x 1408 and a shared expert of 2048 x 2816, 1.7 GB
+// in and out, take 460 us (3.7 TB/s; a large copy reaches 4.8).  One thread per column for
+// the maxima, then a second pass that read the matrices again, took 5.9 ms: 860 us per
+// matrix for a serial chain of row loads, 258 us for the codes with two full divisions.
+constexpr int kPackWaves = 16, kPackRows = kPackWaves * 4 * 32, kPackCols = 64;
+
+__global__ __launch_bounds__(kPackWaves* kWave) void pack_fp8_kernel(PackFp8Jobs jobs) {
+    __shared__ uint32_t wave_max[kPackWaves][kPackCols / 2];   // two columns' magnitudes each
+    __shared__ float col_scale[kPackCols];
+    int bid = blockIdx.x, jn = 0;
+    while (bid >= jobs.job[jn].n_strips) bid -= jobs.job[jn++].n_strips;
+    const PackFp8Job& J = jobs.job[jn];
+    const int N = J.N, Kd = J.Kd, strips = N / kPackCols;
+    const int g = bid / strips, n0 = bid % strips * kPackCols;
+    const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+    const int t = lane % 16, kb = wave * 4 + lane / 16;
+    const bf16_t* src = static_cast<const bf16_t*>(J.W) + static_cast<size_t>(g) * Kd * N + n0 + 4 * t;
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    u32x2 v[32];
+    auto load = [&](int row0) {   // (past the end, Kd being a multiple of 32: the last rows again)
+        const bf16_t* p = src + static_cast<size_t>(min(row0, Kd - 32)) * N;
+#pragma unroll
+        for (int r = 0; r < 32; ++r)
+            v[r] = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p + static_cast<size_t>(r) * N));
+    };
+    // magnitudes of bf16 values compare like their bit patterns
+    u16x2 m[2] = {u16x2{0, 0}, u16x2{0, 0}};
+    for (int c = 0; c < Kd; c += kPackRows) {
+        load(c + kb * 32);
+#pragma unroll
+        for (int r = 0; r < 32; ++r)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                m[h] = __builtin_elementwise_max(m[h], __builtin_bit_cast(u16x2, v[r][h] & 0x7FFF7FFFu));
     }
-    return sign | code;
-}
-
-__global__ __launch_bounds__(256) void column_scale_kernel(const bf16_t* __restrict__ W, int G,
-                                                           int Kd, int N,
-                                                           float* __restrict__ scale,
-                                                           size_t scale_stride) {
-    const size_t idx = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (idx >= static_cast<size_t>(G) * N) return;
-    const int n = idx % N, g = idx / N;
-    const bf16_t* src = W + static_cast<size_t>(g) * Kd * N + n;
-    float amax = 0.f;
-    for (int k = 0; k < Kd; ++k) amax = fmaxf(amax, fabsf(bf16_to_f32(src[static_cast<size_t>(k) * N])));
-    scale[static_cast<size_t>(g) * scale_stride + n] = amax > 0.f ? __fdiv_rn(amax, 448.f) : 1.f;
-}
-
-__global__ __launch_bounds__(256) void pack_b_fp8_kernel(const bf16_t* __restrict__ W, int G, int Kd,
-                                                         int N, uint8_t* __restrict__ out,
-                                                         size_t group_stride, size_t nblock_stride,
-                                                         size_t base_off,
-                                                         const float* __restrict__ scale,
-                                                         size_t scale_stride) {
-    const int KB = Kd / 32, NB = N / 32;
-    const size_t total = static_cast<size_t>(G) * NB * KB * kWave;
-    const size_t idx = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (idx >= total) return;
-    const int l = idx % kWave;
-    size_t f = idx / kWave;
-    const int kb = f % KB;
-    f /= KB;
-    const int nb = f % NB;
-    const int g = f / NB;
-    const int n = nb * 32 + (l % 32);
-    const float sc = scale[static_cast<size_t>(g) * scale_stride + n];
-    uint32_t words[4] = {0, 0, 0, 0};
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int k0 = kb * 32 + 16 * h + 8 * (l / 32);
-        const bf16_t* src = W + (static_cast<size_t>(g) * Kd + k0) * N + n;
+    for (int h = 0; h < 2; ++h) {   // over the lanes with the same columns
+        m[h] = __builtin_elementwise_max(m[h], __builtin_bit_cast(u16x2, lane_xor<16>(__builtin_bit_cast(uint32_t, m[h]))));
+        m[h] = __builtin_elementwise_max(m[h], __builtin_bit_cast(u16x2, lane_xor<32>(__builtin_bit_cast(uint32_t, m[h]))));
+        if (lane < 16) wave_max[wave][2 * t + h] = __builtin_bit_cast(uint32_t, m[h]);
+    }
+    __syncthreads();
+    if (tid < kPackCols) {
+        uint32_t top = 0;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const float w = bf16_to_f32(src[static_cast<size_t>(i) * N]);
-            words[2 * h + i / 4] |= e4m3_encode(__fdiv_rn(w, sc)) << (8 * (i % 4));
+        for (int w = 0; w < kPackWaves; ++w) top = max(top, (wave_max[w][tid / 2] >> (16 * (tid % 2))) & 0xFFFFu);
+        const float amax = __uint_as_float(top << 16);
+        const float sc = amax > 0.f ? __fdiv_rn(amax, 448.f) : 1.f;
+        col_scale[tid] = sc;
+        J.scale[static_cast<size_t>(g) * J.scale_stride + n0 + tid] = sc;
+    }
+    __syncthreads();
+    float sc[4], rc[4];
+    bool moderate = true;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        sc[j] = col_scale[4 * t + j];
+        rc[j] = __fdiv_rn(1.f, sc[j]);
+        moderate = moderate && sc[j] > 0x1p-80f && sc[j] < 0x1p80f;
+    }
+    // w / sc, correctly rounded: the quotient estimate and two corrections by the exact
+    // remainder, as in the full division, whose scaling for extreme exponents is not needed
+    // where the scale's exponent is moderate (a value so small that a remainder underflows
+    // is far below half the smallest code and becomes zero either way; the sign of a zero,
+    // which the remainders lose, is put back)
+    auto quotient = [&](float w, int j) {
+        const float q0 = w * rc[j];
+        const float q1 = fmaf(fmaf(-q0, sc[j], w), rc[j], q0);
+        return copysignf(fmaf(fmaf(-q1, sc[j], w), rc[j], q1), w);
+    };
+    char* out = static_cast<char*>(J.out) + static_cast<size_t>(g) * J.group_stride + J.base_off;
+    auto store_codes = [&](int row0, auto short_division) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int n = n0 + 4 * t + j;
+            char* frag = out + static_cast<size_t>(n / 32) * J.nblock_stride + static_cast<size_t>(row0 / 32) * 1024;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                uint32_t word[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    float y[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const uint32_t pair = v[16 * (q / 2) + 8 * h + 4 * (q % 2) + i][j / 2];
+                        const float w = __uint_as_float((j % 2) ? (pair & 0xFFFF0000u) : (pair << 16));
+                        y[i] = decltype(short_division)::value ? quotient(w, j) : __fdiv_rn(w, sc[j]);
+                    }
+                    word[q] = e4m3_encode4(y);
+                }
+                *reinterpret_cast<uint4*>(frag + (32 * h + n % 32) * 16) = make_uint4(word[0], word[1], word[2], word[3]);
+                __builtin_amdgcn_sched_barrier(0);   // one piece at a time: the strip fills the registers
+            }
         }
+    };
+    const bool all_moderate = __all(moderate);
+    for (int c = 0; c < Kd; c += kPackRows) {
+        const int row0 = c + kb * 32;
+        if (Kd > kPackRows) load(row0);
+        if (row0 >= Kd) continue;
+        if (all_moderate)
+            store_codes(row0, std::true_type{});
+        else
+            store_codes(row0, std::false_type{});
     }
-    uint8_t* dst = out + static_cast<size_t>(g) * group_stride +
-                   static_cast<size_t>(nb) * nblock_stride + base_off +
-                   static_cast<size_t>(kb) * 1024 + static_cast<size_t>(l) * 16;
-    *reinterpret_cast<uint4*>(dst) = make_uint4(words[0], words[1], words[2], words[3]);
 }
 
-hipError_t launch_pack_b_fp8(const void* W, int G, int Kd, int N, void* out, size_t group_stride,
-                             size_t nblock_stride, size_t base_off, float* scale_out,
-                             size_t scale_stride, hipStream_t stream) {
-    const size_t cols = static_cast<size_t>(G) * N;
-    const size_t total = static_cast<size_t>(G) * (N / 32) * (Kd / 32) * kWave;
-    if (total == 0) return hipSuccess;
-    hipLaunchKernelGGL(column_scale_kernel, dim3(static_cast<unsigned>((cols + 255) / 256)),
-                       dim3(256), 0, stream, static_cast<const bf16_t*>(W), G, Kd, N, scale_out,
-                       scale_stride);
-    hipLaunchKernelGGL(pack_b_fp8_kernel, dim3(static_cast<unsigned>((total + 255) / 256)),
-                       dim3(256), 0, stream, static_cast<const bf16_t*>(W), G, Kd, N,
-                       static_cast<uint8_t*>(out), group_stride, nblock_stride, base_off, scale_out,
-                       scale_stride);
+hipError_t launch_pack_fp8(PackFp8Jobs jobs, hipStream_t stream) {
+    int64_t strips = 0;
+    for (int j = 0; j < jobs.n; ++j) {
+        PackFp8Job& J = jobs.job[j];
+        J.n_strips = J.G * (J.N / kPackCols);
+        strips += J.n_strips;
+    }
+    if (strips == 0) return hipSuccess;
+    hipLaunchKernelGGL(pack_fp8_kernel, dim3(static_cast<unsigned>(strips)), dim3(kPackWaves * kWave), 0,
+                       stream, jobs);
     return hipGetLastError();
 }
 
