@@ -615,25 +615,29 @@ allocmoe_status forward_impl(const allocmoe_layer_desc* desc, const void* X,
         }
         if (overlap) ALLOCMOE_TRY(hipStreamWaitEvent(stream, side->join, 0));
     } else {
-        const float* Xf = static_cast<const float*>(X);
+        F32Group r1, r2, h1, h2;   // routed and shared, first and second half
+        if (B > 0) {
+            r1.A = static_cast<const float*>(X); r1.lda = d; r1.row_map = row_token;
+            r1.B1 = static_cast<const float*>(w->W1); r1.B3 = static_cast<const float*>(w->W3);
+            r1.Kd = d; r1.N = I; r1.tile_info = tile_info; r1.max_tiles = s.max_tiles;
+            r1.C = static_cast<float*>(H); r1.ldc = I;
+            r2.A = static_cast<const float*>(H); r2.lda = I;
+            r2.B1 = static_cast<const float*>(w->W2); r2.Kd = I; r2.N = d;
+            r2.tile_info = tile_info; r2.max_tiles = s.max_tiles;
+            r2.C = static_cast<float*>(O); r2.ldc = d;
+        }
+        if (Is) {
+            h1.A = static_cast<const float*>(X); h1.lda = d;
+            h1.B1 = static_cast<const float*>(w->Ws1); h1.B3 = static_cast<const float*>(w->Ws3);
+            h1.Kd = d; h1.N = Is; h1.M_dense = T; h1.C = static_cast<float*>(Hs); h1.ldc = Is;
+            h2.A = static_cast<const float*>(Hs); h2.lda = Is;
+            h2.B1 = static_cast<const float*>(w->Ws2); h2.Kd = Is; h2.N = d; h2.M_dense = T;
+            h2.C = static_cast<float*>(Os); h2.ldc = d;
+        }
         ALLOCMOE_MARK(ALLOCMOE_STAGE_FFN1);
-        if (B > 0)
-            ALLOCMOE_TRY(launch_ffn_f32(true, Xf, d, row_token, static_cast<const float*>(w->W1),
-                                        static_cast<const float*>(w->W3), d, I, tile_info,
-                                        s.max_tiles, 0, static_cast<float*>(H), I, stream));
-        if (Is)
-            ALLOCMOE_TRY(launch_ffn_f32(true, Xf, d, nullptr, static_cast<const float*>(w->Ws1),
-                                        static_cast<const float*>(w->Ws3), d, Is, nullptr, 0, T,
-                                        static_cast<float*>(Hs), Is, stream));
+        ALLOCMOE_TRY(launch_ffn_f32(true, r1, h1, stream));
         ALLOCMOE_MARK(ALLOCMOE_STAGE_FFN2);
-        if (B > 0)
-            ALLOCMOE_TRY(launch_ffn_f32(false, static_cast<const float*>(H), I, nullptr,
-                                        static_cast<const float*>(w->W2), nullptr, I, d, tile_info,
-                                        s.max_tiles, 0, static_cast<float*>(O), d, stream));
-        if (Is)
-            ALLOCMOE_TRY(launch_ffn_f32(false, static_cast<const float*>(Hs), Is, nullptr,
-                                        static_cast<const float*>(w->Ws2), nullptr, Is, d, nullptr,
-                                        0, T, static_cast<float*>(Os), d, stream));
+        ALLOCMOE_TRY(launch_ffn_f32(false, r2, h2, stream));
     }
     // step 6: Eq. (2)
     ALLOCMOE_MARK(ALLOCMOE_STAGE_COMBINE);

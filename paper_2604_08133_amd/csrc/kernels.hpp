@@ -69,11 +69,22 @@ hipError_t launch_plan(const float* topk_s, const int32_t* topk_ids, int T, int 
 
 // ---- ffn_f32.hip : C = A B (or silu(A B1) * (A B3)) over row tiles, fp32, row-major B
 // A rows are taken through row_map when it is not null.  With tile_info null the
-// rows 0..M_dense-1 form one group (group 0).  B1/B3: [G][Kd][N].
-hipError_t launch_ffn_f32(bool swiglu, const float* A, int lda, const int32_t* row_map,
-                          const float* B1, const float* B3, int Kd, int N,
-                          const int32_t* tile_info, int64_t max_tiles, int M_dense, float* C,
-                          int ldc, hipStream_t stream);
+// rows 0..M_dense-1 form one group (group 0).  B1/B3: [G][Kd][N].  A == nullptr
+// marks an absent group.
+struct F32Group {
+    const float* A = nullptr;
+    int lda = 0;
+    const int32_t* row_map = nullptr;
+    const float *B1 = nullptr, *B3 = nullptr;
+    int Kd = 0, N = 0;
+    const int32_t* tile_info = nullptr;
+    int64_t max_tiles = 0;
+    int M_dense = 0;
+    float* C = nullptr;
+    int ldc = 0;
+};
+// routed experts' tiles (tile_info set) and the shared expert's in one launch
+hipError_t launch_ffn_f32(bool swiglu, F32Group routed, F32Group shared, hipStream_t stream);
 
 // ---- ffn_bf16.hip : the same contraction on the matrix cores from packed weights
 // One group of row tiles: A rows (through row_map when not null) times packed

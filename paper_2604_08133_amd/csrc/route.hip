@@ -2,7 +2,7 @@
 // Eq. (6)): logits = x W_gate (+bias), softmax over all E experts, then each
 // token's K largest scores in descending order (ties: lower expert id).
 //
-// Layout: one lane per expert (E <= 64).  A workgroup of 4 waves owns kTok
+// Layout: one lane per expert (E <= 64).  A workgroup of kRouteWaves waves owns kRouteTok
 // tokens; the waves split the hidden dimension, each lane accumulating the
 // logit of its expert, and the partial sums meet in LDS in a fixed order.
 #include "common.hpp"
@@ -11,7 +11,10 @@
 namespace allocmoe {
 
 constexpr int kRouteTok = 4;    // tokens per workgroup
-constexpr int kRouteWaves = 4;  // waves per workgroup, splitting d
+// waves per workgroup, splitting d: the kernel is a chain of loads of the gate matrix, a
+// few workgroups per compute unit at most, so each wave's share is kept to a chunk or two
+constexpr int kRouteWaves = 16;
+constexpr int kRouteBatch = 16;   // rows of the gate matrix loaded together
 
 // Sorted Top-K of N tokens' scores at once, lane = expert: larger score first, equal
 // scores lower expert first.  K rounds of: the largest remaining key of the wave, the
@@ -91,14 +94,24 @@ __global__ __launch_bounds__(kRouteWaves* kWave) void route_kernel(
 #pragma unroll
             for (int q = 0; q < kRouteTok; ++q) gacc[q] += xv[q] * g;
         }
-        const int n = min(kWave, d - h0);
-#pragma unroll 8
-        for (int i = 0; i < n; ++i) {
-            const float wv =
-                lane_is_expert ? load_f32(Wg, static_cast<size_t>(h0 + i) * E + lane) : 0.f;
+        // the token's value of h0 + i goes to all lanes as a scalar (v_readlane: one issue
+        // slot, where a shuffle is a round trip through the LDS crossbar)
+        auto step = [&](int i, float wv) {
 #pragma unroll
-            for (int q = 0; q < kRouteTok; ++q) acc[q] += __shfl(xv[q], i, kWave) * wv;
+            for (int q = 0; q < kRouteTok; ++q)
+                acc[q] += __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(xv[q]), i)) * wv;
+        };
+        const int n = min(kWave, d - h0);
+        const TIn* wp = Wg + static_cast<size_t>(h0) * E + (lane_is_expert ? lane : 0);
+        int i = 0;
+        for (; i + kRouteBatch <= n; i += kRouteBatch) {
+            float wv[kRouteBatch];
+#pragma unroll
+            for (int u = 0; u < kRouteBatch; ++u) wv[u] = load_f32(wp, static_cast<size_t>(i + u) * E);
+#pragma unroll
+            for (int u = 0; u < kRouteBatch; ++u) step(i + u, wv[u]);
         }
+        for (; i < n; ++i) step(i, load_f32(wp, static_cast<size_t>(i) * E));
     }
 #pragma unroll
     for (int q = 0; q < kRouteTok; ++q) {
