@@ -16,100 +16,163 @@ namespace allocmoe {
 
 namespace {
 
-constexpr int kStatThreads = 256;
+// Each kernel is a chain of a few dependent trips to memory, so a workgroup has as many
+// waves as it can hold and a thread's loads go out in batches.  At 6000 tokens, 64 experts
+// and 6 candidates selection, dispatch and the analytics together went from 208 to 65 us (one
+// thread per token or expert with serial loads, the ranks on 24 workgroups, before).
+constexpr int kStatThreads = 1024;
+constexpr int kStatWaves = kStatThreads / kWave;
 
-// H_t = -sum_e s ln s, one wave per token, lane = expert
-__global__ __launch_bounds__(kStatThreads) void token_entropy_kernel(
-    const float* __restrict__ scores, int T, int E, float* __restrict__ H) {
+// H_t = -sum_e s ln s, lane = expert; a wave takes kEntropyTok tokens, whose loads and
+// logarithms overlap
+constexpr int kEntropyTok = 4;
+constexpr int kEntropyWgTok = kStatWaves * kEntropyTok;
+
+__device__ __forceinline__ void token_entropies(const float* __restrict__ scores, int wg, int T, int E,
+                                                float* __restrict__ H) {
     const int lane = lane_id();
-    const int t = blockIdx.x * (kStatThreads / kWave) + threadIdx.x / kWave;
-    if (t >= T) return;
-    const float s = lane < E ? scores[static_cast<size_t>(t) * E + lane] : 0.f;
-    const float term = s > 0.f ? -s * logf(s) : 0.f;
-    const float h = wave_sum(term);
-    if (lane == 0) H[t] = h;
+    const int t0 = wg * kEntropyWgTok + static_cast<int>(threadIdx.x) / kWave * kEntropyTok;
+    float s[kEntropyTok];
+#pragma unroll
+    for (int q = 0; q < kEntropyTok; ++q)
+        s[q] = (lane < E && t0 + q < T) ? scores[static_cast<size_t>(t0 + q) * E + lane] : 0.f;
+#pragma unroll
+    for (int q = 0; q < kEntropyTok; ++q) {
+        const float h = wave_sum(s[q] > 0.f ? -s[q] * logf(s[q]) : 0.f);
+        if (lane == 0 && t0 + q < T) H[t0 + q] = h;
+    }
 }
 
-// one workgroup per expert: counts and score sums of its candidate pairs and of
-// its kept pairs; thread-strided partial sums, then a fixed-order tree
-__global__ __launch_bounds__(kStatThreads) void expert_load_kernel(
-    const int32_t* __restrict__ topk_ids, const float* __restrict__ topk_s,
-    const int32_t* __restrict__ keep_count, int T, int K, int32_t* __restrict__ load_orig,
-    int32_t* __restrict__ load_kept, float* __restrict__ wload_orig,
-    float* __restrict__ wload_kept) {
-    __shared__ int32_t cnt[2][kStatThreads];
-    __shared__ float wsum[2][kStatThreads];
-    const int e = blockIdx.x, tid = threadIdx.x;
+// one workgroup per expert: counts and score sums of its candidate pairs and of its kept
+// pairs; thread-strided partial sums over the flat list of pairs, then a fixed-order tree
+constexpr int kLoadBatch = 12;
+
+__device__ __forceinline__ void expert_load(const int32_t* __restrict__ topk_ids,
+                                            const float* __restrict__ topk_s,
+                                            const int32_t* __restrict__ keep_count, int e, int T, int K,
+                                            int32_t* load_orig, int32_t* load_kept, float* wload_orig,
+                                            float* wload_kept) {
+    __shared__ int32_t cnt[2][kStatWaves];
+    __shared__ float wsum[2][kStatWaves];
+    const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+    const int pairs = T * K;   // < 2^31
+    // p / K = (p M) >> 35 with M = floor(2^35 / K) + 1: the excess is at most p / 2^35 < 1/16 <= 1/K
+    const uint64_t M = (1ull << 35) / K + 1;
     int co = 0, ck = 0;
     float wo = 0.f, wk = 0.f;
-    for (int t = tid; t < T; t += kStatThreads) {
-        const int kt = keep_count[t];
-        for (int j = 0; j < K; ++j) {
-            if (topk_ids[static_cast<size_t>(t) * K + j] != e) continue;
-            const float s = topk_s[static_cast<size_t>(t) * K + j];
+    for (int64_t p0 = tid; p0 < pairs; p0 += kLoadBatch * kStatThreads) {
+        int id[kLoadBatch], kept[kLoadBatch];
+        float s[kLoadBatch];
+#pragma unroll
+        for (int u = 0; u < kLoadBatch; ++u) {   // past the end: the last pair, not counted
+            const int64_t q = p0 + u * kStatThreads;
+            const int p = static_cast<int>(q < pairs ? q : pairs - 1);
+            const int t = static_cast<int>((static_cast<uint64_t>(p) * M) >> 35);
+            id[u] = q < pairs ? topk_ids[p] : -1;
+            s[u] = topk_s[p];
+            kept[u] = p - t * K < keep_count[t];
+        }
+#pragma unroll
+        for (int u = 0; u < kLoadBatch; ++u) {
+            if (id[u] != e) continue;
             ++co;
-            wo += s;
-            if (j < kt) {
+            wo += s[u];
+            if (kept[u]) {
                 ++ck;
-                wk += s;
+                wk += s[u];
             }
         }
     }
-    cnt[0][tid] = co;
-    cnt[1][tid] = ck;
-    wsum[0][tid] = wo;
-    wsum[1][tid] = wk;
-    __syncthreads();
-    for (int half = kStatThreads / 2; half >= 1; half >>= 1) {
-        if (tid < half) {
-            cnt[0][tid] += cnt[0][tid + half];
-            cnt[1][tid] += cnt[1][tid + half];
-            wsum[0][tid] += wsum[0][tid + half];
-            wsum[1][tid] += wsum[1][tid + half];
-        }
-        __syncthreads();
+    wo = wave_sum(wo);
+    wk = wave_sum(wk);
+    co = __builtin_amdgcn_readlane(wave_scan_incl(co), kWave - 1);
+    ck = __builtin_amdgcn_readlane(wave_scan_incl(ck), kWave - 1);
+    if (lane == 0) {
+        cnt[0][wave] = co;
+        cnt[1][wave] = ck;
+        wsum[0][wave] = wo;
+        wsum[1][wave] = wk;
     }
+    __syncthreads();
     if (tid == 0) {
-        load_orig[e] = cnt[0][0];
-        load_kept[e] = cnt[1][0];
-        wload_orig[e] = wsum[0][0];
-        wload_kept[e] = wsum[1][0];
-    }
-}
-
-// doubled average rank of every token's entropy among all T entropies
-__global__ __launch_bounds__(kStatThreads) void entropy_rank_kernel(const float* __restrict__ H,
-                                                                    int T,
-                                                                    int32_t* __restrict__ rank2) {
-    __shared__ float tile[kStatThreads];
-    const int t = blockIdx.x * kStatThreads + threadIdx.x;
-    const float mine = t < T ? H[t] : 0.f;
-    int less = 0, equal = 0;
-    for (int base = 0; base < T; base += kStatThreads) {
-        const int u = base + threadIdx.x;
-        __syncthreads();
-        tile[threadIdx.x] = u < T ? H[u] : 0.f;
-        __syncthreads();
-        const int n = min(kStatThreads, T - base);
-        for (int i = 0; i < n; ++i) {
-            const float v = tile[i];
-            less += v < mine ? 1 : 0;
-            equal += v == mine ? 1 : 0;
+        co = ck = 0;
+        wo = wk = 0.f;
+        for (int w = 0; w < kStatWaves; ++w) {
+            co += cnt[0][w];
+            ck += cnt[1][w];
+            wo += wsum[0][w];
+            wk += wsum[1][w];
         }
+        load_orig[e] = co;
+        load_kept[e] = ck;
+        wload_orig[e] = wo;
+        wload_kept[e] = wk;
     }
-    if (t < T) rank2[t] = 2 * less + equal + 1;
 }
 
-__device__ __forceinline__ long long block_sum_i64(long long v, long long* buf) {
-    const int tid = threadIdx.x;
-    __syncthreads();
-    buf[tid] = v;
-    __syncthreads();
-    for (int half = kStatThreads / 2; half >= 1; half >>= 1) {
-        if (tid < half) buf[tid] += buf[tid + half];
-        __syncthreads();
+// workgroups 0 .. E-1: an expert's loads; the others: the entropies of their tokens
+__global__ __launch_bounds__(kStatThreads) void load_entropy_kernel(
+    const float* __restrict__ scores, const int32_t* __restrict__ topk_ids,
+    const float* __restrict__ topk_s, const int32_t* __restrict__ keep_count, int T, int E, int K,
+    int32_t* __restrict__ load_orig, int32_t* __restrict__ load_kept, float* __restrict__ wload_orig,
+    float* __restrict__ wload_kept, float* __restrict__ H) {
+    const int wg = blockIdx.x;
+    if (wg < E)
+        expert_load(topk_ids, topk_s, keep_count, wg, T, K, load_orig, load_kept, wload_orig, wload_kept);
+    else
+        token_entropies(scores, wg - E, T, E, H);
+}
+
+// Doubled average rank of every token's entropy among all T entropies: 2 #smaller + #equal
+// + 1 = #smaller + #not greater + 1.  All pairs are compared, one compare and one add with
+// carry each: bound by the vector units, so the pairs are spread over all of them: a
+// workgroup ranks 16 tokens (lane % 16), and its 16 waves' 64 groups of 16 lanes take
+// the entropies compared with in turn, four at a time.
+constexpr int kRankTok = 16;
+constexpr int kRankGroups = kStatThreads / kRankTok;
+constexpr int kRankUnroll = 4;
+
+__global__ __launch_bounds__(kStatThreads) void entropy_rank_kernel(const float* __restrict__ H, int T,
+                                                                    int32_t* __restrict__ rank2) {
+    typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));   // H: any 4-byte boundary
+    __shared__ int part[kStatWaves][kRankTok];
+    const int tid = threadIdx.x, wave = tid / kWave;
+    const int t = blockIdx.x * kRankTok + tid % kRankTok;
+    const float mine = H[min(t, T - 1)];
+    int below = 0;   // #smaller + #not greater
+    auto compare = [&](float v) {
+        below += v < mine ? 1 : 0;
+        below += v <= mine ? 1 : 0;
+    };
+    const int quads = T / 4;
+    int c = tid / kRankTok;
+    for (; c + (kRankUnroll - 1) * kRankGroups < quads; c += kRankUnroll * kRankGroups) {
+        f32x4_u v[kRankUnroll];
+#pragma unroll
+        for (int u = 0; u < kRankUnroll; ++u)
+            v[u] = *reinterpret_cast<const f32x4_u*>(H + 4 * static_cast<size_t>(c + u * kRankGroups));
+#pragma unroll
+        for (int u = 0; u < kRankUnroll; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) compare(v[u][i]);
     }
-    return buf[0];
+    for (; c < quads; c += kRankGroups) {
+        const f32x4_u v = *reinterpret_cast<const f32x4_u*>(H + 4 * static_cast<size_t>(c));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) compare(v[i]);
+    }
+    if (tid / kRankTok == 0)
+        for (int u = 4 * quads; u < T; ++u) compare(H[u]);
+    below += static_cast<int>(lane_xor<16>(static_cast<uint32_t>(below)));
+    below += static_cast<int>(lane_xor<32>(static_cast<uint32_t>(below)));
+    if (lane_id() < kRankTok) part[wave][lane_id()] = below;
+    __syncthreads();
+    if (tid < kRankTok && t < T) {
+        int sum = 1;
+#pragma unroll
+        for (int w = 0; w < kStatWaves; ++w) sum += part[w][tid];
+        rank2[t] = sum;
+    }
 }
 
 // Pearson correlation of two rank vectors from exact integer sums (doubled ranks)
@@ -126,30 +189,41 @@ __device__ __forceinline__ float rank_correlation(long long n, long long sa, lon
 }
 
 // one workgroup: the five summary numbers
+constexpr int kMetricsBatch = 6;
 __global__ __launch_bounds__(kStatThreads) void routing_metrics_kernel(
     const int32_t* __restrict__ load_orig, const int32_t* __restrict__ load_kept,
     const float* __restrict__ wload_orig, const float* __restrict__ wload_kept,
     const int32_t* __restrict__ keep_count, const int32_t* __restrict__ entropy_rank2, int T,
     int E, int K, float* __restrict__ metrics) {
-    __shared__ long long buf[kStatThreads];
-    __shared__ int32_t k_hist[64];
-    const int tid = threadIdx.x, lane = lane_id();
+    constexpr int kValues = 64;   // keep counts counted (0 .. K, K <= 16)
+    constexpr int kSums = 5;
+    __shared__ long long buf[kSums][kStatWaves];
+    __shared__ int32_t k_hist[kValues];
+    __shared__ int32_t k_rank2[kValues];   // doubled average rank of a token that keeps v
+    const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+    auto isum = [](long long s) {
+        uint64_t v = static_cast<uint64_t>(s);   // (sums of integers: any order)
+        v += lane_xor<32>(v);
+        v += lane_xor<16>(v);
+        v += lane_xor<8>(v);
+        v += lane_xor<4>(v);
+        v += lane_xor<2>(v);
+        v += lane_xor<1>(v);
+        return static_cast<long long>(v);
+    };
+    if (tid < kValues) k_hist[tid] = 0;
+    __syncthreads();
 
-    // ---- expert side, first wave, lane = expert
-    if (tid < kWave) {
+    // ---- expert side, last wave (the others go on to the tokens), lane = expert
+    if (wave == kStatWaves - 1) {
         const bool valid = lane < E;
         const int lo = valid ? load_orig[lane] : 0, lk = valid ? load_kept[lane] : 0;
         int ro = 1, rk = 1;   // doubled average ranks among the E loads
         for (int o = 0; o < E; ++o) {
-            const int oo = __shfl(lo, o, kWave), ok = __shfl(lk, o, kWave);
+            const int oo = __builtin_amdgcn_readlane(lo, o), ok = __builtin_amdgcn_readlane(lk, o);
             ro += oo < lo ? 2 : (oo == lo ? 1 : 0);
             rk += ok < lk ? 2 : (ok == lk ? 1 : 0);
         }
-        auto isum = [&](long long v) {
-#pragma unroll
-            for (int s = 32; s >= 1; s >>= 1) v += __shfl_xor(v, s, kWave);
-            return v;
-        };
         const long long a = valid ? ro : 0, b = valid ? rk : 0;
         const float rho = rank_correlation(E, isum(a), isum(b), isum(a * a), isum(b * b), isum(a * b));
         // weighted load distributions
@@ -170,30 +244,63 @@ __global__ __launch_bounds__(kStatThreads) void routing_metrics_kernel(
         }
     }
 
-    // ---- token side: doubled ranks of keep_count from its histogram (values 0..K)
-    if (tid < 64) k_hist[tid] = 0;
-    __syncthreads();
-    for (int t = tid; t < T; t += kStatThreads) atomicAdd(&k_hist[keep_count[t]], 1);   // integers
-    __syncthreads();
-    long long sa = 0, sb = 0, saa = 0, sbb = 0, sab = 0;
-    for (int t = tid; t < T; t += kStatThreads) {
-        const int v = keep_count[t];
-        int below = 0;
-        for (int u = 0; u < v; ++u) below += k_hist[u];
-        const long long b = 2ll * below + k_hist[v] + 1, a = entropy_rank2[t];
-        sa += a;
-        sb += b;
-        saa += a * a;
-        sbb += b * b;
-        sab += a * b;
+    // ---- token side: doubled ranks of keep_count from its histogram
+    constexpr int kHistThreads = kStatThreads - kWave;
+    if (wave < kStatWaves - 1) {
+        for (int t0 = tid; t0 - lane < T; t0 += kMetricsBatch * kHistThreads) {   // (whole waves)
+            int v[kMetricsBatch];
+#pragma unroll
+            for (int u = 0; u < kMetricsBatch; ++u) {
+                const int t = t0 + u * kHistThreads;
+                v[u] = t < T ? keep_count[t] : -1;
+            }
+            for (int k = 0; k <= K; ++k) {   // one count per wave and value instead of 64 colliding ones
+                int n = 0;
+#pragma unroll
+                for (int u = 0; u < kMetricsBatch; ++u) n += __popcll(__ballot(v[u] == k));
+                if (lane == 0 && n) atomicAdd(&k_hist[k], n);   // integers
+            }
+#pragma unroll
+            for (int u = 0; u < kMetricsBatch; ++u)
+                if (v[u] > K) atomicAdd(&k_hist[v[u]], 1);
+        }
     }
-    sa = block_sum_i64(sa, buf);
-    sb = block_sum_i64(sb, buf);
-    saa = block_sum_i64(saa, buf);
-    sbb = block_sum_i64(sbb, buf);
-    sab = block_sum_i64(sab, buf);
-    if (tid == 0) metrics[4] = rank_correlation(T, sa, sb, saa, sbb, sab);
-    (void)K;
+    __syncthreads();
+    if (tid < kValues) k_rank2[tid] = 2 * (wave_scan_incl(k_hist[tid]) - k_hist[tid]) + k_hist[tid] + 1;
+    __syncthreads();
+    long long sums[kSums] = {0, 0, 0, 0, 0};   // a, b, a a, b b, a b
+    for (int t0 = tid; t0 < T; t0 += kMetricsBatch * kStatThreads) {
+        int v[kMetricsBatch], r[kMetricsBatch];
+#pragma unroll
+        for (int u = 0; u < kMetricsBatch; ++u) {
+            const int t = min(t0 + u * kStatThreads, T - 1);
+            v[u] = keep_count[t];
+            r[u] = entropy_rank2[t];
+        }
+#pragma unroll
+        for (int u = 0; u < kMetricsBatch; ++u) {
+            if (t0 + u * kStatThreads >= T) continue;
+            const long long b = k_rank2[v[u]], a = r[u];
+            sums[0] += a;
+            sums[1] += b;
+            sums[2] += a * a;
+            sums[3] += b * b;
+            sums[4] += a * b;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kSums; ++i) {
+        const long long v = isum(sums[i]);
+        if (lane == 0) buf[i][wave] = v;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        for (int i = 0; i < kSums; ++i) {
+            sums[i] = 0;
+            for (int w = 0; w < kStatWaves; ++w) sums[i] += buf[i][w];
+        }
+        metrics[4] = rank_correlation(T, sums[0], sums[1], sums[2], sums[3], sums[4]);
+    }
 }
 
 }  // namespace
@@ -203,13 +310,11 @@ hipError_t launch_routing_stats(const float* scores, const int32_t* topk_ids, co
                                 int32_t* load_orig, int32_t* load_kept, float* wload_orig,
                                 float* wload_kept, float* token_entropy, int32_t* entropy_rank2,
                                 float* metrics, hipStream_t stream) {
-    const int tokens_per_wg = kStatThreads / kWave;
-    hipLaunchKernelGGL(token_entropy_kernel, dim3((T + tokens_per_wg - 1) / tokens_per_wg),
-                       dim3(kStatThreads), 0, stream, scores, T, E, token_entropy);
-    hipLaunchKernelGGL(expert_load_kernel, dim3(E), dim3(kStatThreads), 0, stream, topk_ids,
-                       topk_s, keep_count, T, K, load_orig, load_kept, wload_orig, wload_kept);
-    hipLaunchKernelGGL(entropy_rank_kernel, dim3((T + kStatThreads - 1) / kStatThreads),
-                       dim3(kStatThreads), 0, stream, token_entropy, T, entropy_rank2);
+    hipLaunchKernelGGL(load_entropy_kernel, dim3(E + (T + kEntropyWgTok - 1) / kEntropyWgTok),
+                       dim3(kStatThreads), 0, stream, scores, topk_ids, topk_s, keep_count, T, E, K,
+                       load_orig, load_kept, wload_orig, wload_kept, token_entropy);
+    hipLaunchKernelGGL(entropy_rank_kernel, dim3((T + kRankTok - 1) / kRankTok), dim3(kStatThreads), 0,
+                       stream, token_entropy, T, entropy_rank2);
     hipLaunchKernelGGL(routing_metrics_kernel, dim3(1), dim3(kStatThreads), 0, stream, load_orig,
                        load_kept, wload_orig, wload_kept, keep_count, entropy_rank2, T, E, K,
                        metrics);
