@@ -34,9 +34,10 @@ int dense_tile_rows(int M, int col_tiles) {
 hipError_t launch_ffn_bf16_t256(bool swiglu, StreamGroup routed, StreamGroup shared,
                                 hipStream_t stream) {
     const int cols = swiglu ? 128 : 256;
+    auto col_tiles = [cols](const StreamGroup& g) { return (g.N + cols - 1) / cols; };
     if (routed.A != nullptr && routed.tile_info == nullptr)
-        routed.dense_rows = dense_tile_rows(routed.M_dense, routed.N / cols);
-    if (shared.A != nullptr) shared.dense_rows = dense_tile_rows(shared.M_dense, shared.N / cols);
+        routed.dense_rows = dense_tile_rows(routed.M_dense, col_tiles(routed));
+    if (shared.A != nullptr) shared.dense_rows = dense_tile_rows(shared.M_dense, col_tiles(shared));
     // items per XCD; for the routed group an upper bound (the real tile count is
     // known on the device only)
     int64_t per_xcd = 0;
@@ -47,12 +48,12 @@ hipError_t launch_ffn_bf16_t256(bool swiglu, StreamGroup routed, StreamGroup sha
             tiles = 2 * (((routed.max_tiles + 1) / 2 + 1 + kXcds - 1) / kXcds);
         else
             tiles = ((routed.M_dense + routed.dense_rows - 1) / routed.dense_rows + kXcds - 1) / kXcds;
-        per_xcd += tiles * (routed.N / cols);
+        per_xcd += tiles * col_tiles(routed);
     }
     if (shared.A != nullptr) {
         // XCD grid over (row tiles, column tiles): xr x 8/xr, chosen to minimise the
         // bytes the 8 L2s fetch in total: (8/xr) x activations + xr x weights
-        const int64_t rt = (shared.M_dense + shared.dense_rows - 1) / shared.dense_rows, ct = shared.N / cols;
+        const int64_t rt = (shared.M_dense + shared.dense_rows - 1) / shared.dense_rows, ct = col_tiles(shared);
         const double a_bytes = static_cast<double>(shared.M_dense) * shared.Kd;
         const double b_bytes = static_cast<double>(shared.N) * shared.Kd * (swiglu ? 2 : 1);
         int best = 1;

@@ -5,7 +5,8 @@
 // Register-blocked 256 x 256 tile on 4 waves (one per SIMD, all 512 registers).
 //
 // A workgroup owns <= 256 rows of one expert times 128 SwiGLU columns (128 of
-// W1 and the same 128 of W3) or 256 columns of W2.  Wave w owns 64 of those
+// W1 and the same 128 of W3) or 256 columns of W2, fewer in the last column tile of a
+// width that is no multiple of those.  Wave w owns 64 of those
 // weight columns (four 16-column MFMA operands: two of W1 and two of W3 of the
 // same columns, or four neighbouring ones of W2) times every 16-row block of
 // the tile: up to 16 x 4 accumulators of 16x16, 256 registers.
@@ -126,13 +127,15 @@ __device__ __forceinline__ uint32_t widen_fp8x2(uint32_t q) {
 // b0, b1: the wave's two weight streams (bf16 fragments, or with FP8 the codes: a lane's
 // 16 bytes per 32 k hold its fragment of the even k16 step, then of the odd one);
 // sc0, sc1: with FP8 the scales of the 32 columns of each stream.
+// live: the wave's columns exist; a wave past the last column (the other waves still need its
+// share of the activation loads) reads zeros in place of weights and stores nothing.
 // NF: 16-row blocks of the tile.  NR: 32-k steps of weights held in registers.
 template <bool SWIGLU, int NF, bool STREAM_ONCE, bool FP8, int NR>
 __device__ __forceinline__ void t256_body(char* lds, const bf16_t* A, size_t lda,
                                           const int32_t* row_map, const void* b0,
                                           const void* b1, const float* sc0, const float* sc1,
                                           int KT, int wave, int lane, int row0,
-                                          int rows, int nt, void* C, int ldc) {
+                                          int rows, int nt, bool live, void* C, int ldc) {
     // acc[f][c]: 16 token rows (f) x 16 weight columns (c: two blocks per stream)
     f32x4 acc[NF][4];
 #pragma unroll
@@ -164,7 +167,7 @@ __device__ __forceinline__ void t256_body(char* lds, const bf16_t* A, size_t lda
     // of the stream reads zeros instead of faulting.  Weights that no other tile
     // reads are marked non-temporal: they need not displace what the caches hold
     // for tiles that share theirs.
-    const int stream_bytes = KT * kStepK * 32 * (FP8 ? 1 : 2);
+    const int stream_bytes = live ? KT * kStepK * 32 * (FP8 ? 1 : 2) : 0;
     const __amdgpu_buffer_rsrc_t rs0 = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<void*>(b0), 0, stream_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rs1 = __builtin_amdgcn_make_buffer_rsrc(
@@ -346,6 +349,13 @@ __device__ __forceinline__ void t256_body(char* lds, const bf16_t* A, size_t lda
             __builtin_amdgcn_sched_barrier(0);
         }
     };
+    // (Copies of accumulators that the compiler makes between the passes, and the epilogue's
+    // reads, depend on MFMAs it does not know: 16 idle states cover their latency.)
+    auto drain = [] {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_nop 15" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
     // slots [s2, s2 + SLOTS) of the contraction (s2 a multiple of NR / 2); TAIL: the last
     // ones.  The tail issues no weight load that nothing would use (the compiler would drop
     // it, and the count with it).
@@ -359,6 +369,10 @@ __device__ __forceinline__ void t256_body(char* lds, const bf16_t* A, size_t lda
             auto refills = [](int d) { return !TAIL || d < 0 || d + NR - 1 < 2 * SLOTS; };
             constexpr int kIssued = (refills(2 * q - 1) + refills(2 * q) + refills(2 * q + 1)) * kWLoads;
             static_assert(TAIL || kIssued + NL == kWaitA, "the count above");
+            if constexpr (TAIL && q == SLOTS - 1) {   // an odd number of slots ends one earlier
+                drain();
+                if (s >= KT) return;
+            }
             step(0, s, slot, 2 * q, refills(2 * q));
             step(1, s, slot, 2 * q, false);
             step(2, s, slot, 2 * q + 1, refills(2 * q + 1));
@@ -369,15 +383,6 @@ __device__ __forceinline__ void t256_body(char* lds, const bf16_t* A, size_t lda
             step(3, s, slot, 2 * q + 1, false);
         };
         unrolled(slot_body, std::make_integer_sequence<int, SLOTS>{});
-    };
-    // (an odd number of slots is rounded up: the extra slot's weights are the zeros past the
-    // end of the streams)
-    // (Copies of accumulators that the compiler makes between the passes, and the epilogue's
-    // reads, depend on MFMAs it does not know: 16 idle states cover their latency.)
-    auto drain = [] {
-        __builtin_amdgcn_sched_barrier(0);
-        asm volatile("s_nop 15" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
     };
     int s2 = 0;
     for (; s2 + NR / 2 <= KT; s2 += NR / 2) {
@@ -436,7 +441,7 @@ __device__ __forceinline__ void t256_body(char* lds, const bf16_t* A, size_t lda
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
         const int mr = f * 16 + m;
-        if (mr >= rows) continue;   // (the same for the four lanes of a row)
+        if (mr >= rows || !live) continue;   // (the same for the four lanes of a row)
         bf16_t* out = static_cast<bf16_t*>(C) + static_cast<size_t>(row0 + mr) * ldc +
                       nt * (SWIGLU ? 128 : 256) + wave * (SWIGLU ? 32 : 64) + col8;
         if (SWIGLU) {
@@ -504,7 +509,8 @@ __global__ __launch_bounds__(kWaves* kWave, 1) void ffn_bf16_t256_kernel(StreamG
     //    activation rows follow within a few items.
     constexpr int kColsPerTile = SWIGLU ? 128 : 256;
     const int xcd = blockIdx.x % kXcds, idx = blockIdx.x / kXcds;
-    const int nt0 = g0.A ? g0.N / kColsPerTile : 1, nt1 = g1.A ? g1.N / kColsPerTile : 1;
+    const int nt0 = g0.A ? (g0.N + kColsPerTile - 1) / kColsPerTile : 1;
+    const int nt1 = g1.A ? (g1.N + kColsPerTile - 1) / kColsPerTile : 1;
     int S = 0, s_rows = 1;     // dense group: items and row tiles of this XCD
     const int xr = g1.xr, xc = kXcds / xr, xri = xcd % xr, xci = xcd / xr;
     if (g1.A != nullptr) {
@@ -586,8 +592,13 @@ __global__ __launch_bounds__(kWaves* kWave, 1) void ffn_bf16_t256_kernel(StreamG
     // Kd/16 fragments of 64 lanes x 16 B (FP8: Kd/32), contiguous
     constexpr size_t kElemBytes = FP8 ? 1 : 2;
     const size_t stream_elems = static_cast<size_t>(Kd) * 32;
-    const size_t sidx = SWIGLU ? static_cast<size_t>(4 * nt + wave) * 2
-                               : static_cast<size_t>(8 * nt + 2 * wave);
+    // (N is a multiple of 64: a wave's columns exist all or not at all; one without columns
+    // keeps addresses inside the matrix)
+    constexpr int kColsPerWave = kColsPerTile / kWaves;
+    const int col0 = nt * kColsPerTile + wave * kColsPerWave;
+    const bool live = col0 < g.N;
+    const int wcol = live ? col0 : 0;
+    const size_t sidx = SWIGLU ? static_cast<size_t>(wcol / 32) * 2 : static_cast<size_t>(wcol / 32);
     // (wave-uniform pointers: the loads take a scalar base and the lane's offset)
     const char* b0 = Bp + (static_cast<size_t>(e) * g.group_stride + sidx * stream_elems) * kElemBytes;
     const char* b1 = b0 + stream_elems * kElemBytes;
@@ -597,7 +608,7 @@ __global__ __launch_bounds__(kWaves* kWave, 1) void ffn_bf16_t256_kernel(StreamG
     const float* sc1 = nullptr;
     if (FP8) {
         const float* sc = g.scale + static_cast<size_t>(e) * (SWIGLU ? 2 : 1) * g.N;
-        sc0 = sc + nt * kColsPerTile + wave * (SWIGLU ? 32 : 64);
+        sc0 = sc + wcol;
         sc1 = SWIGLU ? sc0 + g.N : sc0 + 32;
     }
 
@@ -609,10 +620,10 @@ __global__ __launch_bounds__(kWaves* kWave, 1) void ffn_bf16_t256_kernel(StreamG
     do {                                                                                            \
         if (only_tile)                                                                              \
             t256_body<SWIGLU, n, true, FP8, ring>(lds, A, lda, row_map, b0, b1, sc0, sc1, KT,       \
-                                                  wave, lane, row0, rows, nt, g.C, ldc);            \
+                                                  wave, lane, row0, rows, nt, live, g.C, ldc);            \
         else                                                                                        \
             t256_body<SWIGLU, n, false, FP8, ring>(lds, A, lda, row_map, b0, b1, sc0, sc1, KT,      \
-                                                   wave, lane, row0, rows, nt, g.C, ldc);           \
+                                                   wave, lane, row0, rows, nt, live, g.C, ldc);           \
     } while (0)
 #define ALLOCMOE_T256_CASE(n)                                                                       \
     case n:                                                                                         \

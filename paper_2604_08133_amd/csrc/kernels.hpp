@@ -116,8 +116,7 @@ hipError_t launch_ffn_bf16_stream(bool swiglu, StreamGroup routed, StreamGroup s
 
 // Register-blocked 256 x 256 tile kernel for prefill-shaped groups (tile map with
 // kTileRowsLarge rows per tile): weights straight from global memory into
-// registers, activations through LDS; needs Kd % 128 == 0 and N % 128 == 0
-// (swiglu) or N % 256 == 0 (plain).
+// registers, activations through LDS; Kd and N multiples of 64.
 constexpr int kTileRowsLarge = 256;
 hipError_t launch_ffn_bf16_t256(bool swiglu, StreamGroup routed, StreamGroup shared,
                                 hipStream_t stream);

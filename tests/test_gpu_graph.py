@@ -13,12 +13,15 @@ from paper_2604_08133_amd.layer import DeviceLayer
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("kind", ["decode-shaped", "prefill-shaped"])
+@pytest.mark.parametrize("kind", ["decode-shaped", "prefill-shaped", "large"])
 def test_forward_replays_from_a_graph(kind):
     if kind == "decode-shaped":      # both groups on the streaming kernel, one stream
         w = synth.Workload("graph_decode", T=24, d=256, E=16, I=128, K=4, K_base=1, budget=48,
                            dtype="bf16", I_shared=128, I_shared_each=128, bias_kind="normal")
-    else:                            # tile kernel, shared expert on the library's side stream
+    elif kind == "large":            # tile kernel, shared expert on the library's side stream
+        w = synth.Workload("graph_large", T=8000, d=1024, E=16, I=512, K=4, K_base=1, budget=16000,
+                           dtype="bf16", I_shared=512, I_shared_each=512, bias_kind="normal")
+    else:                            # several rows per expert, one stream
         w = synth.Workload("graph_prefill", T=300, d=256, E=8, I=128, K=3, K_base=1, budget=500,
                            dtype="bf16", I_shared=128, I_shared_each=128, bias_kind="normal")
     layer = synth.make_layer(w, seed=81)

@@ -1,34 +1,52 @@
 """The bf16 tile kernel at every tile height (1 to 16 blocks of 16 rows, the last one partly
-filled) and at contraction lengths that leave every remainder of its loop: one expert that
-takes all tokens, so that the row count is the token count.  Same reference and tolerance as
-tests/test_gpu_layer.py."""
+filled), at contraction lengths that leave every remainder of its loops (odd numbers of 64-k
+slots among them) and at widths that end inside a column tile; and both sides of the rule that
+chooses between the kernels.  Same reference and tolerance as tests/test_gpu_layer.py."""
 import pytest
+import torch
 
 from paper_2604_08133_amd import synth
 from paper_2604_08133_amd.layer import DeviceLayer
 from tests.test_gpu_fp8 import quantised_reference
-from tests.test_gpu_layer import check_layer, sample_tokens
+from tests.test_gpu_layer import check_layer, sample_tokens, stratified_tokens
 
 pytestmark = pytest.mark.gpu
 
-
-@pytest.mark.parametrize("fp8", [False, True])
-@pytest.mark.parametrize("d,I", [(256, 384), (768, 128), (512, 640)])
-def test_every_tile_height(d, I, fp8):
-    for blocks in range(1, 17):
-        T = 16 * blocks - 3
-        w = synth.Workload("one_expert", T=T, d=d, E=1, I=I, K=1, K_base=1, budget=T, dtype="bf16")
-        layer = synth.make_layer(w, seed=70 + blocks)
-        dev = DeviceLayer(w, layer, weights_fp8=fp8)
-        ref = quantised_reference(layer)[0] if fp8 else None
-        check_layer(w, layer, dev=dev, ref_layer=ref, tokens=sorted({0, T - 1, *sample_tokens(T, 12, blocks)}))
+T, E = 3000, 64
 
 
-def test_light_tiles_among_full_ones():
-    # strongly skewed experts: a few single tiles of at most 64 rows beside full tiles, at a
-    # contraction length that is no multiple of the light tiles' longer weight ring
-    w = synth.Workload("light_tiles", T=1500, d=512, E=10, I=640, K=2, K_base=1, budget=2600,
-                       dtype="bf16", bias_kind="zipf")
-    check_layer(w, synth.make_layer(w, seed=71), tokens=lambda offs, rt: sorted(
-        {int(rt[r]) for e in range(10) for r in range(int(offs[e]), int(offs[e + 1])) if
-         r - int(offs[e]) < 64}))
+@pytest.mark.parametrize("d,I,I_shared,fp8", [
+    (256, 384, 128, False), (768, 128, 0, False), (512, 640, 384, False), (320, 192, 192, False),
+    (64, 1088, 64, False), (1088, 64, 0, False), (448, 832, 320, False), (704, 448, 1408, False),
+    (256, 384, 128, True), (384, 256, 384, True), (640, 128, 0, True), (768, 640, 128, True)])
+def test_tile_heights_and_widths(d, I, I_shared, fp8):
+    # a ramp of popularity: single tiles of a few rows up to experts of several full tiles
+    # (3.3 GFLOP and more at 140 rows an expert: the tile kernel's side of the rule)
+    w = synth.Workload("tile_heights", T=T, d=d, E=E, I=I, K=4, K_base=1, budget=3 * T, dtype="bf16",
+                       I_shared=I_shared, I_shared_each=I_shared, bias_kind="normal")
+    layer = synth.make_layer(w, seed=71)
+    layer["bias"] = torch.linspace(-3.0, 1.0, E)
+    dev = DeviceLayer(w, layer, weights_fp8=fp8)
+    ref = quantised_reference(layer)[0] if fp8 else None
+    heights = set()
+
+    def tokens(offs, row_token):
+        for e in range(E):
+            n = int(offs[e + 1]) - int(offs[e])
+            tiles = -(-n // 256)
+            per = -(-n // max(tiles, 1))
+            heights.update(-(-min(per, n - i * per) // 16) for i in range(tiles))
+        return stratified_tokens(offs, row_token, T)
+
+    check_layer(w, layer, dev=dev, ref_layer=ref, tokens=tokens)
+    # (a height may be missing at one width; 12 widths together leave none out)
+    assert len(heights) >= 12 and min(heights) <= 2 and max(heights) == 16, heights
+
+
+@pytest.mark.parametrize("T,budget", [(32, 127), (40, 128), (128, 512), (500, 1000), (700, 2800)])
+def test_both_sides_of_the_kernel_choice(T, budget):
+    # rows per expert around 8 and 32, work around the two limits; fewer routed rows than the
+    # shared expert has tokens
+    w = synth.Workload("choice", T=T, d=832, E=16, I=448, K=4, K_base=1, budget=budget, dtype="bf16",
+                       I_shared=896, I_shared_each=448, shared_gate=True, bias_kind="normal")
+    check_layer(w, synth.make_layer(w, seed=73), tokens=[0, T - 1, *sample_tokens(T, 24, 9)])
