@@ -240,17 +240,21 @@ allocmoe_status allocmoe_pack_weights(const allocmoe_layer_desc* desc,
     if (packed_bytes < p.total_elems * 2 || !aligned(packed, kAlign)) return ALLOCMOE_EWORKSPACE;
     uint16_t* out = static_cast<uint16_t*>(packed);
     const size_t dd = d, II = I;
-    ALLOCMOE_TRY(launch_pack_b(w->W1, E, d, I, out + p.p13, 2 * dd * II, 2 * dd * 32, 0, stream));
-    ALLOCMOE_TRY(launch_pack_b(w->W3, E, d, I, out + p.p13, 2 * dd * II, 2 * dd * 32, dd * 32, stream));
-    ALLOCMOE_TRY(launch_pack_b(w->W2, E, I, d, out + p.p2, II * dd, II * 32, 0, stream));
-    ALLOCMOE_TRY(launch_pack_gate(w->Wg, desc->shared_gate ? w->w_sg : nullptr, d, E, out + p.gate,
-                                  stream));
+    PackJobs jobs{};
+    jobs.job[0] = {w->W1, E, d, I, out + p.p13, 2 * dd * II, 2 * dd * 32, 0, 0};
+    jobs.job[1] = {w->W3, E, d, I, out + p.p13, 2 * dd * II, 2 * dd * 32, dd * 32, 0};
+    jobs.job[2] = {w->W2, E, I, d, out + p.p2, II * dd, II * 32, 0, 0};
+    jobs.n = 3;
     if (Is) {
         const size_t SS = Is;
-        ALLOCMOE_TRY(launch_pack_b(w->Ws1, 1, d, Is, out + p.ps13, 2 * dd * SS, 2 * dd * 32, 0, stream));
-        ALLOCMOE_TRY(launch_pack_b(w->Ws3, 1, d, Is, out + p.ps13, 2 * dd * SS, 2 * dd * 32, dd * 32, stream));
-        ALLOCMOE_TRY(launch_pack_b(w->Ws2, 1, Is, d, out + p.ps2, SS * dd, SS * 32, 0, stream));
+        jobs.job[3] = {w->Ws1, 1, d, Is, out + p.ps13, 2 * dd * SS, 2 * dd * 32, 0, 0};
+        jobs.job[4] = {w->Ws3, 1, d, Is, out + p.ps13, 2 * dd * SS, 2 * dd * 32, dd * 32, 0};
+        jobs.job[5] = {w->Ws2, 1, Is, d, out + p.ps2, SS * dd, SS * 32, 0, 0};
+        jobs.n = 6;
     }
+    ALLOCMOE_TRY(launch_pack_b(jobs, stream));
+    ALLOCMOE_TRY(launch_pack_gate(w->Wg, desc->shared_gate ? w->w_sg : nullptr, d, E, out + p.gate,
+                                  stream));
     return ALLOCMOE_OK;
 }
 

@@ -143,9 +143,20 @@ struct PackFp8Jobs {
     int n;
 };
 hipError_t launch_pack_fp8(PackFp8Jobs jobs, hipStream_t stream);
-hipError_t launch_pack_b(const void* W, int G, int Kd, int N, void* out,
-                         size_t group_stride_elems, size_t nblock_stride_elems,
-                         size_t base_off_elems, hipStream_t stream);
+// bf16 fragments of 16 k x 32 n, the layout at the head of pack.hip; strides and offset in
+// elements.  Up to six matrices [G][Kd][N] in one launch; Kd and N multiples of 64.
+struct PackJob {
+    const void* W;
+    int G, Kd, N;
+    void* out;
+    size_t group_stride, nblock_stride, base_off;
+    int64_t n_wg;   // filled by the launcher
+};
+struct PackJobs {
+    PackJob job[6];
+    int n;
+};
+hipError_t launch_pack_b(PackJobs jobs, hipStream_t stream);
 
 // ---- stats.hip : routing analytics; metrics: 5 floats (see allocmoe_routing_metrics)
 hipError_t launch_routing_stats(const float* scores, const int32_t* topk_ids, const float* topk_s,
