@@ -57,11 +57,12 @@ __global__ __launch_bounds__(256) void pack_b_kernel(PackJobs jobs) {
 // E4M3 of the OCP 8-bit floating point format: sign, 4 exponent bits (bias 7), 3 mantissa
 // bits, subnormals, no infinities, largest finite magnitude 448.  Nearest code, ties to
 // the even mantissa, magnitudes above 448 saturate: the conversion unit's rounding, on
-// values that were clamped before.  Byte i of the result = code of y[i].
+// values that were clamped before.  A NaN saturates too, with its sign (the minimum passes
+// over it).  Byte i of the result = code of y[i].
 __device__ __forceinline__ uint32_t e4m3_encode4(const float (&y)[4]) {
     float c[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) c[i] = __builtin_amdgcn_fmed3f(y[i], -448.f, 448.f);
+    for (int i = 0; i < 4; ++i) c[i] = copysignf(fminf(fabsf(y[i]), 448.f), y[i]);
     int w = __builtin_amdgcn_cvt_pk_fp8_f32(c[0], c[1], 0, false);
     w = __builtin_amdgcn_cvt_pk_fp8_f32(c[2], c[3], w, true);
     return static_cast<uint32_t>(w);
@@ -90,7 +91,7 @@ __global__ __launch_bounds__(kPackWaves* kWave) void pack_fp8_kernel(PackFp8Jobs
     const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
     const int t = lane % 16, kb = wave * 4 + lane / 16;
     const bf16_t* src = static_cast<const bf16_t*>(J.W) + static_cast<size_t>(g) * Kd * N + n0 + 4 * t;
-    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
     // (a matrix may start at any element)
     typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
     u32x2_any v[32];
@@ -100,28 +101,31 @@ __global__ __launch_bounds__(kPackWaves* kWave) void pack_fp8_kernel(PackFp8Jobs
         for (int r = 0; r < 32; ++r)
             v[r] = __builtin_nontemporal_load(reinterpret_cast<const u32x2_any*>(p + static_cast<size_t>(r) * N));
     };
-    // magnitudes of bf16 values compare like their bit patterns
-    u16x2 m[2] = {u16x2{0, 0}, u16x2{0, 0}};
+    // Magnitudes of bf16 values compare like their bit patterns.  A NaN must not count (its
+    // pattern is above infinity's and would be the maximum): with 0x7F added the patterns up
+    // to infinity's (0x7F80) stay below 0x8000, those of NaNs become negative.
+    constexpr int16_t kShift = 0x7F;
+    i16x2 m[2] = {i16x2{kShift, kShift}, i16x2{kShift, kShift}};
     for (int c = 0; c < Kd; c += kPackRows) {
         load(c + kb * 32);
 #pragma unroll
         for (int r = 0; r < 32; ++r)
 #pragma unroll
             for (int h = 0; h < 2; ++h)
-                m[h] = __builtin_elementwise_max(m[h], __builtin_bit_cast(u16x2, v[r][h] & 0x7FFF7FFFu));
+                m[h] = __builtin_elementwise_max(m[h], __builtin_bit_cast(i16x2, (v[r][h] & 0x7FFF7FFFu) + kShift * 0x10001u));
     }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {   // over the lanes with the same columns
-        m[h] = __builtin_elementwise_max(m[h], __builtin_bit_cast(u16x2, lane_xor<16>(__builtin_bit_cast(uint32_t, m[h]))));
-        m[h] = __builtin_elementwise_max(m[h], __builtin_bit_cast(u16x2, lane_xor<32>(__builtin_bit_cast(uint32_t, m[h]))));
+        m[h] = __builtin_elementwise_max(m[h], __builtin_bit_cast(i16x2, lane_xor<16>(__builtin_bit_cast(uint32_t, m[h]))));
+        m[h] = __builtin_elementwise_max(m[h], __builtin_bit_cast(i16x2, lane_xor<32>(__builtin_bit_cast(uint32_t, m[h]))));
         if (lane < 16) wave_max[wave][2 * t + h] = __builtin_bit_cast(uint32_t, m[h]);
     }
     __syncthreads();
     if (tid < kPackCols) {
-        uint32_t top = 0;
+        uint32_t top = kShift;
 #pragma unroll
         for (int w = 0; w < kPackWaves; ++w) top = max(top, (wave_max[w][tid / 2] >> (16 * (tid % 2))) & 0xFFFFu);
-        const float amax = __uint_as_float(top << 16);
+        const float amax = __uint_as_float((top - kShift) << 16);
         const float sc = amax > 0.f ? __fdiv_rn(amax, 448.f) : 1.f;
         col_scale[tid] = sc;
         J.scale[static_cast<size_t>(g) * J.scale_stride + n0 + tid] = sc;
