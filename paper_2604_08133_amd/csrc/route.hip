@@ -2,7 +2,7 @@
 // Eq. (6)): logits = x W_gate (+bias), softmax over all E experts, then each
 // token's K largest scores in descending order (ties: lower expert id).
 //
-// Layout: one lane per expert (E <= 64).  A workgroup of kRouteWaves waves owns kRouteTok
+// Layout: one lane per expert (E <= 64).  A workgroup of WAVES waves owns kRouteTok
 // tokens; the waves split the hidden dimension, each lane accumulating the
 // logit of its expert, and the partial sums meet in LDS in a fixed order.
 #include "common.hpp"
@@ -11,9 +11,6 @@
 namespace allocmoe {
 
 constexpr int kRouteTok = 4;    // tokens per workgroup
-// waves per workgroup, splitting d: the kernel is a chain of loads of the gate matrix, a
-// few workgroups per compute unit at most, so each wave's share is kept to a chunk or two
-constexpr int kRouteWaves = 16;
 constexpr int kRouteBatch = 16;   // rows of the gate matrix loaded together
 
 // Sorted Top-K of N tokens' scores at once, lane = expert: larger score first, equal
@@ -56,13 +53,13 @@ __device__ __forceinline__ void wave_topk_store(float score, bool valid, int K,
     wave_topk_store_n<1>(sc, valid, K, ids, ss, live);
 }
 
-template <typename TIn>
-__global__ __launch_bounds__(kRouteWaves* kWave) void route_kernel(
+template <typename TIn, int WAVES>
+__global__ __launch_bounds__(WAVES* kWave) void route_kernel(
     const TIn* __restrict__ X, const TIn* __restrict__ Wg, const float* __restrict__ bias,
     const TIn* __restrict__ w_sg, int T, int d, int E, int K, float* __restrict__ scores,
     int32_t* __restrict__ topk_ids, float* __restrict__ topk_s, float* __restrict__ sgate) {
-    __shared__ float part[kRouteWaves][kRouteTok][kWave];
-    __shared__ float gpart[kRouteWaves][kRouteTok];
+    __shared__ float part[WAVES][kRouteTok][kWave];
+    __shared__ float gpart[WAVES][kRouteTok];
 
     const int lane = lane_id();
     const int wave = threadIdx.x / kWave;
@@ -70,7 +67,7 @@ __global__ __launch_bounds__(kRouteWaves* kWave) void route_kernel(
 
     // this wave's slice of the hidden dimension, in chunks of 64
     const int chunks = (d + kWave - 1) / kWave;
-    const int per_wave = (chunks + kRouteWaves - 1) / kRouteWaves;
+    const int per_wave = (chunks + WAVES - 1) / WAVES;
     const int c_begin = wave * per_wave;
     const int c_end = min(chunks, c_begin + per_wave);
 
@@ -124,12 +121,12 @@ __global__ __launch_bounds__(kRouteWaves* kWave) void route_kernel(
     __syncthreads();
 
     // wave q finishes token t0 + q
-    for (int q = wave; q < kRouteTok; q += kRouteWaves) {
+    for (int q = wave; q < kRouteTok; q += WAVES) {
         const int t = t0 + q;
         if (t >= T) continue;
         float logit = 0.f;
 #pragma unroll
-        for (int w = 0; w < kRouteWaves; ++w) logit += part[w][q][lane];
+        for (int w = 0; w < WAVES; ++w) logit += part[w][q][lane];
         if (bias != nullptr && lane_is_expert) logit += bias[lane];
         if (!lane_is_expert) logit = -INFINITY;
         const float m = wave_max(logit);
@@ -142,7 +139,7 @@ __global__ __launch_bounds__(kRouteWaves* kWave) void route_kernel(
         if (w_sg != nullptr && lane == 0) {
             float g = 0.f;
 #pragma unroll
-            for (int w = 0; w < kRouteWaves; ++w) g += gpart[w][q];
+            for (int w = 0; w < WAVES; ++w) g += gpart[w][q];
             sgate[t] = 1.f / (1.f + expf(-g));
         }
     }
@@ -344,21 +341,35 @@ __global__ __launch_bounds__(256) void topk_from_scores_kernel(
                     topk_s + static_cast<size_t>(t) * K);
 }
 
+namespace {
+
+template <typename TIn, int WAVES>
+void enqueue_route(const void* X, const void* Wg, const float* bias, const void* w_sg, int T, int d,
+                   int E, int K, float* scores, int32_t* topk_ids, float* topk_s, float* sgate,
+                   hipStream_t stream) {
+    hipLaunchKernelGGL((route_kernel<TIn, WAVES>), dim3((T + kRouteTok - 1) / kRouteTok),
+                       dim3(WAVES * kWave), 0, stream, static_cast<const TIn*>(X),
+                       static_cast<const TIn*>(Wg), bias, static_cast<const TIn*>(w_sg), T, d, E, K,
+                       scores, topk_ids, topk_s, sgate);
+}
+
+}  // namespace
+
 hipError_t launch_route(int dtype, const void* X, const void* Wg, const float* bias,
                         const void* w_sg, int T, int d, int E, int K, float* scores,
                         int32_t* topk_ids, float* topk_s, float* sgate, hipStream_t stream) {
-    const dim3 grid((T + kRouteTok - 1) / kRouteTok), block(kRouteWaves * kWave);
-    if (dtype == 0) {
-        hipLaunchKernelGGL(route_kernel<float>, grid, block, 0, stream,
-                           static_cast<const float*>(X), static_cast<const float*>(Wg), bias,
-                           static_cast<const float*>(w_sg), T, d, E, K, scores, topk_ids, topk_s,
-                           sgate);
-    } else {
-        hipLaunchKernelGGL(route_kernel<bf16_t>, grid, block, 0, stream,
-                           static_cast<const bf16_t*>(X), static_cast<const bf16_t*>(Wg), bias,
-                           static_cast<const bf16_t*>(w_sg), T, d, E, K, scores, topk_ids,
-                           topk_s, sgate);
-    }
+    // Waves per workgroup, splitting d.  Few tokens are a chain of loads of the gate matrix: 16
+    // waves keep a wave's share of it to a chunk or two (16 tokens, d 2048: 4 waves 30.0 us, 16
+    // waves 19.4; d 384: 11.9, 9.6).  From four chunks of 64 down 4 waves hold one each and the
+    // others would have nothing to do but fill the compute unit (d 128: 1 token 7.7 both, 8192
+    // tokens 34.0 and 44.7).  With many tokens the short chains of several small workgroups
+    // overlap (d 512: 4096 tokens 35.7 and 35.9, 8192: 52.9 and 54.1, 65536: 249 and 316; d
+    // 2048: 8192 tokens 130 and 126, 65536: 830 and 842).  (A launch has less than 2^32 threads:
+    // 16 waves end at 2^24 tokens, 4 at 2^26.)
+    const bool many = d > 4 * kWave && T < (d <= 12 * kWave ? 8192 : 65536);
+    const auto enqueue = dtype == 0 ? (many ? enqueue_route<float, 16> : enqueue_route<float, 4>)
+                                    : (many ? enqueue_route<bf16_t, 16> : enqueue_route<bf16_t, 4>);
+    enqueue(X, Wg, bias, w_sg, T, d, E, K, scores, topk_ids, topk_s, sgate, stream);
     return hipGetLastError();
 }
 
