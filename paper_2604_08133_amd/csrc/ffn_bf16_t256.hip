@@ -24,20 +24,25 @@ constexpr int kXcds = 8;                // accelerator dies (one L2 each) of an 
 // DeepSeek-V2-Lite shapes, targets of 64 to 192 workgroups differ by < 2 %, 256 and
 // more lose 1-5 % from 2048 tokens on; against fixed 256-row tiles the step is 4-6 %
 // shorter at 128-512 tokens with bf16 weights, 9-13 % with 8-bit weights.
-int dense_tile_rows(int M, int col_tiles) {
+//
+// Where the target is met (short tiles, less than one round) the group also takes the deeper
+// weight rings; above it they crowd the memory system (300 tokens, shared expert of 22528 on
+// 2048, 176 column tiles in the first half: layer 325 us, 332 with them).
+void lay_out_dense(StreamGroup& g, int col_tiles) {
     constexpr int kTargetWorkgroups = 128;
+    auto workgroups = [&](int h) { return static_cast<int64_t>((g.M_dense + h - 1) / h) * col_tiles; };
     int h = 32;
-    while (h < kRows && static_cast<int64_t>((M + h - 1) / h) * col_tiles > kTargetWorkgroups) h += 32;
-    return h;
+    while (h < kRows && workgroups(h) > kTargetWorkgroups) h += 32;
+    g.dense_rows = h;
+    g.deep_ring = workgroups(h) <= kTargetWorkgroups;
 }
 
 hipError_t launch_ffn_bf16_t256(bool swiglu, StreamGroup routed, StreamGroup shared,
                                 hipStream_t stream) {
     const int cols = swiglu ? 128 : 256;
     auto col_tiles = [cols](const StreamGroup& g) { return (g.N + cols - 1) / cols; };
-    if (routed.A != nullptr && routed.tile_info == nullptr)
-        routed.dense_rows = dense_tile_rows(routed.M_dense, col_tiles(routed));
-    if (shared.A != nullptr) shared.dense_rows = dense_tile_rows(shared.M_dense, col_tiles(shared));
+    if (routed.A != nullptr && routed.tile_info == nullptr) lay_out_dense(routed, col_tiles(routed));
+    if (shared.A != nullptr) lay_out_dense(shared, col_tiles(shared));
     // items per XCD; for the routed group an upper bound (the real tile count is
     // known on the device only)
     int64_t per_xcd = 0;

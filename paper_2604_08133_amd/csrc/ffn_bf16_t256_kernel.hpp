@@ -62,9 +62,8 @@ constexpr int kXcds = 8;                // accelerator dies (one L2 each) of an 
 // 64 experts: 327.5 against 329 us and 223 against 225 us a layer), full tiles need the
 // longer one (8192 tokens, skewed experts: 729 us, 760 us with the shorter ring everywhere).
 constexpr int ring_steps(int row_blocks16, bool fp8) { return !fp8 && row_blocks16 <= 8 ? 4 : 8; }
-constexpr int kRingDeep = 12;           // bf16, the light tiles
+constexpr int kRingDeep = 12;           // bf16, tiles of up to 64 rows: the light ones, dense groups of few workgroups
 constexpr int kLightRowBlocks = 2;
-
 
 // 8 rows x 128 B of activations, global -> LDS directly: lane l's 16 bytes land
 // at M0 + 16 l (M0 holds the wave-uniform LDS base; one other instruction has to stand
@@ -585,7 +584,7 @@ __global__ __launch_bounds__(kWaves* kWave, 1) void ffn_bf16_t256_kernel(StreamG
     }
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int n_f = (rows + 15) / 16;   // 16-row blocks that hold real rows
-    const bool deep_ring = tile_info != nullptr && only_tile && light_class_of(tile_info, FP8) > 0;
+    const bool deep_ring = g.deep_ring || (tile_info != nullptr && only_tile && light_class_of(tile_info, FP8) > 0);
     const int KT = Kd / kStepK;
 
     // B: the two fragment streams of this wave's 64 weight columns; a stream is
@@ -615,7 +614,11 @@ __global__ __launch_bounds__(kWaves* kWave, 1) void ffn_bf16_t256_kernel(StreamG
     // The deeper weight ring is for light tiles that run among matrix-bound ones; where
     // most tiles are light (few tokens) the launch as a whole is bound by the memory
     // system, which more loads in flight per unit only crowd (measured: +3 % step time at
-    // 256 tokens, +17 % on a layer whose experts all hold 128 rows).
+    // 256 tokens, +17 % on a layer whose experts all hold 128 rows).  A dense group of few
+    // workgroups (StreamGroup::deep_ring) has no such crowd either: a workgroup is alone with
+    // the latency of its long weight streams.  Shared expert of 16384 on 512, 130 tokens (10
+    // workgroups of 32 rows in the second half): layer 146 us with the short ring, 135 with the
+    // longer ones; 22528 on 2048: 221, 209; 300 tokens, 16384 on 1024 (one round): 163, 155.
 #define ALLOCMOE_T256_BODY(n, ring)                                                                 \
     do {                                                                                            \
         if (only_tile)                                                                              \
@@ -632,8 +635,13 @@ __global__ __launch_bounds__(kWaves* kWave, 1) void ffn_bf16_t256_kernel(StreamG
                 ALLOCMOE_T256_BODY(n, kRingDeep);                                                   \
                 break;                                                                              \
             }                                                                                       \
+        } else if constexpr (!FP8 && ring_steps(n, FP8) < 8) {                                      \
+            if (g.deep_ring) {                                                                      \
+                ALLOCMOE_T256_BODY(n, 8);                                                           \
+                break;                                                                              \
+            }                                                                                       \
         }                                                                                           \
-        ALLOCMOE_T256_BODY(n, ring_steps(n, FP8));                                                               \
+        ALLOCMOE_T256_BODY(n, ring_steps(n, FP8));                                                  \
         break;
     switch (n_f) {   // uniform over the workgroup
         ALLOCMOE_T256_CASE(1)
