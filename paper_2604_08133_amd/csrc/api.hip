@@ -3,6 +3,7 @@
 // allocates, synchronises or copies to the host.
 #include "../../include/allocmoe.h"
 
+#include "choice.hpp"
 #include "kernels.hpp"
 
 #include <algorithm>
@@ -470,53 +471,22 @@ allocmoe_status forward_impl(const allocmoe_layer_desc* desc, const void* X,
     void* O = base + L.O;
     void* Os = Is ? base + L.Os : nullptr;
 
-    // Kernel choice for step 5 (bf16), from the descriptor alone: the register-blocked tile
-    // kernel (256-row tiles) or the weight-streaming kernel (32-row tiles).
-    //
-    // Large layers (kLargeWeights or kLargeFlops) decide per group: the routed experts are
-    // tiled from about eight rows each on, the shared expert from about 128 tokens on.
-    // Measured on DeepSeek-V2-Lite shapes the two kernels cross between 6 and 9 rows per
-    // expert for the routed group (B = 6E: 174 us a step streaming, 182 tiled; B = 9E: 200
-    // against 193; B = 12E: 227 against 201).
-    //
-    // Smaller layers run both groups on one kernel, in one launch per half: a fork and join
-    // of two streams costs 10-20 us there and two launches behind each other 6-20 us (320 x
-    // 192, 32 experts, 300 tokens: one launch 33 us streaming, 38 tiled, side stream 51;
-    // 1088 x 704, 777 tokens: 117, 82, 83; 1472 x 1344, 64 experts, 300 and 1600 tokens: 174,
-    // 161, 170 and 494, 209, 201).  Tiled where the experts see ten rows or more on average
-    // (8 rows, 64 experts of 1472 x 1344: 143 us streaming, 149 tiled; 11.5: 172, 163) and the
-    // work covers the tile kernel's longer start and end.  With more than 32 rows an expert's
-    // weights are streamed more than once, and the tile kernel wins earlier:
-    //   32 and more rows: 1.9 GFLOP 54 us streaming, 56 tiled; 3.4: 60, 57; 3.7: 58, 51;
-    //                     4.9: 69, 59; 11: 94, 69
-    //   fewer:            2.1: 57, 56; 2.6: 47, 58; 4.2: 66, 63 and 62, 67; 11: 174, 161
-    constexpr int64_t kRoutedTiledRowsPerExpert = 8;
-    constexpr int kSharedTiledTokens = 128;
-    constexpr int64_t kSmallTiledRowsPerExpert = 10;
-    constexpr double kLargeWeights = 4e8, kLargeFlops = 4e10;
-    constexpr double kTiledFlops = 4.5e9, kTiledFlopsManyRows = 3e9;
-    // Both kernels read bf16 or 8-bit weights (one format per layer).
+    // Kernel and stream of step 5 (bf16), from the descriptor alone (choice.hpp); both kernels
+    // read bf16 or 8-bit weights (one format per layer).
     const bool fp8 = fp8_of(desc);
-    const double flops = 6.0 * d * (static_cast<double>(B) * I + static_cast<double>(T) * Is);
-    const bool large = 3.0 * d * (static_cast<double>(E) * I + Is) >= kLargeWeights || flops >= kLargeFlops;
-    bool routed_tiled = bf16 && B >= kRoutedTiledRowsPerExpert * static_cast<int64_t>(E);
-    bool shared_tiled = bf16 && T >= kSharedTiledTokens;
-    if (bf16 && !large) {
-        const int64_t rows = B + (Is > 0 ? T : 0), experts = (B > 0 ? E : 0) + (Is > 0 ? 1 : 0);
-        routed_tiled = shared_tiled = rows >= kSmallTiledRowsPerExpert * experts &&
-                                      flops >= (rows >= 32 * experts ? kTiledFlopsManyRows : kTiledFlops);
-    }
+    const FfnChoice choice = bf16 ? choose_ffn(T, d, E, I, Is, B) : FfnChoice{};
+    const bool routed_tiled = choice.routed_tiled, shared_tiled = choice.shared_tiled;
     const int bm = routed_tiled ? kTileRowsLarge : kTileRowsSmall;
     const int64_t max_tiles = max_tiles_for(desc, bm);
-    // The shared expert depends on nothing but X.  Where a group of a large layer uses the
-    // tile kernel (prefill shapes), the shared expert's two GEMMs run on a side stream beside
-    // selection and the routed experts' GEMMs, and the streams meet again before the
+    // The shared expert depends on nothing but X.  On a stream of its own (large layers where a
+    // group uses the tile kernel, smaller ones that are mostly shared expert) its two GEMMs run
+    // beside selection and the routed experts' GEMMs, and the streams meet again before the
     // combine: the side stream starts after the routing kernel and the
     // single-workgroup plan kernel is enqueued first, so that it gets a compute unit
     // at once.  Decode shapes (both groups on the weight-streaming kernel) keep one
     // stream and one launch per half for both groups: there the two event waits of a
     // fork and join cost more than the overlap gains.
-    const bool overlap = large && bf16 && Is > 0 && B > 0 && (routed_tiled || shared_tiled);
+    const bool overlap = choice.own_stream;
     struct { hipStream_t stream; hipEvent_t fork, join; } side_{}, *side = &side_;
     StreamGroup s1, s2;   // the shared expert's two GEMMs
     if (bf16 && Is) {

@@ -1,0 +1,43 @@
+"""Kernel and stream of the bf16 expert networks: both sides of every limit of the rule."""
+import pytest
+
+from tests.ffn_choice import choose
+
+STREAMING, TILED = (False, False, False), (True, True, False)
+BESIDE, BESIDE_TILED, BESIDE_STREAMING = (False, True, True), (True, True, True), (True, False, True)
+
+
+@pytest.mark.parametrize("below,above,sizes", [
+    # 4e8 weights: 9.4 rows an expert are tiled in a large layer only
+    (STREAMING, (True, False, False), [(100, 1024, 64, 2034, 0, 600), (100, 1024, 64, 2035, 0, 600)]),
+    # 40 GFLOP: the shared expert goes to its own stream
+    (TILED, BESIDE_TILED, [(1000, 1024, 64, 1024, 1024, 5357), (1000, 1024, 64, 1024, 1024, 5358)]),
+    # large: 8 rows an expert; 128 tokens
+    (STREAMING, BESIDE_STREAMING, [(100, 2048, 64, 1408, 2816, 511), (100, 2048, 64, 1408, 2816, 512)]),
+    (STREAMING, BESIDE, [(127, 2048, 64, 1408, 2816, 300), (128, 2048, 64, 1408, 2816, 300)]),
+    # smaller: 10 rows an expert
+    (STREAMING, TILED, [(200, 1472, 64, 1344, 0, 639), (200, 1472, 64, 1344, 0, 640)]),
+    # 4.5 GFLOP below 48 rows an expert, 3 GFLOP from there
+    (STREAMING, TILED, [(100, 1024, 8, 4096, 0, 178), (100, 1024, 8, 4096, 0, 179)]),
+    (STREAMING, TILED, [(200, 1024, 4, 1024, 0, 476), (200, 1024, 4, 1024, 0, 477)]),
+    (STREAMING, TILED, [(200, 1024, 8, 1536, 0, 383), (200, 1024, 8, 1536, 0, 384)]),
+    # a wide shared expert over sparse experts: 7 GFLOP of its own; 128 tokens
+    (STREAMING, TILED, [(278, 1024, 64, 256, 4096, 75), (279, 1024, 64, 256, 4096, 75)]),
+    (STREAMING, TILED, [(127, 1024, 64, 256, 9024, 75), (128, 1024, 64, 256, 9024, 75)]),
+    # 16 GFLOP, ten times the routed experts': its own stream, the routed experts tiled from 8 rows on
+    (TILED, BESIDE, [(317, 1024, 64, 256, 8192, 75), (318, 1024, 64, 256, 8192, 75)]),
+    (TILED, BESIDE_TILED, [(400, 1024, 64, 256, 8192, 1281), (400, 1024, 64, 256, 8192, 1280)]),
+    (BESIDE, BESIDE_TILED, [(400, 1024, 64, 256, 8192, 511), (400, 1024, 64, 256, 8192, 512)]),
+    # fewer than 160 tokens, more than half of the work: streaming
+    (STREAMING, TILED, [(159, 1024, 8, 1024, 4096, 300), (160, 1024, 8, 1024, 4096, 300)]),
+    (STREAMING, TILED, [(100, 1024, 8, 1024, 4096, 399), (100, 1024, 8, 1024, 4096, 400)]),
+])
+def test_both_sides_of_every_limit(below, above, sizes):
+    assert [choose(*s) for s in sizes] == [below, above]
+
+
+def test_a_layer_without_one_of_the_groups_has_one_stream():
+    for T in (1, 40, 130, 1000, 16384):
+        for Is, B in ((0, 6 * T), (0, T), (2816, 0), (45056, 0)):
+            assert not choose(T, 2048, 64, 1408, Is, B)[2]
+            assert not choose(T, 512, 16, 512, Is, B)[2]
