@@ -67,18 +67,27 @@ constexpr int kLightRowBlocks = 2;
 
 // 8 rows x 128 B of activations, global -> LDS directly: lane l's 16 bytes land
 // at M0 + 16 l (M0 holds the wave-uniform LDS base; one other instruction has to stand
-// between writing M0 and the load that reads it: an MFMA, see the callers).  Written as
+// between writing M0 and the load that reads it: an MFMA, see the callers).  The base
+// travels from the one to the other as a value that lives in M0: whatever the compiler
+// might put there in between, it would have to put the base back.  (It does not see an MFMA
+// written as asm as that other instruction: the loop has the address computation there too,
+// so that it adds no idle state.)  Written as
 // asm, hidden from the compiler's wait-count insertion: it treats a direct-to-LDS load as
 // touching both memory paths and then drains *all* outstanding loads (vmcnt(0)) at the
 // next use of any loaded register, which would serialise the weight prefetch.
 // Hidden, these loads still count in vmcnt, in issue order: every wait the
 // compiler emits for a weight register is then stricter than needed, never
 // weaker, and the waits for the slots themselves are written by hand.
-__device__ __forceinline__ void set_lds_base(uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %0" : : "s"(lds_addr) : "memory", "m0");
+struct LdsBase {
+    uint32_t m0;
+};
+__device__ __forceinline__ LdsBase set_lds_base(uint32_t lds_addr) {
+    LdsBase b;
+    asm volatile("s_mov_b32 %0, %1" : "={m0}"(b.m0) : "s"(lds_addr) : "memory");
+    return b;
 }
-__device__ __forceinline__ void load_rows_to_lds(const bf16x8* g) {
-    asm volatile("global_load_lds_dwordx4 %0, off" : : "v"(g) : "memory");
+__device__ __forceinline__ void load_rows_to_lds(const bf16x8* g, LdsBase b) {
+    asm volatile("global_load_lds_dwordx4 %0, off" : : "v"(g), "{m0}"(b.m0) : "memory");
 }
 
 // Workgroup barrier without the memory fence of __syncthreads(): the fence
@@ -278,9 +287,9 @@ __device__ __forceinline__ void t256_body(char* lds, const bf16_t* A, size_t lda
     auto issue_slot = [&](int s, int slot) {
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
-            set_lds_base(lds_wave + slot * kSlotBytes + i * 4096);
+            const LdsBase base = set_lds_base(lds_wave + slot * kSlotBytes + i * 4096);
             asm volatile("s_nop 0");
-            load_rows_to_lds(arow[i] + s * (kStepK / 8));
+            load_rows_to_lds(arow[i] + s * (kStepK / 8), base);
         }
     };
     issue_slot(0, 0);
@@ -308,6 +317,7 @@ __device__ __forceinline__ void t256_body(char* lds, const bf16_t* A, size_t lda
         const int next_f0 = odd ? 0 : NE;
         const int far = min(s + 2, KT - 1) * (kStepK / 8), far_slot = (slot + 2) & 3;
         const bf16x8* p[NL];
+        LdsBase base[NL];
         // instruction t of cnt, spread over the step, `off` MFMAs behind its share's start
         auto due = [&](int n, int t, int cnt, int off) {
             return NM == 0 ? true : n == min(NM - 1, t * NM / cnt + off);
@@ -329,9 +339,9 @@ __device__ __forceinline__ void t256_body(char* lds, const bf16_t* A, size_t lda
             if (kc == 0) {
 #pragma unroll
                 for (int i = 0; i < NL; ++i) {
-                    if (due(n, i, NL, 1)) p[i] = arow[i] + far;
-                    if (due(n, i, NL, 2)) set_lds_base(lds_wave + far_slot * kSlotBytes + i * 4096);
-                    if (due(n, i, NL, 3)) load_rows_to_lds(p[i]);
+                    if (due(n, i, NL, 1)) base[i] = set_lds_base(lds_wave + far_slot * kSlotBytes + i * 4096);
+                    if (due(n, i, NL, 2)) p[i] = arow[i] + far;
+                    if (due(n, i, NL, 3)) load_rows_to_lds(p[i], base[i]);
                 }
             }
         };
