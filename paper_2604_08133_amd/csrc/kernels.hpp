@@ -129,7 +129,8 @@ hipError_t launch_ffn_bf16_t256(bool swiglu, StreamGroup routed, StreamGroup sha
 // k = 32 kb + 16 + 8 (l/32) + i in bytes 8 + i, column 32 nb + l%32.  Destination of
 // fragment (g, nb, kb): out + g*group_stride + nb*nblock_stride + base_off + kb*1024
 // (bytes).  scale[g*scale_stride + n].
-// Up to six matrices [G][Kd][N] in one launch; Kd and N multiples of 128.
+// Up to six matrices [G][Kd][N] in one launch (where it can hold them); Kd and N multiples of
+// 128.
 struct PackFp8Job {
     const void* W;
     int G, Kd, N;
@@ -142,10 +143,12 @@ struct PackFp8Job {
 struct PackFp8Jobs {
     PackFp8Job job[6];
     int n;
+    int first_strip;   // of this launch (filled by the launcher)
 };
 hipError_t launch_pack_fp8(PackFp8Jobs jobs, hipStream_t stream);
 // bf16 fragments of 16 k x 32 n, the layout at the head of pack.hip; strides and offset in
-// elements.  Up to six matrices [G][Kd][N] in one launch; Kd and N multiples of 64.
+// elements.  Up to six matrices [G][Kd][N] in one launch (where it can hold them); Kd and N
+// multiples of 64.
 struct PackJob {
     const void* W;
     int G, Kd, N;
@@ -156,6 +159,7 @@ struct PackJob {
 struct PackJobs {
     PackJob job[6];
     int n;
+    int64_t first_wg;   // of this launch (filled by the launcher)
 };
 hipError_t launch_pack_b(PackJobs jobs, hipStream_t stream);
 

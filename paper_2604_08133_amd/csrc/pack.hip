@@ -7,6 +7,7 @@
 // stored as 64 lanes x 16 bytes = 1 KB.  The fragments of one column block nb
 // are contiguous along k (kb = 0 .. Kd/16-1).  Destination of fragment
 // (g, nb, kb):  out + g*group_stride + nb*nblock_stride + base_off + kb*512.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.hpp"
@@ -23,7 +24,7 @@ namespace allocmoe {
 // 16 experts of 576 x 320 took 17.4 us instead of 12.8, 32 experts of 1088 x 704 and a shared
 // expert 80.6 instead of 69.6.
 __global__ __launch_bounds__(256) void pack_b_kernel(PackJobs jobs) {
-    int64_t bid = blockIdx.x;
+    int64_t bid = jobs.first_wg + blockIdx.x;
     int jn = 0;
     while (bid >= jobs.job[jn].n_wg) bid -= jobs.job[jn++].n_wg;
     const PackJob& J = jobs.job[jn];
@@ -83,7 +84,7 @@ constexpr int kPackWaves = 16, kPackRows = kPackWaves * 4 * 32, kPackCols = 64;
 __global__ __launch_bounds__(kPackWaves* kWave) void pack_fp8_kernel(PackFp8Jobs jobs) {
     __shared__ uint32_t wave_max[kPackWaves][kPackCols / 2];   // two columns' magnitudes each
     __shared__ float col_scale[kPackCols];
-    int bid = blockIdx.x, jn = 0;
+    int bid = jobs.first_strip + blockIdx.x, jn = 0;
     while (bid >= jobs.job[jn].n_strips) bid -= jobs.job[jn++].n_strips;
     const PackFp8Job& J = jobs.job[jn];
     const int N = J.N, Kd = J.Kd, strips = N / kPackCols;
@@ -193,9 +194,12 @@ hipError_t launch_pack_fp8(PackFp8Jobs jobs, hipStream_t stream) {
         J.n_strips = J.G * (J.N / kPackCols);
         strips += J.n_strips;
     }
-    if (strips == 0) return hipSuccess;
-    hipLaunchKernelGGL(pack_fp8_kernel, dim3(static_cast<unsigned>(strips)), dim3(kPackWaves * kWave), 0,
-                       stream, jobs);
+    constexpr int64_t kMaxStrips = (1ll << 32) / (kPackWaves * kWave) - 1;   // threads of a launch: 2^32 - 1
+    for (int64_t first = 0; first < strips; first += kMaxStrips) {
+        jobs.first_strip = static_cast<int>(first);
+        hipLaunchKernelGGL(pack_fp8_kernel, dim3(static_cast<unsigned>(std::min(kMaxStrips, strips - first))),
+                           dim3(kPackWaves * kWave), 0, stream, jobs);
+    }
     return hipGetLastError();
 }
 
@@ -206,8 +210,11 @@ hipError_t launch_pack_b(PackJobs jobs, hipStream_t stream) {
         J.n_wg = (static_cast<int64_t>(J.G) * (J.N / 32) * (J.Kd / 16) * kWave + 255) / 256;
         wgs += J.n_wg;
     }
-    if (wgs == 0) return hipSuccess;
-    hipLaunchKernelGGL(pack_b_kernel, dim3(static_cast<unsigned>(wgs)), dim3(256), 0, stream, jobs);
+    // a launch has less than 2^32 threads: layers of 3.4e10 weights take a second one
+    constexpr int64_t kMaxWg = (1ll << 32) / 256 - 1;
+    for (jobs.first_wg = 0; jobs.first_wg < wgs; jobs.first_wg += kMaxWg)
+        hipLaunchKernelGGL(pack_b_kernel, dim3(static_cast<unsigned>(std::min(kMaxWg, wgs - jobs.first_wg))),
+                           dim3(256), 0, stream, jobs);
     return hipGetLastError();
 }
 

@@ -1,0 +1,62 @@
+"""Work that is more than one launch can hold (2^32 threads): nothing is left undone.  Inputs are
+shared or repeated where that saves memory; results are checked where a short launch would end."""
+import gc
+
+import pytest
+import torch
+
+from paper_2604_08133_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def need(gigabytes):
+    gc.collect()
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < gigabytes * 1e9:
+        pytest.skip(f"needs {gigabytes} GB of device memory")
+
+
+def test_bf16_packing_of_a_very_large_layer():
+    # 3.87e10 weights, 8 per thread; the matrices in between fit a launch each
+    need(115)
+    E, d, I = 64, 12288, 16384
+    W = torch.empty(E * d * I, dtype=torch.int16, device="cuda").random_()
+    Wg = torch.zeros((d, E), dtype=torch.bfloat16, device="cuda")
+    desc = B.make_desc(1, d, E, I, 1, 1, 1, "bf16")
+    packed = torch.zeros(B.allocmoe_packed_bytes(desc), dtype=torch.uint8, device="cuda")
+    B.allocmoe_pack_weights(desc, B.make_weights(Wg=Wg, W1=W, W3=W, W2=W), packed)
+
+    def fragments(e, Kd, N):   # [N/32][Kd/16] fragments of 64 lanes x 8 values
+        m = W[e * d * I:(e + 1) * d * I].view(Kd // 16, 2, 8, N // 32, 32)
+        return m.permute(3, 0, 1, 4, 2).reshape(N // 32, -1)
+
+    out = packed[:E * 3 * d * I * 2].view(torch.int16)
+    first, second = out[:E * 2 * d * I].view(E, I // 32, 2, -1), out[E * 2 * d * I:].view(E, d // 32, -1)
+    for e in (0, 31, E - 1):
+        want = fragments(e, d, I)
+        assert torch.equal(first[e, :, 0], want) and torch.equal(first[e, :, 1], want)
+        assert torch.equal(second[e], fragments(e, I, d))
+
+
+def test_8bit_packing_of_a_very_wide_layer():
+    # 4.19e6 strips of 64 columns, 1024 threads each: every expert as it is packed alone
+    need(95)
+    E, d, I = 64, 128, 2 ** 21 + 128
+    W = torch.empty(E * d * I, dtype=torch.int16, device="cuda").random_()
+    Wg = torch.zeros((d, E), dtype=torch.bfloat16, device="cuda")
+
+    def pack(W, E):
+        desc = B.make_desc(1, d, E, I, 1, 1, 1, "bf16", weights_fp8=True)
+        packed = torch.zeros(B.allocmoe_packed_bytes(desc), dtype=torch.uint8, device="cuda")
+        B.allocmoe_pack_weights(desc, B.make_weights(Wg=Wg, W1=W, W3=W, W2=W), packed)
+        at13, at2 = 0, E * 2 * d * I
+        scales13 = at2 + E * d * I + (5 * 16 * d * 2)
+        scales2 = scales13 + (E * 2 * I * 4)
+        return [packed[at13:at2].view(E, -1), packed[at2:at2 + E * d * I].view(E, -1),
+                packed[scales13:scales2].view(E, -1), packed[scales2:scales2 + E * d * 4].view(E, -1)]
+
+    whole = pack(W, E)
+    for e in (0, 40, 63):
+        for got, want in zip(whole, pack(W[e * d * I:(e + 1) * d * I], 1)):
+            assert torch.equal(got[e], want[0])
