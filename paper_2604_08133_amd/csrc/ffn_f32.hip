@@ -19,6 +19,8 @@
 // 32 clocks against 10 loads.  A layer of 500 tokens (d 1000, 16 experts of 700, 1000 pairs, shared
 // expert of 1400; 8.4 GFLOP) went from 909 to 182 us against a 32 x 64 tile on the vector
 // ALUs with scalar loads through LDS; relative error against 64 bits 5.4e-7 (was 1.07e-6).
+#include <algorithm>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -159,16 +161,16 @@ __device__ __forceinline__ void f32_tile(const F32Group& g, int e, int row0, int
     }
 }
 
-// Grid: kF32Xcds * (dense_chunk + most routed workgroups per XCD); consecutive workgroups
-// go to the XCDs in turn.  Each XCD takes a contiguous part of the list "column block,
-// then row tile" of each group, so that the row tiles of an expert read a column
-// block's weights out of one XCD's L2.
+// Grid: kF32Xcds * (dense_chunk + most routed workgroups per XCD), slots from first_slot on where
+// that is more than a launch holds; consecutive workgroups go to the XCDs in turn.  Each XCD
+// takes a contiguous part of the list "column block, then row tile" of each group, so that the
+// row tiles of an expert read a column block's weights out of one XCD's L2.
 template <bool SWIGLU>
 __global__ __launch_bounds__(kF32Waves* kWave, 2) void ffn_f32_kernel(F32Group routed, F32Group shared,
-                                                                      int dense_chunk) {
+                                                                      int dense_chunk, int first_slot) {
     __shared__ float red[kF32Waves * (SWIGLU ? 2 : 1) * 2 * 16 * kWave];
     const int xcd = blockIdx.x % kF32Xcds;
-    int slot = blockIdx.x / kF32Xcds;
+    int slot = first_slot + blockIdx.x / kF32Xcds;
     const bool dense = slot < dense_chunk;
     const F32Group& g = dense ? shared : routed;
     const int n_blocks = (g.N + kF32BN - 1) / kF32BN;
@@ -253,9 +255,13 @@ hipError_t launch_f32(F32Group routed, F32Group shared, hipStream_t stream) {
         const int64_t n_blocks = (g.N + kF32BN - 1) / kF32BN;
         chunk[i] = (tiles * n_blocks + kF32Xcds - 1) / kF32Xcds;
     }
-    if (chunk[0] + chunk[1] > 0)
-        hipLaunchKernelGGL(ffn_f32_kernel<SWIGLU>, dim3(static_cast<unsigned>(kF32Xcds * (chunk[0] + chunk[1]))),
-                           block, 0, stream, routed, shared, static_cast<int>(chunk[1]));
+    // a launch has less than 2^32 threads
+    constexpr int64_t kMaxSlots = (1ll << 32) / (kF32Waves * kWave) / kF32Xcds - 1;
+    const int64_t slots = chunk[0] + chunk[1];
+    for (int64_t first = 0; first < slots; first += kMaxSlots)
+        hipLaunchKernelGGL(ffn_f32_kernel<SWIGLU>,
+                           dim3(static_cast<unsigned>(kF32Xcds * std::min(kMaxSlots, slots - first))), block, 0,
+                           stream, routed, shared, static_cast<int>(chunk[1]), static_cast<int>(first));
     return hipGetLastError();
 }
 

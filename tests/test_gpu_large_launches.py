@@ -6,6 +6,8 @@ import pytest
 import torch
 
 from paper_2604_08133_amd import binding as B
+from paper_2604_08133_amd import synth
+from paper_2604_08133_amd.layer import DeviceLayer
 
 pytestmark = pytest.mark.gpu
 
@@ -60,3 +62,22 @@ def test_8bit_packing_of_a_very_wide_layer():
     for e in (0, 40, 63):
         for got, want in zip(whole, pack(W[e * d * I:(e + 1) * d * I], 1)):
             assert torch.equal(got[e], want[0])
+
+
+def test_fp32_networks_of_a_very_large_batch():
+    # 2^23 workgroups of routed rows and as many of the shared expert's in each first half
+    need(160)
+    w = synth.Workload("large_f32", T=2 ** 20, d=64, E=2, I=16384, K=1, K_base=1, budget=2 ** 20, dtype="f32",
+                       I_shared=16384, I_shared_each=16384)
+    t = synth.make_layer(w, seed=95, device="cuda:0")
+    dev = DeviceLayer(w, t)
+    dev.workspace(dev.desc()).zero_()
+    Y = dev.forward()
+    ids = dev.intermediates()["topk_ids"][:, 0].long()
+    s = dev.intermediates()["topk_s"]
+    rows = torch.cat([torch.arange(0, w.T, 5003, device="cuda"), torch.arange(w.T - 40, w.T, device="cuda")])
+    x = t["X"][rows].double()
+    net = lambda a, b, c: (torch.nn.functional.silu(x @ a.double()) * (x @ b.double())) @ c.double()
+    routed = torch.stack([net(t["W1"][e], t["W3"][e], t["W2"][e]) for e in range(w.E)], dim=1)
+    want = routed[torch.arange(len(rows), device="cuda"), ids[rows]] * s[rows].double() + net(t["Ws1"], t["Ws3"], t["Ws2"])
+    assert float((Y[rows].double() - want).abs().max() / want.abs().max()) <= 1e-4
