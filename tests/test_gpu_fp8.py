@@ -95,13 +95,14 @@ def test_packed_codes_and_scales_bit_exact():
 @pytest.mark.parametrize("T,E,K,budget,Kb,I,Ish,gate", [
     (40, 8, 3, 70, 1, 128, 128, False),       # ragged row tiles, several experts per tile size
     (7, 4, 2, 9, 1, 256, 0, False),           # no shared expert
-    (300, 16, 4, 700, 0, 128, 256, True),     # routed and shared expert on the tile kernel
-    (700, 4, 2, 1000, 1, 256, 256, False),    # several 256-row tiles per expert, partial tiles
-    (100, 4, 3, 200, 1, 128, 128, False),     # routed on the tile kernel, shared streaming
-    (200, 64, 2, 300, 1, 128, 256, False),    # routed streaming, shared on the tile kernel
+    (300, 16, 4, 700, 0, 128, 256, True),     # gated shared expert, more than 32 rows per expert
+    (700, 4, 2, 1000, 1, 256, 256, False),    # hundreds of rows per expert
+    (100, 4, 3, 200, 1, 128, 128, False),     # 50 rows per expert, fewer tokens
+    (200, 64, 2, 300, 1, 128, 256, False),    # 5 rows per expert, a wider shared expert
     (513, 6, 4, 2052, 0, 384, 0, False),      # full budget, no shared expert
 ])
 def test_layer_with_fp8_weights(T, E, K, budget, Kb, I, Ish, gate):
+    # (the streaming kernel; the paths through the tile kernel: tests/test_gpu_ffn_paths.py)
     w = synth.Workload("fp8_layer", T=T, d=256, E=E, I=I, K=K, K_base=Kb, budget=budget,
                        dtype="bf16", I_shared=Ish, I_shared_each=Ish, shared_gate=gate,
                        bias_kind="normal")

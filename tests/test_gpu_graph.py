@@ -9,6 +9,7 @@ import torch
 
 from paper_2604_08133_amd import binding as B, synth
 from paper_2604_08133_amd.layer import DeviceLayer
+from tests.ffn_choice import choice_of
 
 pytestmark = pytest.mark.gpu
 
@@ -21,9 +22,10 @@ def test_forward_replays_from_a_graph(kind):
     elif kind == "large":            # tile kernel, shared expert on the library's side stream
         w = synth.Workload("graph_large", T=8000, d=1024, E=16, I=512, K=4, K_base=1, budget=16000,
                            dtype="bf16", I_shared=512, I_shared_each=512, bias_kind="normal")
-    else:                            # several rows per expert, one stream
+    else:                            # tens of rows per expert, still one stream and the streaming kernel
         w = synth.Workload("graph_prefill", T=300, d=256, E=8, I=128, K=3, K_base=1, budget=500,
                            dtype="bf16", I_shared=128, I_shared_each=128, bias_kind="normal")
+    assert choice_of(w) == (kind == "large",) * 3
     layer = synth.make_layer(w, seed=81)
     dev = DeviceLayer(w, layer)
     desc = dev.desc()

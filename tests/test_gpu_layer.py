@@ -10,6 +10,7 @@ import torch
 import oracle
 from paper_2604_08133_amd import synth
 from paper_2604_08133_amd.layer import DeviceLayer
+from tests.ffn_choice import choice_of
 
 pytestmark = pytest.mark.gpu
 TOL = {"f32": 1e-4, "bf16": 2e-2}
@@ -131,15 +132,18 @@ def test_bf16_no_shared_expert():
 
 
 @pytest.mark.parametrize("T,E,K,budget,Kb,I,Ish,bias", [
-    (300, 8, 3, 500, 1, 128, 128, "normal"),    # routed + shared on the tiled kernel, partial tiles
-    (700, 4, 2, 1000, 1, 256, 256, "zipf"),     # several 128-row tiles per expert, skewed
-    (100, 4, 3, 200, 1, 128, 128, "none"),      # routed tiled, shared on the streaming kernel
-    (200, 64, 2, 300, 1, 128, 256, "normal"),   # routed streaming, shared tiled
+    (300, 8, 3, 500, 1, 128, 128, "normal"),    # about as many routed rows as shared ones
+    (700, 4, 2, 1000, 1, 256, 256, "zipf"),     # hundreds of rows per expert, skewed
+    (100, 4, 3, 200, 1, 128, 128, "none"),      # fewer tokens, 50 rows per expert
+    (200, 64, 2, 300, 1, 128, 256, "normal"),   # 5 rows per expert, a wider shared expert
     (513, 6, 4, 2052, 0, 384, 0, "zipf"),       # full budget, no shared expert, K_base = 0
 ])
 def test_bf16_tiled_kernel_paths(T, E, K, budget, Kb, I, Ish, bias):
+    # (layers of this size keep to the streaming kernel's 32-row tiles; every combination of
+    # kernels and streams by name: tests/test_gpu_ffn_paths.py)
     w = synth.Workload("tiled_bf16", T=T, d=256, E=E, I=I, K=K, K_base=Kb, budget=budget,
                        dtype="bf16", I_shared=Ish, I_shared_each=Ish, bias_kind=bias)
+    assert choice_of(w) == (False, False, False)
     check_layer(w, synth.make_layer(w, seed=51))
 
 
@@ -177,6 +181,7 @@ def test_olmoe_shape_no_shared_expert():
     w = synth.olmoe(budget=4 * 256, T=256)
     layer = synth.make_layer(w)
     tokens = sample_tokens(w.T, 24, seed=8)           # outputs checked on a sample, indices on all
+    assert [choice_of(w, b)[0] for b in (4 * 256, 8 * 256, 256)] == [True, True, False]
     dev = check_layer(w, layer, tokens=tokens)                        # 16 rows per expert: tile kernel
     check_layer(w, layer, budget=8 * 256, tokens=tokens, dev=dev)     # original Top-8, tile kernel
     check_layer(w, layer, budget=256, K_base=1, tokens=tokens, dev=dev)   # Top-1 only: streaming kernel
@@ -249,6 +254,7 @@ def test_qwen_full_size_sampled():
 
 
 def test_forward_is_bitwise_reproducible():
+    # (the streaming kernel; the other paths: tests/test_gpu_ffn_paths.py)
     w = synth.Workload("repro", T=500, d=256, E=32, I=128, K=4, K_base=1, budget=1100,
                        dtype="bf16", I_shared=128, I_shared_each=128)
     dev = DeviceLayer(w, synth.make_layer(w, seed=41))

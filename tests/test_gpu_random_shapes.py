@@ -1,5 +1,6 @@
-"""GPU parity of the layer forward over seeded random shapes: token counts on both
-sides of every kernel-choice threshold, expert counts 1 .. 64, any K_base <= K, budgets
+"""GPU parity of the layer forward over seeded random shapes: narrow layers of 1 to 9000 tokens
+(streaming kernel, tile kernel from about 1000 tokens on) and wider ones that reach every
+combination of kernels and streams of layers under the size limit, expert counts 1 .. 64, any K_base <= K, budgets
 anywhere in [T*K_base, T*K], with and without shared expert / gate / popularity bias /
 8-bit weights.  Indices on all tokens, outputs on a seeded sample (same protocol and
 tolerances as tests/test_gpu_layer.py)."""
@@ -9,6 +10,7 @@ import pytest
 
 from paper_2604_08133_amd import synth
 from paper_2604_08133_amd.layer import DeviceLayer
+from tests.ffn_choice import choice_of
 from tests.test_gpu_fp8 import quantised_reference
 from tests.test_gpu_layer import check_layer, sample_tokens
 
@@ -18,10 +20,10 @@ SMALL_T = [1, 2, 7, 16, 17, 33, 64, 65, 100, 129, 200, 300, 513, 700]
 LARGE_T = [1000, 2048, 3000, 4097, 8192, 8193, 9000]
 
 
-def draw_case(rng, token_counts):
-    d = rng.choice([128, 256, 512])
-    I = rng.choice([64, 128, 192, 256, 384])
-    Ish = rng.choice([0, 64, 128, 256])
+def draw_case(rng, token_counts, wide=False):
+    d = rng.choice([512, 640, 1024, 1088] if wide else [128, 256, 512])
+    I = rng.choice([128, 448, 512] if wide else [64, 128, 192, 256, 384])
+    Ish = rng.choice([0, I, 8 * I, 8192, 16384] if wide else [0, 64, 128, 256])
     E = rng.choice([1, 2, 3, 5, 8, 16, 17, 33, 60, 64])
     K = rng.randint(1, min(E, 8))
     Kb = rng.randint(0, K)
@@ -36,11 +38,14 @@ def draw_case(rng, token_counts):
     return w, fp8, rng.randint(1, 10**6)
 
 
-@pytest.mark.parametrize("stream_seed,token_counts,n_cases", [(11, SMALL_T, 60), (12, LARGE_T, 25)])
-def test_random_shapes(stream_seed, token_counts, n_cases):
+@pytest.mark.parametrize("stream_seed,token_counts,n_cases,wide", [(11, SMALL_T, 60, False), (12, LARGE_T, 25, False),
+                                                                    (25, [24, 130, 200, 350, 700], 24, True)])
+def test_random_shapes(stream_seed, token_counts, n_cases, wide):
     rng = random.Random(stream_seed)
+    paths = set()
     for _ in range(n_cases):
-        w, fp8, seed = draw_case(rng, token_counts)
+        w, fp8, seed = draw_case(rng, token_counts, wide)
+        paths.add(choice_of(w))
         layer = synth.make_layer(w, seed=seed)
         toks = sample_tokens(w.T, min(w.T, 6), seed)
         tag = f"d={w.d} E={w.E} I={w.I} K={w.K} Ish={w.I_shared} gate={w.shared_gate} " \
@@ -51,3 +56,7 @@ def test_random_shapes(stream_seed, token_counts, n_cases):
                         tokens=toks, tag=tag)
         else:
             check_layer(w, layer, tokens=toks, tag=tag)
+    reached = {(False, False, False), (True, True, False)}
+    if wide:
+        reached |= {(True, True, True), (False, True, True)}
+    assert paths == reached
