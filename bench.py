@@ -172,7 +172,7 @@ def measure_ceilings(with_vendor_gemm: bool = True):
         for waves in (1, 2):
             best = (0.0, 0.0)
             for _ in range(3):   # ~10 ms each
-                tf, mhz = B.allocmoe_probe_mfma(ops, waves, 40000 // waves, sink)
+                tf, mhz = B.allocmoe_probe_mfma(ops, waves, 160000 // waves, sink)
                 if tf > best[0]:
                     best = (tf, mhz)
             out["mfma_bf16"][f"{name}_{waves}_waves_per_simd"] = {

@@ -255,8 +255,8 @@ allocmoe_status allocmoe_moe_forward_timed(const allocmoe_layer_desc *desc, cons
  * kernels and copy a few bytes back).  The rooflines of the layer's kernels are quoted
  * against the published peaks; these re-measure what the device at hand sustains.
  *
- * allocmoe_probe_mfma: the matrix-core instruction the expert GEMMs use
- * (32x32x16 bf16, fp32 accumulate) issued back to back on eight independent
+ * allocmoe_probe_mfma: the matrix-core instruction the prefill-shaped expert GEMMs use
+ * (16x16x32 bf16, fp32 accumulate) issued back to back on eight independent
  * accumulators per wave, `waves_per_simd` (1 or 2) waves on every SIMD of every compute
  * unit (a grid of 256 workgroups), `iters` passes of 8 instructions.  The operand
  * fragments come from `operands` (device, allocmoe_probe_mfma_operand_bytes() bytes of

@@ -1,8 +1,8 @@
 // Measurement utilities: the two ceilings a roofline of the layer's kernels is
 // judged against, re-measured on the device at hand.  Not on the layer's path.
 //
-//  * matrix-core issue loop: v_mfma_f32_32x32x16_bf16 back to back on eight
-//    independent accumulators per wave, one or two waves per SIMD on every
+//  * matrix-core issue loop: v_mfma_f32_16x16x32_bf16 (the tile kernel's
+//    instruction) back to back on eight independent accumulators per wave, one or two waves per SIMD on every
 //    compute unit, operands taken from a caller-filled buffer (zeros or random
 //    values: the sustained clock, and with it the rate, depends on the data);
 //    the shader clock is read as the ratio of the core-clock counter to the
@@ -16,7 +16,7 @@
 namespace {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 
 constexpr int kProbeGrid = 256;        // one workgroup per compute unit
@@ -32,21 +32,36 @@ __global__ __launch_bounds__(THREADS) void mfma_probe_kernel(const bf16x8* __res
     for (int j = 0; j < 4; ++j) a[j] = operands[me * kFragsPerLane + j];
 #pragma unroll
     for (int j = 0; j < 2; ++j) b[j] = operands[me * kFragsPerLane + 4 + j];
-    f32x16 acc[8];
+    f32x4 acc[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] = f32x16{0};
+    for (int j = 0; j < 8; ++j) acc[j] = f32x4{0};
+    // (as in the tile kernel: sums in AGPRs, the instruction as asm, which the compiler would
+    // otherwise surround with copies of the sums; idle states before the first one, whose
+    // operands ordinary instructions wrote, and behind the last one, whose sums they read)
+    auto idle = [&] {
+        asm volatile("s_nop 15" : "+a"(acc[0]), "+a"(acc[1]), "+a"(acc[2]), "+a"(acc[3]),
+                     "+a"(acc[4]), "+a"(acc[5]), "+a"(acc[6]), "+a"(acc[7]));
+    };
+    idle();
     const long long c0 = clock64(), w0 = wall_clock64();
-    for (int it = 0; it < iters; ++it) {
+    auto pass = [&] {
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-            acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j % 4], b[j / 4], acc[j], 0, 0, 0);
+            asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[j]) : "v"(a[j % 4]), "v"(b[j / 4]));
+    };
+    int it = 0;
+    for (; it + 8 <= iters; it += 8) {   // (the loop's branch weighs a tenth of 8 instructions)
+#pragma unroll
+        for (int p = 0; p < 8; ++p) pass();
     }
+    for (; it < iters; ++it) pass();
     const long long c1 = clock64(), w1 = wall_clock64();
+    idle();
     float s = 0.f;
 #pragma unroll
     for (int j = 0; j < 8; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s += acc[j][r];
+        for (int r = 0; r < 4; ++r) s += acc[j][r];
     sink[me] = s;
     if (threadIdx.x == 0) {
         clocks[2 * blockIdx.x] = c1 - c0;
@@ -132,7 +147,7 @@ allocmoe_status allocmoe_probe_mfma(const void* operands, size_t operand_bytes, 
         core += static_cast<double>(h[2 * i]);
         wall += static_cast<double>(h[2 * i + 1]);
     }
-    const double flops = static_cast<double>(kProbeGrid) * 4 * waves_per_simd * iters * 8.0 * 32768.0;
+    const double flops = static_cast<double>(kProbeGrid) * 4 * waves_per_simd * iters * 8.0 * 16384.0;
     *tflops = static_cast<float>(flops / (ms * 1e-3) / 1e12);
     *shader_mhz = wall > 0 ? static_cast<float>(core / wall * 100.0) : 0.f;
     (void)hipEventDestroy(e0);
