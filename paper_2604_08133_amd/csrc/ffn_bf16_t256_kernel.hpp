@@ -14,9 +14,9 @@
 //  * v_mfma_f32_16x16x32_bf16 and not the 32x32x16 form: the chip is limited by
 //    power on real data, and the longer contraction per instruction moves the
 //    sums half as often.  Issued back to back on N(0,1) operands the 16x16x32
-//    form sustains 1.89 PFLOP/s, the 32x32x16 form 1.68.  A 16384 x 2816 x 2048
-//    product (second half, 8192 rows) went from 1.17 to 1.31 PFLOP/s with it, the
-//    SwiGLU half from 1.16 to 1.24.
+//    form sustains 2.12 PFLOP/s (allocmoe_probe_mfma), the 32x32x16 form 1.85 on the
+//    same box.  A 16384 x 2816 x 2048 product (second half) runs at 1.34 PFLOP/s (1.19
+//    with the 32x32x16 form), 16384 x 2048 x 5632 (SwiGLU half) at 1.25 (1.15).
 //  * The weights never pass through LDS: they were re-tiled once into MFMA
 //    fragment order, a wave is the only consumer of its columns, so each lane
 //    loads its 16 bytes per fragment straight from global memory (1 KB
@@ -62,8 +62,8 @@ constexpr int kXcds = 8;                // accelerator dies (one L2 each) of an 
 // 64 experts: 327.5 against 329 us and 223 against 225 us a layer), full tiles need the
 // longer one (8192 tokens, skewed experts: 729 us, 760 us with the shorter ring everywhere).
 constexpr int ring_steps(int row_blocks16, bool fp8) { return !fp8 && row_blocks16 <= 8 ? 4 : 8; }
-constexpr int kRingDeep = 12;           // bf16, tiles of up to 64 rows: the light ones, dense groups of few workgroups
-constexpr int kLightRowBlocks = 2;
+constexpr int kRingDeep = 12;       // bf16, tiles of up to 64 rows: light ones, dense groups of few workgroups
+constexpr int kLightRowBlocks = 4;  // 16-row blocks of such a tile (the plan counts the light ones: up to 64 rows)
 
 // 8 rows x 128 B of activations, global -> LDS directly: lane l's 16 bytes land
 // at M0 + 16 l (M0 holds the wave-uniform LDS base; one other instruction has to stand
@@ -489,7 +489,7 @@ __device__ __forceinline__ void t256_body(char* lds, const bf16_t* A, size_t lda
 }
 
 // How many tiles at the end of the tile map form the light class (single tiles of at most
-// kLightRowBlocks row blocks, spread among the others and run with the deeper weight ring):
+// kLightRowBlocks 16-row blocks, spread among the others and run with the deeper weight ring):
 // all of them if they are the minority, else none.  8-bit weights: none (no deeper ring for
 // them, and without it spreading the light tiles only costs).
 __device__ __forceinline__ int light_class_of(const int32_t* tile_info, bool fp8) {
@@ -542,7 +542,7 @@ __global__ __launch_bounds__(kWaves* kWave, 1) void ffn_bf16_t256_kernel(StreamG
             // right to left, which evens out the XCDs' totals of the sorted tile costs)
             const int round = sub / (2 * nt0), in_pair = sub % (2 * nt0);
             const int q = round * kXcds + ((round & 1) ? kXcds - 1 - xcd : xcd);
-            // The light tiles (single tiles of at most kLightRowBlocks row blocks: the end
+            // The light tiles (single tiles of at most kLightRowBlocks 16-row blocks: the end
             // of the tile map) wait for their weights, the others for the matrix unit:
             // their pairs are spread evenly among the pairs of the others, so that both
             // kinds run side by side through the whole launch.  Of the first q + 1 pair
@@ -633,14 +633,14 @@ __global__ __launch_bounds__(kWaves* kWave, 1) void ffn_bf16_t256_kernel(StreamG
     do {                                                                                            \
         if (only_tile)                                                                              \
             t256_body<SWIGLU, n, true, FP8, ring>(lds, A, lda, row_map, b0, b1, sc0, sc1, KT,       \
-                                                  wave, lane, row0, rows, nt, live, g.C, ldc);            \
+                                                  wave, lane, row0, rows, nt, live, g.C, ldc);      \
         else                                                                                        \
             t256_body<SWIGLU, n, false, FP8, ring>(lds, A, lda, row_map, b0, b1, sc0, sc1, KT,      \
-                                                   wave, lane, row0, rows, nt, live, g.C, ldc);           \
+                                                   wave, lane, row0, rows, nt, live, g.C, ldc);     \
     } while (0)
 #define ALLOCMOE_T256_CASE(n)                                                                       \
     case n:                                                                                         \
-        if constexpr (!FP8 && n <= 2 * kLightRowBlocks) {                                           \
+        if constexpr (!FP8 && n <= kLightRowBlocks) {                                               \
             if (deep_ring) {                                                                        \
                 ALLOCMOE_T256_BODY(n, kRingDeep);                                                   \
                 break;                                                                              \

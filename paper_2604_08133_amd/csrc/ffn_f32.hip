@@ -15,10 +15,13 @@
 // registers in 16-byte loads, one step ahead of the MFMAs: which k a lane's slot means
 // and which column is free to choose, so a lane takes 4 consecutive k of its row of A
 // (slot i of step k0: k0 + 4 (lane/16) + i) and 4 consecutive columns of those 4 rows of B
-// (column block j: n0 + 4 (lane%16) + j).  Bound by the matrix pipe: a step is 64 MFMAs of
-// 32 clocks against 10 loads.  A layer of 500 tokens (d 1000, 16 experts of 700, 1000 pairs, shared
-// expert of 1400; 8.4 GFLOP) went from 909 to 182 us against a 32 x 64 tile on the vector
-// ALUs with scalar loads through LDS; relative error against 64 bits 5.4e-7 (was 1.07e-6).
+// (column block j: n0 + 4 (lane%16) + j).  A layer of 500 tokens (d 1000, 16 experts of 700,
+// 1000 pairs, shared expert of 1400; 8.4 GFLOP) takes 181 us, 100 and 54 of them in the two
+// halves; 909 with a 32 x 64 tile on the vector ALUs and scalar loads through LDS (relative
+// error against 64 bits 5.4e-7, then 1.07e-6).  Bound, by counters, by the matrix pipe inside a
+// workgroup (0.77 of the waves' cycles an instruction waits for its unit, 0.13 for loads) and
+// by the rounds of workgroups around it: 864 and 992 of them, two to a unit, keep the units
+// busy 0.68 of a launch and the pipes 0.40 and 0.35.
 #include <algorithm>
 
 #include "common.hpp"
@@ -38,7 +41,7 @@ __device__ __forceinline__ f32x4 load4u(const float* p) {
     return f32x4{v.x, v.y, v.z, v.w};
 }
 
-// One tile: rows row0 .. row0 + rows - 1 (at most 16 MB of them) of expert e, columns n0 .. n0 + 63.
+// One tile: rows row0 .. row0 + rows - 1 (at most 16 * MB) of expert e, columns n0 .. n0 + 63.
 // Kd >= 4 and N >= 4: the last lanes' 4 k and 4 columns step back to the end of the
 // matrix; the k that another lane has already are zeroed in both operands, the columns
 // that another lane has already are not stored.

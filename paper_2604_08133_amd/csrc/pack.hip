@@ -15,7 +15,6 @@
 
 namespace allocmoe {
 
-//
 // A lane gathers its 8 values (a wave-load covers 64 bytes of a row; consecutive waves go down
 // the rows, the neighbouring column block finds the other half of the lines in L2) and stores
 // them as one piece.  Bound by HBM: 64 experts of 2048 x 1408 and a shared expert, 2.2 GB in
@@ -76,7 +75,8 @@ __device__ __forceinline__ uint32_t e4m3_encode4(const float (&y)[4]) {
 // fragments.  Longer columns are read twice, in chunks of 2048 rows.  All six matrices of a
 // layer go in one launch, so that the shared expert's few strips fill up the others' last
 // round.  Bound by HBM: 64 experts of 2048 x 1408 and a shared expert of 2048 x 2816, 1.7 GB
-// in and out, take 460 us (3.7 TB/s; a large copy reaches 4.8).  One thread per column for
+// in and out, take 460 us (3.7 TB/s; a 2 GiB copy reaches 5.0, the bf16 packing 5.5: here one
+// workgroup fills a unit's registers, so that a unit reads or writes).  One thread per column for
 // the maxima, then a second pass that read the matrices again, took 5.9 ms: 860 us per
 // matrix for a serial chain of row loads, 258 us for the codes with two full divisions.
 constexpr int kPackWaves = 16, kPackRows = kPackWaves * 4 * 32, kPackCols = 64;
