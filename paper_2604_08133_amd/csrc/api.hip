@@ -232,9 +232,8 @@ allocmoe_status allocmoe_pack_weights(const allocmoe_layer_desc* desc,
             jobs.job[5] = {w->Ws2, 1, Is, d, out + q.qs2, SS * dd, SS * 32, 0, at<float>(out, q.scs2), dd, 0};
             jobs.n = 6;
         }
+        jobs.gate = {w->Wg, desc->shared_gate ? w->w_sg : nullptr, d, E, out + q.gate, 0};
         ALLOCMOE_TRY(launch_pack_fp8(jobs, stream));
-        ALLOCMOE_TRY(launch_pack_gate(w->Wg, desc->shared_gate ? w->w_sg : nullptr, d, E,
-                                      out + q.gate, stream));
         return ALLOCMOE_OK;
     }
     const PackedLayout p = packed_of(desc);
@@ -253,9 +252,8 @@ allocmoe_status allocmoe_pack_weights(const allocmoe_layer_desc* desc,
         jobs.job[5] = {w->Ws2, 1, Is, d, out + p.ps2, SS * dd, SS * 32, 0, 0};
         jobs.n = 6;
     }
+    jobs.gate = {w->Wg, desc->shared_gate ? w->w_sg : nullptr, d, E, out + p.gate, 0};
     ALLOCMOE_TRY(launch_pack_b(jobs, stream));
-    ALLOCMOE_TRY(launch_pack_gate(w->Wg, desc->shared_gate ? w->w_sg : nullptr, d, E, out + p.gate,
-                                  stream));
     return ALLOCMOE_OK;
 }
 

@@ -34,8 +34,6 @@ inline size_t gate_packed_elems(int d) { return static_cast<size_t>(kGateBlocks)
 hipError_t launch_route_mfma(const void* X, const void* gate_packed, const float* bias,
                              bool with_gate, int T, int d, int E, int K, float* scores,
                              int32_t* topk_ids, float* topk_s, float* sgate, hipStream_t stream);
-hipError_t launch_pack_gate(const void* Wg, const void* w_sg, int d, int E, void* out,
-                            hipStream_t stream);
 hipError_t launch_topk_from_scores(const float* scores, int T, int E, int K, int32_t* topk_ids,
                                    float* topk_s, hipStream_t stream);
 
@@ -123,6 +121,13 @@ hipError_t launch_ffn_bf16_t256(bool swiglu, StreamGroup routed, StreamGroup sha
                                 hipStream_t stream);
 
 // ---- pack.hip : row-major [G][Kd][N] bf16 -> MFMA fragment order
+// the gate matrix and the shared expert's gate vector (may be null), re-tiled in the same launch
+struct PackGate {
+    const void *Wg, *w_sg;
+    int d, E;
+    void* out;
+    int n_wg;   // filled by the launcher
+};
 // 8-bit variant: per output column a scale (max |w| / 448, 1 for a zero column) and E4M3
 // codes of w / scale (nearest, ties to even mantissa, saturating), in fragments of
 // 32 k x 32 n: lane l holds 16 bytes, k = 32 kb + 8 (l/32) + i in bytes i = 0..7 and
@@ -142,6 +147,7 @@ struct PackFp8Job {
 };
 struct PackFp8Jobs {
     PackFp8Job job[6];
+    PackGate gate;
     int n;
     int first_strip;   // of this launch (filled by the launcher)
 };
@@ -158,6 +164,7 @@ struct PackJob {
 };
 struct PackJobs {
     PackJob job[6];
+    PackGate gate;
     int n;
     int64_t first_wg;   // of this launch (filled by the launcher)
 };

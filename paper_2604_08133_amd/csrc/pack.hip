@@ -15,6 +15,38 @@
 
 namespace allocmoe {
 
+// Re-tiles the gate matrix Wg [d,E] (and, as column 64, the shared expert's
+// gate vector w_sg [d]) into the B-operand order of v_mfma_f32_16x16x32_bf16:
+// fragment (nb, s) = 64 lanes x 8 values, lane l holding
+//   G[32 s + 8 (l/16) + i][16 nb + l%16],  i = 0..7,
+// with G's columns E..63 and 65..79 zero.  Layout: [nb][s][lane][8].  Done by the first
+// workgroups of the expert matrices' launch, beside them (a launch of its own behind them:
+// 4-7 us).
+__device__ __forceinline__ void pack_gate(const PackGate& G, int64_t idx) {
+    const int KB = G.d / 32;
+    if (idx >= static_cast<int64_t>(kGateBlocks) * KB * kWave) return;
+    const bf16_t *Wg = static_cast<const bf16_t*>(G.Wg), *w_sg = static_cast<const bf16_t*>(G.w_sg);
+    const int l = idx % kWave, s = (idx / kWave) % KB, nb = static_cast<int>(idx / (static_cast<int64_t>(kWave) * KB));
+    const int n = 16 * nb + l % 16, k0 = 32 * s + 8 * (l / 16);
+    bf16_t* dst = static_cast<bf16_t*>(G.out) + static_cast<size_t>(idx) * 8;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        bf16_t v = 0;
+        if (n < G.E)
+            v = Wg[static_cast<size_t>(k0 + i) * G.E + n];
+        else if (n == 64 && w_sg != nullptr)
+            v = w_sg[k0 + i];
+        dst[i] = v;
+    }
+}
+
+// workgroups of a launch that re-tile the gate matrix: whole rounds over the XCDs
+constexpr int kPackXcds = 8;
+inline int gate_workgroups(const PackGate& G, int threads) {
+    const int64_t pieces = static_cast<int64_t>(kGateBlocks) * (G.d / 32) * kWave;
+    return static_cast<int>((pieces + threads * kPackXcds - 1) / (threads * kPackXcds) * kPackXcds);
+}
+
 // A lane gathers its 8 values (a wave-load covers 64 bytes of a row; consecutive waves go down
 // the rows, the neighbouring column block finds the other half of the lines in L2) and stores
 // them as one piece.  Bound by HBM: 64 experts of 2048 x 1408 and a shared expert, 2.2 GB in
@@ -23,7 +55,11 @@ namespace allocmoe {
 // 16 experts of 576 x 320 took 17.4 us instead of 12.8, 32 experts of 1088 x 704 and a shared
 // expert 80.6 instead of 69.6.
 __global__ __launch_bounds__(256) void pack_b_kernel(PackJobs jobs) {
-    int64_t bid = jobs.first_wg + blockIdx.x;
+    if (static_cast<int>(blockIdx.x) < jobs.gate.n_wg) {
+        pack_gate(jobs.gate, static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x);
+        return;
+    }
+    int64_t bid = jobs.first_wg + blockIdx.x - jobs.gate.n_wg;
     int jn = 0;
     while (bid >= jobs.job[jn].n_wg) bid -= jobs.job[jn++].n_wg;
     const PackJob& J = jobs.job[jn];
@@ -56,70 +92,91 @@ __global__ __launch_bounds__(256) void pack_b_kernel(PackJobs jobs) {
 
 // E4M3 of the OCP 8-bit floating point format: sign, 4 exponent bits (bias 7), 3 mantissa
 // bits, subnormals, no infinities, largest finite magnitude 448.  Nearest code, ties to
-// the even mantissa, magnitudes above 448 saturate: the conversion unit's rounding, on
-// values that were clamped before.  A NaN saturates too, with its sign (the minimum passes
-// over it).  Byte i of the result = code of y[i].
+// the even mantissa: the conversion unit's rounding.  Byte i of the result = code of y[i].
 __device__ __forceinline__ uint32_t e4m3_encode4(const float (&y)[4]) {
-    float c[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) c[i] = copysignf(fminf(fabsf(y[i]), 448.f), y[i]);
-    int w = __builtin_amdgcn_cvt_pk_fp8_f32(c[0], c[1], 0, false);
-    w = __builtin_amdgcn_cvt_pk_fp8_f32(c[2], c[3], w, true);
+    int w = __builtin_amdgcn_cvt_pk_fp8_f32(y[0], y[1], 0, false);
+    w = __builtin_amdgcn_cvt_pk_fp8_f32(y[2], y[3], w, true);
     return static_cast<uint32_t>(w);
 }
 
-// A workgroup owns 64 columns (128 bytes of every row) of one matrix.  Lane 16 g + t of wave
-// w loads columns 4 t .. + 3 of the 32 rows of k block 4 w + g, i.e. the 16 waves hold 2048
-// rows of the strip in registers: the matrix is read once, the column maxima are formed
-// from the registers (lanes, then LDS), and the codes leave as whole 16-byte pieces of the
-// fragments.  Longer columns are read twice, in chunks of 2048 rows.  All six matrices of a
-// layer go in one launch, so that the shared expert's few strips fill up the others' last
-// round.  Bound by HBM: 64 experts of 2048 x 1408 and a shared expert of 2048 x 2816, 1.7 GB
-// in and out, take 460 us (3.7 TB/s; a 2 GiB copy reaches 5.0, the bf16 packing 5.5: here one
-// workgroup fills a unit's registers, so that a unit reads or writes).  One thread per column for
-// the maxima, then a second pass that read the matrices again, took 5.9 ms: 860 us per
-// matrix for a serial chain of row loads, 258 us for the codes with two full divisions.
-constexpr int kPackWaves = 16, kPackRows = kPackWaves * 4 * 32, kPackCols = 64;
+// A workgroup owns 32 columns (64 bytes of every row: one column block of fragments) of one
+// matrix.  Its 8 waves hold 2048 rows of the strip in registers, so the matrix is read once:
+// lane 8 b + 4 h + t of wave w has columns 8 t .. + 7 of the 16 rows that make the pieces of
+// half h (lanes 32 h .. of a fragment) of k block 8 w + b.  The column maxima are formed from
+// the registers (lanes, then LDS), and the codes are turned in LDS, wave by wave, so that
+// they leave as whole fragments (1 KB per store).  Longer columns are read twice, in chunks
+// of 2048 rows.  All six matrices of a layer go in one launch, so that the shared expert's few
+// strips fill up the others' last round.
+constexpr int kPackWaves = 8, kPackWaveRows = 256, kPackRows = kPackWaves * kPackWaveRows, kPackCols = 32;
+constexpr int kPackGroup = 16;   // neighbouring strips of an XCD
 
-__global__ __launch_bounds__(kPackWaves* kWave) void pack_fp8_kernel(PackFp8Jobs jobs) {
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+__global__ __launch_bounds__(kPackWaves* kWave, 4) void pack_fp8_kernel(PackFp8Jobs jobs) {
     __shared__ uint32_t wave_max[kPackWaves][kPackCols / 2];   // two columns' magnitudes each
-    __shared__ float col_scale[kPackCols];
-    int bid = jobs.first_strip + blockIdx.x, jn = 0;
-    while (bid >= jobs.job[jn].n_strips) bid -= jobs.job[jn++].n_strips;
+    __shared__ float2 col_scale[kPackCols];   // and its reciprocal
+    __shared__ u32x4 turn[kPackWaves][kPackWaveRows * kPackCols / 16];
+    if (static_cast<int>(blockIdx.x) < jobs.gate.n_wg) {
+        pack_gate(jobs.gate, static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x);
+        return;
+    }
+    // Workgroups are dealt to the XCDs in turn: an XCD takes kPackGroup neighbouring strips one
+    // after the other.  Two of them share every 128-byte line, and the rows then are read in
+    // runs of 1 KB.
+    const int wg = blockIdx.x - jobs.gate.n_wg, xcd = wg % kPackXcds, idx = wg / kPackXcds;
+    int bid = jobs.first_strip + (idx / kPackGroup * kPackXcds + xcd) * kPackGroup + idx % kPackGroup, jn = 0;
+    while (bid >= jobs.job[jn].n_strips) {
+        bid -= jobs.job[jn++].n_strips;
+        if (jn == jobs.n) return;
+    }
     const PackFp8Job& J = jobs.job[jn];
     const int N = J.N, Kd = J.Kd, strips = N / kPackCols;
     const int g = bid / strips, n0 = bid % strips * kPackCols;
-    const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
-    const int t = lane % 16, kb = wave * 4 + lane / 16;
-    const bf16_t* src = static_cast<const bf16_t*>(J.W) + static_cast<size_t>(g) * Kd * N + n0 + 4 * t;
+    const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int t = lane % 4, h = lane / 4 % 2, kb = lane / 8;
+    const int row_lane = kPackWaveRows * wave + 32 * kb + 8 * h;   // rows + 0 .. 7 and + 16 .. 23
+    const bf16_t* src = static_cast<const bf16_t*>(J.W) + static_cast<size_t>(g) * Kd * N + n0;
     typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
     // (a matrix may start at any element)
-    typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
-    u32x2_any v[32];
-    auto load = [&](int row0) {   // (past the end, Kd being a multiple of 32: the last rows again)
-        const bf16_t* p = src + static_cast<size_t>(min(row0, Kd - 32)) * N;
+    typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+    u32x4_any v[16];
+    auto load = [&](int row0) {   // (past the end, Kd being a multiple of 32: the lane's rows of the last k block)
+        const bf16_t* p = src + static_cast<size_t>(min(row0, Kd - 32 + 8 * h)) * N + 8 * t;
 #pragma unroll
-        for (int r = 0; r < 32; ++r)
-            v[r] = __builtin_nontemporal_load(reinterpret_cast<const u32x2_any*>(p + static_cast<size_t>(r) * N));
+        for (int r = 0; r < 16; ++r) {
+            v[r] = *reinterpret_cast<const u32x4_any*>(p);
+            p += static_cast<size_t>(r == 7 ? 9 : 1) * N;
+        }
     };
     // Magnitudes of bf16 values compare like their bit patterns.  A NaN must not count (its
     // pattern is above infinity's and would be the maximum): with 0x7F added the patterns up
     // to infinity's (0x7F80) stay below 0x8000, those of NaNs become negative.
     constexpr int16_t kShift = 0x7F;
-    i16x2 m[2] = {i16x2{kShift, kShift}, i16x2{kShift, kShift}};
+    i16x2 m[4], low = i16x2{kShift, kShift};   // low: negative once a NaN was seen
+#pragma unroll
+    for (int q = 0; q < 4; ++q) m[q] = i16x2{kShift, kShift};
     for (int c = 0; c < Kd; c += kPackRows) {
-        load(c + kb * 32);
+        if (c + kPackWaveRows * wave >= Kd) break;   // (the wave has no rows in this chunk)
+        load(c + row_lane);
 #pragma unroll
-        for (int r = 0; r < 32; ++r)
+        for (int r = 0; r < 16; ++r)
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
-                m[h] = __builtin_elementwise_max(m[h], __builtin_bit_cast(i16x2, (v[r][h] & 0x7FFF7FFFu) + kShift * 0x10001u));
+            for (int q = 0; q < 4; ++q) {
+                const i16x2 x = __builtin_bit_cast(i16x2, (v[r][q] & 0x7FFF7FFFu) + kShift * 0x10001u);
+                m[q] = __builtin_elementwise_max(m[q], x);
+                low = __builtin_elementwise_min(low, x);
+            }
     }
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {   // over the lanes with the same columns
-        m[h] = __builtin_elementwise_max(m[h], __builtin_bit_cast(i16x2, lane_xor<16>(__builtin_bit_cast(uint32_t, m[h]))));
-        m[h] = __builtin_elementwise_max(m[h], __builtin_bit_cast(i16x2, lane_xor<32>(__builtin_bit_cast(uint32_t, m[h]))));
-        if (lane < 16) wave_max[wave][2 * t + h] = __builtin_bit_cast(uint32_t, m[h]);
+    for (int q = 0; q < 4; ++q) {   // over the lanes with the same columns
+        auto fold = [&](uint32_t other) {
+            m[q] = __builtin_elementwise_max(m[q], __builtin_bit_cast(i16x2, other));
+        };
+        fold(lane_xor<4>(__builtin_bit_cast(uint32_t, m[q])));
+        fold(lane_xor<8>(__builtin_bit_cast(uint32_t, m[q])));
+        fold(lane_xor<16>(__builtin_bit_cast(uint32_t, m[q])));
+        fold(lane_xor<32>(__builtin_bit_cast(uint32_t, m[q])));
+        if (lane < 4) wave_max[wave][4 * t + q] = __builtin_bit_cast(uint32_t, m[q]);
     }
     __syncthreads();
     if (tid < kPackCols) {
@@ -128,62 +185,80 @@ __global__ __launch_bounds__(kPackWaves* kWave) void pack_fp8_kernel(PackFp8Jobs
         for (int w = 0; w < kPackWaves; ++w) top = max(top, (wave_max[w][tid / 2] >> (16 * (tid % 2))) & 0xFFFFu);
         const float amax = __uint_as_float((top - kShift) << 16);
         const float sc = amax > 0.f ? __fdiv_rn(amax, 448.f) : 1.f;
-        col_scale[tid] = sc;
+        col_scale[tid] = make_float2(sc, __fdiv_rn(1.f, sc));
         J.scale[static_cast<size_t>(g) * J.scale_stride + n0 + tid] = sc;
     }
     __syncthreads();
-    float sc[4], rc[4];
-    bool moderate = true;
+    bool plain = low[0] >= 0 && low[1] >= 0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        sc[j] = col_scale[4 * t + j];
-        rc[j] = __fdiv_rn(1.f, sc[j]);
-        moderate = moderate && sc[j] > 0x1p-80f && sc[j] < 0x1p80f;
+    for (int j = 0; j < 8; ++j) {
+        const float sc = col_scale[8 * t + j].x;
+        plain = plain && sc > 0x1p-80f && sc < 0x1p80f;
     }
-    // w / sc, correctly rounded: the quotient estimate and two corrections by the exact
-    // remainder, as in the full division, whose scaling for extreme exponents is not needed
-    // where the scale's exponent is moderate (a value so small that a remainder underflows
-    // is far below half the smallest code and becomes zero either way; the sign of a zero,
-    // which the remainders lose, is put back)
-    auto quotient = [&](float w, int j) {
-        const float q0 = w * rc[j];
-        const float q1 = fmaf(fmaf(-q0, sc[j], w), rc[j], q0);
-        return copysignf(fmaf(fmaf(-q1, sc[j], w), rc[j], q1), w);
+    // Plain columns: w / sc by the quotient estimate and one correction by the exact remainder.
+    // That is the correctly rounded quotient for every magnitude of w (8 significant bits) and
+    // every scale a column of such magnitudes can have (128 mantissas: the pairs were compared
+    // one by one, tests/test_quant.py), where the scale's exponent is moderate (a value so
+    // small that a remainder underflows is far below half the smallest code and becomes zero
+    // either way).  The remainder is formed with its sign turned, which keeps a zero's.  The
+    // quotient's magnitude is at most 448 and an ulp, which rounds to 448.
+    auto quotient = [](float w, float2 sc) {
+        const float q = w * sc.y;
+        return fmaf(-fmaf(q, sc.x, -w), sc.y, q);
     };
-    char* out = static_cast<char*>(J.out) + static_cast<size_t>(g) * J.group_stride + J.base_off;
-    auto store_codes = [&](int row0, auto short_division) {
+    // Others: the full division; above 448 saturates, and so does a NaN, with its sign (the
+    // minimum passes over it).
+    auto saturated = [](float w, float2 sc) {
+        const float y = __fdiv_rn(w, sc.x);
+        return copysignf(fminf(fabsf(y), 448.f), y);
+    };
+    char* out = static_cast<char*>(J.out) + static_cast<size_t>(g) * J.group_stride + J.base_off +
+                static_cast<size_t>(n0 / kPackCols) * J.nblock_stride;
+    u32x4* my = turn[wave];
+    // Piece 32 h + n of a fragment stands at position p ^ x of its 64 in LDS, x such that 16
+    // neighbouring lanes write 16 different 16-byte units of the 256 bytes the banks span (on
+    // the way out the lanes read within the same eight units).
+    const int x_in = (t >> 1) | (h << 1) | ((kb & 1) << 2), at_lane = 64 * kb + 32 * h + 8 * t;
+    auto turn_codes = [&](auto fast) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + 4 * t + j;
-            char* frag = out + static_cast<size_t>(n / 32) * J.nblock_stride + static_cast<size_t>(row0 / 32) * 1024;
+        for (int j = 0; j < 8; ++j) {
+            const float2 sc = col_scale[8 * t + j];
+            uint32_t word[4];
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                uint32_t word[4];
+            for (int q = 0; q < 4; ++q) {
+                float y[4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    float y[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const uint32_t pair = v[16 * (q / 2) + 8 * h + 4 * (q % 2) + i][j / 2];
-                        const float w = __uint_as_float((j % 2) ? (pair & 0xFFFF0000u) : (pair << 16));
-                        y[i] = decltype(short_division)::value ? quotient(w, j) : __fdiv_rn(w, sc[j]);
-                    }
-                    word[q] = e4m3_encode4(y);
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t pair = v[4 * q + i][j / 2];
+                    const float w = __uint_as_float((j % 2) ? (pair & 0xFFFF0000u) : (pair << 16));
+                    y[i] = decltype(fast)::value ? quotient(w, sc) : saturated(w, sc);
                 }
-                *reinterpret_cast<uint4*>(frag + (32 * h + n % 32) * 16) = make_uint4(word[0], word[1], word[2], word[3]);
-                __builtin_amdgcn_sched_barrier(0);   // one piece at a time: the strip fills the registers
+                word[q] = e4m3_encode4(y);
             }
+            int at = x_in;
+            asm("" : "+v"(at));   // (eight positions kept in registers would not fit beside the strip)
+            my[at_lane + (j ^ at)] = u32x4{word[0], word[1], word[2], word[3]};
+            __builtin_amdgcn_sched_barrier(0);   // one piece at a time: the strip fills the registers
         }
     };
-    const bool all_moderate = __all(moderate);
+    const bool all_plain = __all(plain);
     for (int c = 0; c < Kd; c += kPackRows) {
-        const int row0 = c + kb * 32;
-        if (Kd > kPackRows) load(row0);
-        if (row0 >= Kd) continue;
-        if (all_moderate)
-            store_codes(row0, std::true_type{});
+        const int first = c + kPackWaveRows * wave;
+        if (first >= Kd) break;
+        if (Kd > kPackRows) load(c + row_lane);
+        if (all_plain)
+            turn_codes(std::true_type{});
         else
-            store_codes(row0, std::false_type{});
+            turn_codes(std::false_type{});
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int i = 0; i < kPackWaveRows / 32; ++i) {
+            if (first + 32 * i >= Kd) break;
+            const int x_out = ((lane >> 4) & 1) | ((lane >> 5) << 1) | ((i & 1) << 2);
+            __builtin_nontemporal_store(my[64 * i + (lane ^ x_out)],
+                                        reinterpret_cast<u32x4*>(out + static_cast<size_t>(first / 32 + i) * 1024 + lane * 16));
+        }
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -194,11 +269,16 @@ hipError_t launch_pack_fp8(PackFp8Jobs jobs, hipStream_t stream) {
         J.n_strips = J.G * (J.N / kPackCols);
         strips += J.n_strips;
     }
-    constexpr int64_t kMaxStrips = (1ll << 32) / (kPackWaves * kWave) - 1;   // threads of a launch: 2^32 - 1
-    for (int64_t first = 0; first < strips; first += kMaxStrips) {
+    // threads of a launch: 2^32 - 1; whole rounds of groups over the XCDs
+    constexpr int64_t kRound = kPackGroup * kPackXcds, kMaxWg = (1ll << 32) / (kPackWaves * kWave) - 1;
+    jobs.gate.n_wg = gate_workgroups(jobs.gate, kPackWaves * kWave);
+    for (int64_t first = 0; first < strips;) {
+        const int64_t n = std::min((kMaxWg - jobs.gate.n_wg) / kRound, (strips - first + kRound - 1) / kRound) * kRound;
         jobs.first_strip = static_cast<int>(first);
-        hipLaunchKernelGGL(pack_fp8_kernel, dim3(static_cast<unsigned>(std::min(kMaxStrips, strips - first))),
+        hipLaunchKernelGGL(pack_fp8_kernel, dim3(static_cast<unsigned>(jobs.gate.n_wg + n)),
                            dim3(kPackWaves * kWave), 0, stream, jobs);
+        first += n;
+        jobs.gate.n_wg = 0;   // (done by the first launch)
     }
     return hipGetLastError();
 }
@@ -212,9 +292,13 @@ hipError_t launch_pack_b(PackJobs jobs, hipStream_t stream) {
     }
     // a launch has less than 2^32 threads: layers of 3.4e10 weights take a second one
     constexpr int64_t kMaxWg = (1ll << 32) / 256 - 1;
-    for (jobs.first_wg = 0; jobs.first_wg < wgs; jobs.first_wg += kMaxWg)
-        hipLaunchKernelGGL(pack_b_kernel, dim3(static_cast<unsigned>(std::min(kMaxWg, wgs - jobs.first_wg))),
-                           dim3(256), 0, stream, jobs);
+    jobs.gate.n_wg = gate_workgroups(jobs.gate, 256);
+    for (jobs.first_wg = 0; jobs.first_wg < wgs;) {
+        const int64_t n = std::min(kMaxWg - jobs.gate.n_wg, wgs - jobs.first_wg);
+        hipLaunchKernelGGL(pack_b_kernel, dim3(static_cast<unsigned>(jobs.gate.n_wg + n)), dim3(256), 0, stream, jobs);
+        jobs.first_wg += n;
+        jobs.gate.n_wg = 0;   // (done by the first launch)
+    }
     return hipGetLastError();
 }
 

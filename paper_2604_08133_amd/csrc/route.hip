@@ -150,7 +150,7 @@ __global__ __launch_bounds__(WAVES* kWave) void route_kernel(
 // owns 16 MT tokens; the waves split the hidden dimension into slices of 32-wide
 // steps, each wave running v_mfma_f32_16x16x32_bf16 on its slice with the A
 // operand read straight from X (64 contiguous bytes per token and step) and the
-// B operand from the gate matrix re-tiled by pack_gate_kernel (one 16-byte load
+// B operand from the gate matrix re-tiled at load time (pack.hip) (one 16-byte load
 // per lane).  The partial logits meet in LDS in a fixed order, then one wave
 // per token does the softmax and the Top-K with one lane per expert.
 //
@@ -302,32 +302,6 @@ __global__ __launch_bounds__(kRmWaves* kWave) void route_mfma_kernel(
     }
 }
 
-// Re-tiles the gate matrix Wg [d,E] (and, as column 64, the shared expert's
-// gate vector w_sg [d]) into the B-operand order of v_mfma_f32_16x16x32_bf16:
-// fragment (nb, s) = 64 lanes x 8 values, lane l holding
-//   G[32 s + 8 (l/16) + i][16 nb + l%16],  i = 0..7,
-// with G's columns E..63 and 65..79 zero.  Layout: [nb][s][lane][8].
-__global__ __launch_bounds__(256) void pack_gate_kernel(const bf16_t* __restrict__ Wg,
-                                                        const bf16_t* __restrict__ w_sg, int d,
-                                                        int E, bf16_t* __restrict__ out) {
-    const int KB = d / 32;
-    const int total = kGateBlocks * KB * kWave;
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= total) return;
-    const int l = idx % kWave, s = (idx / kWave) % KB, nb = idx / (kWave * KB);
-    const int n = 16 * nb + l % 16, k0 = 32 * s + 8 * (l / 16);
-    bf16_t* dst = out + static_cast<size_t>(idx) * 8;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        bf16_t v = 0;
-        if (n < E)
-            v = Wg[static_cast<size_t>(k0 + i) * E + n];
-        else if (n == 64 && w_sg != nullptr)
-            v = w_sg[k0 + i];
-        dst[i] = v;
-    }
-}
-
 // Candidates from caller-supplied scores: one wave per token.
 __global__ __launch_bounds__(256) void topk_from_scores_kernel(
     const float* __restrict__ scores, int T, int E, int K, int32_t* __restrict__ topk_ids,
@@ -396,15 +370,6 @@ hipError_t launch_route_mfma(const void* X, const void* gate_packed, const float
     else
         ALLOCMOE_ROUTE_LAUNCH(false, 1);
 #undef ALLOCMOE_ROUTE_LAUNCH
-    return hipGetLastError();
-}
-
-hipError_t launch_pack_gate(const void* Wg, const void* w_sg, int d, int E, void* out,
-                            hipStream_t stream) {
-    const int total = kGateBlocks * (d / 32) * kWave;
-    hipLaunchKernelGGL(pack_gate_kernel, dim3((total + 255) / 256), dim3(256), 0, stream,
-                       static_cast<const bf16_t*>(Wg), static_cast<const bf16_t*>(w_sg), d, E,
-                       static_cast<bf16_t*>(out));
     return hipGetLastError();
 }
 

@@ -81,3 +81,24 @@ def test_quantise_columns_properties():
     assert np.all(np.abs(back - W) <= bound)
     # signs survive, zeros stay zeros
     assert np.array_equal(np.signbit(back[W != 0]), np.signbit(W[W != 0]))
+
+
+def test_quotient_with_one_correction():
+    """The packing kernel divides a weight (8 significant bits) by its column's scale (the
+    largest magnitude / 448, rounded) as q + (w - q sc) rc with q = w rc, rc = 1 / sc, all rounded
+    to fp32: the correctly rounded quotient for all 128 x 128 pairs of mantissas (exact rational
+    arithmetic; scaling by powers of two changes nothing)."""
+    def rn(x):   # to 24 significant bits, ties to even
+        if x == 0:
+            return x
+        n, d = abs(x.numerator), x.denominator
+        e = n.bit_length() - d.bit_length()
+        e -= Fraction(2) ** e > abs(x)
+        return round(x / Fraction(2) ** (e - 23)) * Fraction(2) ** (e - 23)
+
+    for a in range(128, 256):
+        sc = rn(Fraction(a, 448))
+        rc = rn(1 / sc)
+        for m in range(128, 256):
+            q = rn(m * rc)
+            assert rn(q - rn(q * sc - m) * rc) == rn(m / sc), (a, m)
