@@ -15,6 +15,8 @@
 
 namespace allocmoe {
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
 // Re-tiles the gate matrix Wg [d,E] (and, as column 64, the shared expert's
 // gate vector w_sg [d]) into the B-operand order of v_mfma_f32_16x16x32_bf16:
 // fragment (nb, s) = 64 lanes x 8 values, lane l holding
@@ -42,37 +44,43 @@ __device__ __forceinline__ void pack_gate(const PackGate& G, int64_t idx) {
 
 // workgroups of a launch that re-tile the gate matrix: whole rounds over the XCDs
 constexpr int kPackXcds = 8;
+constexpr int kPackGroup = 16;   // neighbouring column blocks of an XCD
 inline int gate_workgroups(const PackGate& G, int threads) {
     const int64_t pieces = static_cast<int64_t>(kGateBlocks) * (G.d / 32) * kWave;
     return static_cast<int>((pieces + threads * kPackXcds - 1) / (threads * kPackXcds) * kPackXcds);
 }
 
-// A lane gathers its 8 values (a wave-load covers 64 bytes of a row; consecutive waves go down
-// the rows, the neighbouring column block finds the other half of the lines in L2) and stores
-// them as one piece.  Bound by HBM: 64 experts of 2048 x 1408 and a shared expert, 2.2 GB in
-// and out, take 417 us (5.5 TB/s).  Whole 256-byte row pieces per wave, turned in registers, were slower
-// there (467 us).  All matrices of a layer go in one launch: with a launch each, a layer of
-// 16 experts of 576 x 320 took 17.4 us instead of 12.8, 32 experts of 1088 x 704 and a shared
-// expert 80.6 instead of 69.6.
+// A lane gathers its 8 values (a wave-load covers 64 bytes of a row; the four waves of a
+// workgroup go down the rows) and stores them as one piece, past the caches (the packed matrices
+// are larger than those).  Bound by HBM: 64 experts of 2048 x 1408 and a shared expert, 2.2 GB in
+// and out, take 388 us (5.7 TB/s).  An XCD takes neighbouring column blocks, so that the halves
+// of a line meet in its L2 and rows are read in runs of 1 KB (consecutive workgroups down the
+// rows of one column block instead, with plain stores: 418 us; 32 experts of 1088 x 704 and a
+// shared expert 70, now 46; 60 of 1472 x 1024 217, 183).  Whole 256-byte row pieces per wave,
+// turned in registers, were slower (467 us).  All matrices of a layer go in one launch: with a
+// launch each, a layer of 16 experts of 576 x 320 took 17.4 us instead of 12.8 (8.3 with the gate
+// matrix in the launch as well).
 __global__ __launch_bounds__(256) void pack_b_kernel(PackJobs jobs) {
     if (static_cast<int>(blockIdx.x) < jobs.gate.n_wg) {
         pack_gate(jobs.gate, static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x);
         return;
     }
-    int64_t bid = jobs.first_wg + blockIdx.x - jobs.gate.n_wg;
+    // (XCDs as in the 8-bit kernel: an XCD takes kPackGroup neighbouring column blocks of the same
+    // rows one after the other)
+    const int64_t wg = static_cast<int64_t>(blockIdx.x) - jobs.gate.n_wg;
+    const int xcd = wg % kPackXcds;
+    const int64_t idx = wg / kPackXcds;
+    int64_t bid = jobs.first_wg + (idx / kPackGroup * kPackXcds + xcd) * kPackGroup + idx % kPackGroup;
     int jn = 0;
-    while (bid >= jobs.job[jn].n_wg) bid -= jobs.job[jn++].n_wg;
+    while (bid >= jobs.job[jn].n_wg) {
+        bid -= jobs.job[jn++].n_wg;
+        if (jn == jobs.n) return;
+    }
     const PackJob& J = jobs.job[jn];
-    const int N = J.N, KB = J.Kd / 16, NB = N / 32;
-    const size_t total = static_cast<size_t>(J.G) * NB * KB * kWave;
-    const size_t idx = static_cast<size_t>(bid) * blockDim.x + threadIdx.x;
-    if (idx >= total) return;
-    const int l = idx % kWave;
-    size_t f = idx / kWave;
-    const int kb = f % KB;
-    f /= KB;
-    const int nb = f % NB;
-    const int g = f / NB;
+    const int N = J.N, NB = N / 32, KQ = J.Kd / 64;   // a workgroup: four fragments of a column block
+    const int l = lane_id(), nb = static_cast<int>(bid % NB);
+    const int kb = 4 * static_cast<int>(bid / NB % KQ) + threadIdx.x / kWave;
+    const int g = static_cast<int>(bid / NB / KQ);
     const int n = nb * 32 + (l % 32), k0 = kb * 16 + 8 * (l / 32);
     const bf16_t* src = static_cast<const bf16_t*>(J.W) + (static_cast<size_t>(g) * J.Kd + k0) * N + n;
     bf16_t* dst = static_cast<bf16_t*>(J.out) + static_cast<size_t>(g) * J.group_stride +
@@ -85,7 +93,7 @@ __global__ __launch_bounds__(256) void pack_b_kernel(PackJobs jobs) {
         const uint32_t hi = src[static_cast<size_t>(2 * i + 1) * N];
         packed[i] = lo | (hi << 16);
     }
-    *reinterpret_cast<uint4*>(dst) = make_uint4(packed[0], packed[1], packed[2], packed[3]);
+    __builtin_nontemporal_store(u32x4{packed[0], packed[1], packed[2], packed[3]}, reinterpret_cast<u32x4*>(dst));
 }
 
 // ---- 8-bit expert weights (E4M3 codes, one fp32 scale per output column)
@@ -106,11 +114,13 @@ __device__ __forceinline__ uint32_t e4m3_encode4(const float (&y)[4]) {
 // the registers (lanes, then LDS), and the codes are turned in LDS, wave by wave, so that
 // they leave as whole fragments (1 KB per store).  Longer columns are read twice, in chunks
 // of 2048 rows.  All six matrices of a layer go in one launch, so that the shared expert's few
-// strips fill up the others' last round.
+// strips fill up the others' last round.  Bound by HBM: 64 experts of 2048 x 1408 and a shared
+// expert, 1.7 GB in and out, take 326 us (5.2 TB/s).  Two workgroups to a unit, so that one reads
+// while the other converts or writes: with strips of 64 columns, which fill a unit's registers,
+// and 16-byte stores 64 bytes apart it was 455 us.  Pairs of strips to an XCD instead of groups
+// of 16: 368 us, with non-temporal loads (which do not wait in L2 for the line's other half) 403;
+// neighbouring strips on different XCDs 570; plain stores 375 instead of 368.
 constexpr int kPackWaves = 8, kPackWaveRows = 256, kPackRows = kPackWaves * kPackWaveRows, kPackCols = 32;
-constexpr int kPackGroup = 16;   // neighbouring strips of an XCD
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __global__ __launch_bounds__(kPackWaves* kWave, 4) void pack_fp8_kernel(PackFp8Jobs jobs) {
     __shared__ uint32_t wave_max[kPackWaves][kPackCols / 2];   // two columns' magnitudes each
@@ -287,14 +297,14 @@ hipError_t launch_pack_b(PackJobs jobs, hipStream_t stream) {
     int64_t wgs = 0;
     for (int j = 0; j < jobs.n; ++j) {
         PackJob& J = jobs.job[j];
-        J.n_wg = (static_cast<int64_t>(J.G) * (J.N / 32) * (J.Kd / 16) * kWave + 255) / 256;
+        J.n_wg = static_cast<int64_t>(J.G) * (J.N / 32) * (J.Kd / 64);
         wgs += J.n_wg;
     }
     // a launch has less than 2^32 threads: layers of 3.4e10 weights take a second one
-    constexpr int64_t kMaxWg = (1ll << 32) / 256 - 1;
+    constexpr int64_t kRound = kPackGroup * kPackXcds, kMaxWg = (1ll << 32) / 256 - 1;
     jobs.gate.n_wg = gate_workgroups(jobs.gate, 256);
     for (jobs.first_wg = 0; jobs.first_wg < wgs;) {
-        const int64_t n = std::min(kMaxWg - jobs.gate.n_wg, wgs - jobs.first_wg);
+        const int64_t n = std::min((kMaxWg - jobs.gate.n_wg) / kRound, (wgs - jobs.first_wg + kRound - 1) / kRound) * kRound;
         hipLaunchKernelGGL(pack_b_kernel, dim3(static_cast<unsigned>(jobs.gate.n_wg + n)), dim3(256), 0, stream, jobs);
         jobs.first_wg += n;
         jobs.gate.n_wg = 0;   // (done by the first launch)
