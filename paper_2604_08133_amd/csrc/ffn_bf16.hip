@@ -8,10 +8,14 @@
 // HBM.  A workgroup owns one (row tile of <= 32 rows, block of 32 output
 // columns); its 4 waves split the contraction dimension, each streaming its
 // share of the packed weight fragments straight from global memory into MFMA B
-// operands (1 KB contiguous per wave-load, every byte read once), with many
-// independent loads in flight.  The A operand (<= 32 activation rows, L2
-// resident) is gathered per lane.  Partial accumulators meet in LDS in a fixed
-// order, so results are bitwise reproducible.
+// operands (1 KB contiguous per wave-load, every byte read once).  The loads form a ring: an
+// entry is filled again as soon as its products are issued, so that the same number of them is
+// in flight from the first to the last (batches of 8 steps, the next one issued behind the
+// products of the one before, and the column scales read at the end: 32 tokens, 96 pairs, 64
+// experts of 2048 x 1408 with 8-bit weights 98.3 us a layer, now 92.3; 64 tokens 125.9, 117.0;
+// bf16 1 token 35.6, 33.5; from 2 tokens on the bf16 launches stand at 0.9 of the read rate
+// either way).  The A operand (<= 32 activation rows, L2 resident) is gathered per lane.
+// Partial accumulators meet in LDS in a fixed order, so results are bitwise reproducible.
 #include <type_traits>
 
 #include "common.hpp"
@@ -23,7 +27,6 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
 constexpr int kStreamWaves = 4;
-constexpr int kStreamUnroll = 8;
 
 // 32x32 accumulator layout of v_mfma_f32_32x32x16_bf16: register r of lane l
 // holds C[8*(r/4) + 4*(l/32) + r%4][l%32].
@@ -47,174 +50,208 @@ __device__ __forceinline__ bf16x8 fp8x8_to_bf16x8(uint32_t lo, uint32_t hi) {
 // 16-byte load then holds its fragments of TWO k16 steps, the codes are widened to bf16
 // in registers (exact) and the column scale multiplies the fp32 sum at the end.  The
 // waves take blocks of 32 k round-robin; Kd must be a multiple of 128.
-template <bool SWIGLU, bool FP8>
-__global__ __launch_bounds__(kStreamWaves* kWave) void ffn_bf16_stream_kernel(StreamGroup g0,
-                                                                             StreamGroup g1) {
-    constexpr int NACC = SWIGLU ? 2 : 1;
-    __shared__ float red[kStreamWaves][NACC][16][kWave];
+//
+// UNROLL: loads per weight stream that a wave has in flight.
+// STREAMS: weight streams of a workgroup (SWIGLU: W1 and W3 of a column block; else one or two
+// neighbouring column blocks).
+template <bool SWIGLU, bool FP8, int UNROLL, int STREAMS>
+__global__ __launch_bounds__(kStreamWaves* kWave) void ffn_bf16_stream_kernel(StreamGroup g0, StreamGroup g1) {
+    static_assert(!SWIGLU || STREAMS == 2, "W1 and W3");
+    constexpr int kBlocks = SWIGLU ? 1 : STREAMS;   // column blocks of a workgroup
+    __shared__ float red[kStreamWaves][STREAMS][16][kWave];
 
     // The grid is the shared expert's workgroups followed by the routed group's: the
     // shared expert has few workgroups with a long stream each, which should start
     // at once and run beside the routed ones instead of forming the launch's tail.
     const bool dense = static_cast<int64_t>(blockIdx.x) < g1.n_wg;
-    const StreamGroup& g = dense ? g1 : g0;
+    // (field by field, so that all arguments of both groups are loaded at once)
+#define ALLOCMOE_FIELD(f) (dense ? g1.f : g0.f)
+    const char* __restrict__ A = static_cast<const char*>(ALLOCMOE_FIELD(A));
+    const char* __restrict__ Bp = static_cast<const char*>(ALLOCMOE_FIELD(Bp));
+    const int32_t* __restrict__ row_map = ALLOCMOE_FIELD(row_map);
+    const int32_t* __restrict__ tile_info = ALLOCMOE_FIELD(tile_info);
+    const float* __restrict__ scales = ALLOCMOE_FIELD(scale);
+    bf16_t* C = static_cast<bf16_t*>(ALLOCMOE_FIELD(C));
+    const size_t group_stride = ALLOCMOE_FIELD(group_stride);
+    const int lda = ALLOCMOE_FIELD(lda), ldc = ALLOCMOE_FIELD(ldc), Kd = ALLOCMOE_FIELD(Kd), N = ALLOCMOE_FIELD(N);
+    const int M_dense = ALLOCMOE_FIELD(M_dense);
+#undef ALLOCMOE_FIELD
     const int bid = dense ? blockIdx.x : blockIdx.x - static_cast<unsigned>(g1.n_wg);
-    const bf16_t* __restrict__ A = static_cast<const bf16_t*>(g.A);
-    const bf16_t* __restrict__ Bp = static_cast<const bf16_t*>(g.Bp);
-    const int32_t* __restrict__ row_map = g.row_map;
-    const int32_t* __restrict__ tile_info = g.tile_info;
-    const int lda = g.lda, Kd = g.Kd, N = g.N, ldc = g.ldc, M_dense = g.M_dense;
-    const size_t group_stride = g.group_stride;
-    void* Cv = g.C;
-
-    const int n_blocks = N / 32;
+    const int n_blocks = N / (32 * kBlocks);
     const int tile = bid / n_blocks, nb = bid % n_blocks;
     int e, row0, rows;
     if (tile_info != nullptr) {
-        if (tile >= tile_info[0]) return;
+        // (the entry is inside the map whether the batch fills it or not: both loads at once)
+        const int n_tiles = tile_info[0];
         const int32_t* ent = tile_info + kTileHdr + 4 * static_cast<size_t>(tile);
         e = ent[0];
         row0 = ent[1];
         rows = ent[2];
+        asm volatile("" : : "s"(n_tiles), "s"(e), "s"(row0), "s"(rows));
+        if (tile >= n_tiles) return;
     } else {
         e = 0;
         row0 = tile * 32;
         if (row0 >= M_dense) return;
         rows = min(32, M_dense - row0);
     }
-    const int lane = lane_id(), wave = threadIdx.x / kWave;
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     constexpr int kStepK = FP8 ? 32 : 16;   // k per load
     const int KB = Kd / kStepK;             // loads per stream in total
-    const int steps = KB / kStreamWaves;    // per wave (Kd is a multiple of 64; 128 with FP8)
-    // The waves take the k16 steps round-robin (wave w: steps w, w+4, ...), so at
-    // any time the workgroup reads one contiguous run of each weight stream.
+    // The waves take the steps round-robin (wave w: steps w, w + kStreamWaves, ...), so at any time
+    // the workgroup reads one contiguous run of each weight stream.
+    const int steps = (KB - wave + kStreamWaves - 1) / kStreamWaves;   // of this wave
 
-    // packed B: for this expert and column block, KB fragments of 64 x bf16x8
-    // (W1 stream, then for SWIGLU the W3 stream)
-    // (a stream of one column block holds Kd * 32 elements: 2 bytes each, or 1 with FP8)
-    const bf16x8* b1 = reinterpret_cast<const bf16x8*>(
-                           reinterpret_cast<const char*>(Bp) +
-                           (static_cast<size_t>(e) * group_stride +
-                            static_cast<size_t>(nb) * (static_cast<size_t>(NACC) * Kd * 32)) *
-                               (FP8 ? 1 : 2)) +
-                       static_cast<size_t>(wave) * kWave + lane;
-    const bf16x8* b3 = b1 + static_cast<size_t>(KB) * kWave;
-    constexpr size_t kStepB = static_cast<size_t>(kStreamWaves) * kWave;   // fragments per round
-
-    // A: lane (m = l%32, kg = l/32) reads 8 consecutive k of its row per step
+    // A: lane (m = l%32, kg = l/32) reads 8 consecutive k of its row per step (rows past the
+    // end: the last one again, not stored)
     const int m = lane % 32, kg = lane / 32;
-    const bool a_ok = m < rows;
-    long src = 0;
-    if (a_ok) {
-        const int r = row0 + m;
-        src = row_map ? row_map[r] : r;
+    int src = row0 + min(m, rows - 1);
+    if (row_map) src = row_map[src];
+    // FP8: the column scales of the sums this thread finishes (below)
+    float scale[STREAMS];
+    if constexpr (FP8) {
+        const float* sc = scales + static_cast<size_t>(e) * (SWIGLU ? 2 : 1) * N + nb * 32 * kBlocks + m;
+#pragma unroll
+        for (int j = 0; j < STREAMS; ++j) scale[j] = sc[j * (SWIGLU ? N : 32)];
     }
-    const bf16x8* ap = reinterpret_cast<const bf16x8*>(A + static_cast<size_t>(src) * lda) +
-                       wave * (kStepK / 8) + kg;
-    constexpr int kStepA = kStreamWaves * (kStepK / 8);
-
-    f32x16 acc1 = {0}, acc3 = {0};
-    const bf16x8 zero = {0};
-    // a batch of N steps: all loads first (they are in flight together), then the MFMAs
-    auto batch = [&](int s, auto n_const) {
-        constexpr int N = decltype(n_const)::value;
-        bf16x8 av[N], av2[N], w1[N], w3[N];
+    // packed B: for this expert and column block, KB fragments of 64 x 16 bytes (the W1 stream,
+    // then for SWIGLU the W3 stream, else the next column block's; a stream holds Kd * 32
+    // elements: 2 bytes each, or 1 with FP8).  Through buffer loads: scalar base and step
+    // offset, and a step past the end reads zeros.
+    const uint32_t stream_bytes = static_cast<uint32_t>(KB) * 1024u;
+    const char* b0 = Bp + (static_cast<size_t>(e) * group_stride +
+                           static_cast<size_t>(nb) * (static_cast<size_t>(STREAMS) * Kd * 32)) * (FP8 ? 1 : 2);
+    __amdgpu_buffer_rsrc_t rs[STREAMS];
 #pragma unroll
-        for (int u = 0; u < N; ++u) {
-            w1[u] = __builtin_nontemporal_load(b1 + static_cast<size_t>(s + u) * kStepB);
-            if (SWIGLU) w3[u] = __builtin_nontemporal_load(b3 + static_cast<size_t>(s + u) * kStepB);
-            av[u] = a_ok ? ap[(s + u) * kStepA] : zero;
-            if (FP8) av2[u] = a_ok ? ap[(s + u) * kStepA + 2] : zero;
-        }
+    for (int j = 0; j < STREAMS; ++j)
+        rs[j] = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(b0 + static_cast<size_t>(j) * stream_bytes), 0,
+                                                  stream_bytes, 0x00020000);
+    typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4;
+    constexpr int kNonTemporal = 2;
+    i32x4 w[UNROLL][STREAMS];
+    bf16x8 av[UNROLL][FP8 ? 2 : 1];
+    auto load_w = [&](int u, int step) {
 #pragma unroll
-        for (int u = 0; u < N; ++u) {
-            if (FP8) {
+        for (int j = 0; j < STREAMS; ++j)
+            w[u][j] = __builtin_amdgcn_raw_buffer_load_b128(rs[j], lane * 16, (step * kStreamWaves + wave) * 1024, kNonTemporal);
+    };
+    const bf16x8* ap;
+    auto load_a = [&](int u, int step) {   // (past the end: the last step's again)
+        const bf16x8* p = ap + min(step, steps - 1) * (kStreamWaves * (kStepK / 8));
+        av[u][0] = p[0];
+        if constexpr (FP8) av[u][1] = p[2];
+    };
+    f32x16 acc[STREAMS];
+#pragma unroll
+    for (int j = 0; j < STREAMS; ++j) acc[j] = f32x16{0};
+    auto multiply = [&](int u) {
+#pragma unroll
+        for (int j = 0; j < STREAMS; ++j) {
+            if constexpr (FP8) {
                 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-                const u32x4 q1 = __builtin_bit_cast(u32x4, w1[u]);
-                acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[u], fp8x8_to_bf16x8(q1[0], q1[1]), acc1, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av2[u], fp8x8_to_bf16x8(q1[2], q1[3]), acc1, 0, 0, 0);
-                if (SWIGLU) {
-                    const u32x4 q3 = __builtin_bit_cast(u32x4, w3[u]);
-                    acc3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[u], fp8x8_to_bf16x8(q3[0], q3[1]), acc3, 0, 0, 0);
-                    acc3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av2[u], fp8x8_to_bf16x8(q3[2], q3[3]), acc3, 0, 0, 0);
-                }
+                const u32x4 q = __builtin_bit_cast(u32x4, w[u][j]);
+                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[u][0], fp8x8_to_bf16x8(q[0], q[1]), acc[j], 0, 0, 0);
+                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[u][FP8 ? 1 : 0], fp8x8_to_bf16x8(q[2], q[3]), acc[j], 0, 0, 0);
             } else {
-                acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[u], w1[u], acc1, 0, 0, 0);
-                if (SWIGLU) acc3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[u], w3[u], acc3, 0, 0, 0);
+                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[u][0], __builtin_bit_cast(bf16x8, w[u][j]), acc[j], 0, 0, 0);
             }
         }
     };
+    // UNROLL steps in flight all the time: an entry is loaded again as soon as it is used.  The
+    // first weights do not wait for the row map.
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) load_w(u, u);
+    __builtin_amdgcn_sched_barrier(0);
+    ap = reinterpret_cast<const bf16x8*>(A + static_cast<size_t>(src) * lda * 2) + wave * (kStepK / 8) + kg;
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) load_a(u, u);
+    __builtin_amdgcn_sched_barrier(0);
     int s = 0;
-    for (; s + kStreamUnroll <= steps; s += kStreamUnroll)
-        batch(s, std::integral_constant<int, kStreamUnroll>{});
-    static_assert(kStreamUnroll == 8, "the switch below lists the short last batches");
-    switch (steps - s) {   // uniform
-        case 7: batch(s, std::integral_constant<int, 7>{}); break;
-        case 6: batch(s, std::integral_constant<int, 6>{}); break;
-        case 5: batch(s, std::integral_constant<int, 5>{}); break;
-        case 4: batch(s, std::integral_constant<int, 4>{}); break;
-        case 3: batch(s, std::integral_constant<int, 3>{}); break;
-        case 2: batch(s, std::integral_constant<int, 2>{}); break;
-        case 1: batch(s, std::integral_constant<int, 1>{}); break;
-        default: break;
-    }
+    auto pass = [&]() {
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) {
+            multiply(u);
+            load_w(u, s + UNROLL + u);
+            load_a(u, s + UNROLL + u);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        s += UNROLL;
+    };
+    // (The first pass by itself: its loads stand in another order, and in a loop the compiler
+    // would wait for either.)
+    if (s + UNROLL < steps) pass();
+    while (s + UNROLL < steps) pass();
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u)
+        if (s + u < steps) multiply(u);   // uniform
 
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        red[wave][0][r][lane] = acc1[r];
-        if (SWIGLU) red[wave][NACC - 1][r][lane] = acc3[r];
-    }
+    for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int j = 0; j < STREAMS; ++j) red[wave][j][r][lane] = acc[j][r];
     __syncthreads();
-    // 16 x 64 accumulator slots, 256 threads: 4 slots each, waves summed in order
+    // 16 x 64 accumulator slots per stream (SwiGLU: both streams of a slot to one thread),
+    // waves summed in order
+    constexpr int kSums = STREAMS / kBlocks, kTurns = 16 * kBlocks / kStreamWaves;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int slot = threadIdx.x + 256 * q, r = slot / kWave, l = slot % kWave;
-        float v1 = 0.f, v3 = 0.f;
+    for (int q = 0; q < kTurns; ++q) {
+        const int slot = q * kStreamWaves + wave, j0 = q * kStreamWaves / 16, r = slot % 16;
+        float v[kSums];
 #pragma unroll
-        for (int w = 0; w < kStreamWaves; ++w) {
-            v1 += red[w][0][r][l];
-            if (SWIGLU) v3 += red[w][NACC - 1][r][l];
+        for (int j = 0; j < kSums; ++j) {
+            v[j] = 0.f;
+#pragma unroll
+            for (int x = 0; x < kStreamWaves; ++x) v[j] += red[x][j0 + j][r][lane];
+            if constexpr (FP8) v[j] *= scale[j0 + j];
         }
-        const int mr = acc_row(r, l), n = nb * 32 + (l % 32);
-        if (FP8) {   // the column scales
-            const float* sc = g.scale + static_cast<size_t>(e) * NACC * N;
-            v1 *= sc[n];
-            if (SWIGLU) v3 *= sc[N + n];
-        }
+        const int mr = acc_row(r, lane);
         if (mr < rows) {
-            const size_t off = static_cast<size_t>(row0 + mr) * ldc + n;
-            if (SWIGLU)
-                static_cast<bf16_t*>(Cv)[off] = f32_to_bf16(v1 * v3 * __builtin_amdgcn_rcpf(1.f + __expf(-v1)));
-            else
-                static_cast<bf16_t*>(Cv)[off] = f32_to_bf16(v1);
+            const size_t off = static_cast<size_t>(row0 + mr) * ldc + (nb * kBlocks + j0) * 32 + m;
+            float out = v[0];
+            if constexpr (SWIGLU) out = v[0] * v[kSums - 1] * __builtin_amdgcn_rcpf(1.f + __expf(-v[0]));
+            C[off] = f32_to_bf16(out);
         }
     }
 }
 
 hipError_t launch_ffn_bf16_stream(bool swiglu, StreamGroup routed, StreamGroup shared,
                                   hipStream_t stream) {
-    auto count = [](StreamGroup& g) {
-        const int64_t tiles = g.A == nullptr ? 0 : (g.tile_info ? g.max_tiles : (g.M_dense + 31) / 32);
-        g.n_wg = tiles * (g.N / 32);
+    // workgroups with `blocks` column blocks each
+    auto count = [&](int blocks) {
+        for (StreamGroup* g : {&routed, &shared}) {
+            const int64_t tiles = g->A == nullptr ? 0 : (g->tile_info ? g->max_tiles : (g->M_dense + 31) / 32);
+            g->n_wg = tiles * (g->N / (32 * blocks));
+        }
+        return routed.n_wg + shared.n_wg;
     };
-    count(routed);
-    count(shared);
-    const int64_t total = routed.n_wg + shared.n_wg;
+    int64_t total = count(1);
     if (total <= 0) return hipSuccess;
-    const dim3 grid(static_cast<unsigned>(total)), block(kStreamWaves * kWave);
     const bool fp8 = (routed.A ? routed.scale : shared.scale) != nullptr;
     if (routed.A && shared.A && (routed.scale != nullptr) != (shared.scale != nullptr))
         return hipErrorInvalidValue;   // one weight format per launch
     if (fp8 && ((routed.A && routed.Kd % 128) || (shared.A && shared.Kd % 128)))
         return hipErrorInvalidValue;
+    // Second half, 8-bit weights: a column block is a short stream (45 KB at 1408 k); two of them
+    // a workgroup unless that leaves compute units idle (2048 x 1408, 64 experts: 4 tokens 43.8
+    // us with two, 42.1 with one and the whole stream in flight, 1: 31.6, 29.5; 64 tokens: 117.0,
+    // 125.6).  bf16: one (32 tokens: 156.4 with two, 155.2).
+    constexpr int64_t kFewWorkgroups = 1024;
+    const bool pairs = !swiglu && fp8 && total > kFewWorkgroups;
+    if (pairs) total = count(2);   // (N is a multiple of 64)
+    const dim3 grid(static_cast<unsigned>(total)), block(kStreamWaves * kWave);
+#define ALLOCMOE_STREAM_LAUNCH(...) \
+    hipLaunchKernelGGL((ffn_bf16_stream_kernel<__VA_ARGS__>), grid, block, 0, stream, routed, shared)
     if (swiglu && fp8)
-        hipLaunchKernelGGL((ffn_bf16_stream_kernel<true, true>), grid, block, 0, stream, routed, shared);
+        ALLOCMOE_STREAM_LAUNCH(true, true, 6, 2);
     else if (swiglu)
-        hipLaunchKernelGGL((ffn_bf16_stream_kernel<true, false>), grid, block, 0, stream, routed, shared);
+        ALLOCMOE_STREAM_LAUNCH(true, false, 8, 2);
+    else if (pairs)
+        ALLOCMOE_STREAM_LAUNCH(false, true, 6, 2);
     else if (fp8)
-        hipLaunchKernelGGL((ffn_bf16_stream_kernel<false, true>), grid, block, 0, stream, routed, shared);
+        ALLOCMOE_STREAM_LAUNCH(false, true, 12, 1);
     else
-        hipLaunchKernelGGL((ffn_bf16_stream_kernel<false, false>), grid, block, 0, stream, routed, shared);
+        ALLOCMOE_STREAM_LAUNCH(false, false, 8, 1);
+#undef ALLOCMOE_STREAM_LAUNCH
     return hipGetLastError();
 }
 
