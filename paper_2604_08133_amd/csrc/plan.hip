@@ -20,6 +20,8 @@
 // "token keeps e" is a 64-bit word M[e][batch]; the row of pair (t, e) is
 //   offset[e] + (kept pairs of e in earlier batches) + popcount(M[e][batch] below lane t).
 #include <algorithm>
+#include <type_traits>
+#include <utility>
 
 #include "common.hpp"
 #include "kernels.hpp"
@@ -317,44 +319,58 @@ __device__ void tilemap_phase(PlanShared& sh, int E, int bm, int32_t* __restrict
 }
 
 // ---------------------------------------------------------------------------
-// Fast path (T <= 8192 and at most 48 pool keys per thread): the same two
-// phases, but the pool keys are read from global memory once and stay in
-// registers for every pass, and the keep counts, ballot words and prefixes live
-// in LDS, so no phase waits on a global round trip of its own.
+// Fast path (T <= 8192 and at most 48 pool keys per thread): the same two phases, but
+// everything is read from global memory once: the pool keys into registers, where they stay
+// for every pass, the candidate ids into LDS (one byte each), where the keep counts, ballot
+// words and prefixes live as well.
 //
-// Selection: thread i owns the contiguous slice [i*C, (i+1)*C) of the pool in
-// (token, rank) order, so "equal keys that precede" is a block-wide exclusive
-// scan of per-thread counts plus a walk through the thread's own keys.
+// Selection: entry p of the pool (token p / P, rank Kb + p % P) belongs to thread p % NT, so
+// that loads are coalesced and a wave's ballot over its entries is a word of a bit map in pool
+// order.  A pass histograms the keys in [lo, hi]; every wave then finds the bin with the
+// wanted rank by itself (no exchange, one barrier a pass).  As soon as a bin holds at most 64
+// keys they are ranked directly, as (key, complement of p): the order (score descending, token
+// ascending, rank ascending) as one number, so that ties need nothing further.  The result is
+// the last pair kept; a second ballot compares all entries with it, and a token's keep count is
+// the number of its bits.  More than 64 equal keys at the threshold: the last one kept is found
+// by counting the bits of a ballot map of the equal ones.
 // Dispatch: the 64 x 64 bit matrix "token t of the batch keeps expert e" is
 // transposed with a 6-stage butterfly of lane exchanges instead of 64 ballots.
+//
+// Bound by latency: a chain of loads, barriers and LDS round trips on one compute unit.  Phases
+// of 333 tokens with 8 candidates, us: loads 4.4, range 1.0, passes 6.0, counts 2.6, words and
+// prefixes 1.7, rows 2.0 with thread-contiguous slices of the pool staged through LDS, three
+// passes that ended at a single key and block-wide scans.
 constexpr int kFastMaxT = 8192;
 constexpr int kFastMaxKeys = 48;
-// Pools up to this size are ranked directly (quadratic in the pool); measured on
-// DeepSeek-V2-Lite shapes the histogram search is faster from about 300 entries on
-// (T = 64, pool 320: 25 us direct, 17 us by histogram; pool 240: 15 against 18).
-constexpr int kDirectPool = 256;
+constexpr int kCollect = 64;       // keys of a bin that a wave ranks directly
 constexpr int kMaxK = 16;          // candidates per token the interface allows
+constexpr int kMaxPasses = 4;      // 32 key bits, 9 or 10 a pass
 
+template <int NT>
 struct FastShared {
-    uint32_t hist[kBins];
-    uint32_t wave_tot[kPlanWaves];
-    uint32_t red_lo[kPlanWaves];
-    uint32_t red_hi[kPlanWaves];
-    uint32_t pick_bin, pick_rank, pick_count;
-    int32_t expert_off[kWave + 1];
-    int32_t seg_tot[kPlanWaves][kWave];
-    int32_t cnt[kFastMaxT];        // keep_count
+    static constexpr int kWaves = NT / kWave;
+    static constexpr int kTokens = NT == 1024 ? kFastMaxT : 1024;
+    static constexpr int kIds = NT == 1024 ? 49152 : kTokens * kMaxK;
+    static constexpr int kBinsLog2 = NT == 1024 ? 10 : 9;
+    static constexpr int kWords = kFastMaxKeys * kWaves;   // of a bit map over the pool
     union {
-        struct {
-            uint64_t words[kFastMaxT];   // [batch][expert]
-            int32_t prefix[kFastMaxT];   // [batch][expert]
+        struct {   // selection
+            uint32_t hist[kMaxPasses][1 << kBinsLog2];
+            uint64_t equal[kWords];
+            uint64_t collected[kCollect];
         };
-        // during the selection, before the dispatch arrays are needed: the candidate
-        // scores, copied in with coalesced loads
-        float stage[kFastMaxT * 3];
+        uint64_t words[kTokens];       // dispatch: [batch][expert]
     };
+    uint64_t bits[kWords + 1];         // pool entries kept
+    uint32_t n_collected;
+    uint32_t red_lo[kWaves], red_hi[kWaves];
+    int32_t expert_off[kWave + 1];
+    int32_t seg_tot[kWaves][kWave];
+    uint8_t cnt[kTokens];              // keep_count
+    uint16_t prefix[kTokens];          // [batch][expert]
+    uint32_t ids[kIds / 4 + 4];        // candidate ids, one byte each, [token][rank]
 };
-constexpr int kStageFloats = kFastMaxT * 3;
+static_assert(sizeof(FastShared<1024>) <= 160 * 1024, "LDS of a compute unit");
 
 // Transpose of a 64 x 64 bit matrix held one row per lane: afterwards lane e
 // holds column e (bit t = former bit e of lane t).
@@ -381,17 +397,162 @@ __device__ __forceinline__ uint64_t wave_transpose64(uint64_t x) {
     return x;
 }
 
+// f(q) for every q with entries of the pool (q a compile-time constant: the keys stay in registers)
+template <int NT, typename F, int... Q>
+__device__ __forceinline__ void for_entries(int n_pool, F f, std::integer_sequence<int, Q...>) {
+    (void)((Q * NT < n_pool && (f(std::integral_constant<int, Q>{}), true)) && ...);
+}
+template <int NT, typename F>
+__device__ __forceinline__ void for_entries(int n_pool, F f) {
+    for_entries<NT>(n_pool, f, std::make_integer_sequence<int, kFastMaxKeys>{});
+}
+
+// The last pool entry kept: entries are kept iff their key is larger than `key`, or equal and
+// their index is at most `index`.
+struct Threshold {
+    uint32_t key, index;
+};
+
+// Wave-wide: the position i with above(i) < r <= above(i) + count(i), lane l holding the counts of
+// positions l * N .. + N - 1 in c.  Returns i, and in `above` the sum before it.
+template <int N>
+__device__ __forceinline__ int wave_find_rank(const uint32_t (&c)[N], uint32_t r, uint32_t& above) {
+    uint32_t sum = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) sum += c[i];
+    const uint32_t incl = static_cast<uint32_t>(wave_scan_incl(static_cast<int>(sum)));
+    const int src = __builtin_ctzll(__ballot(incl >= r) | (1ull << (kWave - 1)));
+    uint32_t run = incl - sum;
+    int at = 0;
+#pragma unroll
+    for (int i = 0; i < N - 1; ++i) {
+        const bool past = at == i && run + c[i] < r;
+        run += past ? c[i] : 0u;
+        at += past ? 1 : 0;
+    }
+    above = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(run), src));
+    return src * N + __builtin_amdgcn_readlane(at, src);
+}
+
+template <int NT>
+__device__ __forceinline__ Threshold find_threshold(FastShared<NT>& sh, const uint32_t (&key)[kFastMaxKeys],
+                                                    int n_pool, uint32_t want) {
+    using Sh = FastShared<NT>;
+    constexpr int NW = NT / kWave, kBinsLane = (1 << Sh::kBinsLog2) / kWave;
+    const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    uint32_t lo = 0xFFFFFFFFu, hi = 0u, r = want, count = n_pool;
+    if (count > kCollect) {
+        // ---- range of the keys (entries past the end hold 0, below every key)
+        for_entries<NT>(n_pool, [&](auto q_const) {
+            constexpr int q = decltype(q_const)::value;
+            lo = min(lo, key[q] - 1u);
+            hi = max(hi, key[q]);
+        });
+        lo = wave_min_u32(lo);
+        hi = wave_max_u32(hi);
+        if (lane == 0) {
+            sh.red_lo[wave] = lo;
+            sh.red_hi[wave] = hi;
+        }
+        __syncthreads();
+        lo = wave_min_u32(sh.red_lo[lane % NW]) + 1u;
+        hi = wave_max_u32(sh.red_hi[lane % NW]);
+    } else {
+        lo = 1u;
+        hi = 0xFFFFFFFFu;
+        __syncthreads();   // (the cleared counters)
+    }
+    // ---- narrowing passes: rank r counts from the top of [lo, hi]
+    for (int pass = 0; count > kCollect && lo < hi; ++pass) {
+        const int bits = 32 - __builtin_clz(hi - lo);   // width <= 2^bits
+        const int shift = max(0, bits - Sh::kBinsLog2);
+        uint32_t* hist = sh.hist[pass];   // (bins from the top of the range)
+        for_entries<NT>(n_pool, [&](auto q_const) {
+            constexpr int q = decltype(q_const)::value;
+            if (key[q] >= lo && key[q] <= hi) atomicAdd(&hist[(hi - key[q]) >> shift], 1u);
+        });
+        __syncthreads();
+        uint32_t c[kBinsLane], above;
+#pragma unroll
+        for (int i = 0; i < kBinsLane; i += 4) {
+            const uint4 v = *reinterpret_cast<const uint4*>(&hist[lane * kBinsLane + i]);
+            c[i] = v.x;
+            c[i + 1] = v.y;
+            c[i + 2] = v.z;
+            c[i + 3] = v.w;
+        }
+        const int bin = wave_find_rank(c, r, above);
+        count = hist[bin];
+        r -= above;
+        hi -= static_cast<uint32_t>(bin) << shift;
+        const uint32_t span_m1 = (1u << shift) - 1u;
+        lo = hi - lo > span_m1 ? hi - span_m1 : lo;
+    }
+    if (count <= kCollect) {
+        // ---- rank the bin's keys directly
+        uint32_t n = 0;
+        for_entries<NT>(n_pool, [&](auto q_const) {
+            constexpr int q = decltype(q_const)::value;
+            n += key[q] >= lo && key[q] <= hi ? 1u : 0u;
+        });
+        uint32_t slot = n ? atomicAdd(&sh.n_collected, n) : 0u;   // (the order does not matter)
+        if (__ballot(n != 0u)) {
+            for_entries<NT>(n_pool, [&](auto q_const) {
+                constexpr int q = decltype(q_const)::value;
+                if (key[q] >= lo && key[q] <= hi) {
+                    if (slot < kCollect)
+                        sh.collected[slot] = (static_cast<uint64_t>(key[q]) << 32) | ~static_cast<uint32_t>(q * NT + tid);
+                    ++slot;
+                }
+            });
+        }
+        __syncthreads();
+        const uint64_t mine = lane < static_cast<int>(count) ? sh.collected[lane] : 0ull;
+        const int mine_lo = static_cast<int>(static_cast<uint32_t>(mine)), mine_hi = static_cast<int>(mine >> 32);
+        uint32_t before = 0;
+        for (int l = 0; l < static_cast<int>(count); ++l) {
+            const uint64_t other =
+                static_cast<uint32_t>(__builtin_amdgcn_readlane(mine_lo, l)) |
+                (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(mine_hi, l))) << 32);
+            before += other > mine ? 1u : 0u;
+        }
+        const int last = __builtin_ctzll(__ballot(before == r - 1) | (1ull << (kWave - 1)));
+        return {static_cast<uint32_t>(__builtin_amdgcn_readlane(mine_hi, last)),
+                ~static_cast<uint32_t>(__builtin_amdgcn_readlane(mine_lo, last))};
+    }
+    if (r == count) return {lo, 0xFFFFFFFFu};   // no tie is split: a plain threshold
+    // ---- more equal keys than a wave ranks: the r-th of them in pool order
+    for_entries<NT>(n_pool, [&](auto q_const) {
+        constexpr int q = decltype(q_const)::value;
+        const uint64_t eq = __ballot(key[q] == lo);
+        if (lane == 0) sh.equal[q * NW + wave] = eq;
+    });
+    __syncthreads();
+    constexpr int kPer = Sh::kWords / kWave;
+    static_assert(Sh::kWords % kWave == 0, "words per lane");
+    uint32_t c[kPer], above;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int w = lane * kPer + i;
+        c[i] = w * kWave < n_pool ? static_cast<uint32_t>(__popcll(sh.equal[w])) : 0u;
+    }
+    const int word = wave_find_rank(c, r, above);
+    const uint64_t in_word = sh.equal[word];
+    // (lane = bit)
+    const bool hit = ((in_word >> lane) & 1ull) && __popcll(in_word & ((2ull << lane) - 1ull)) == static_cast<int>(r - above);
+    return {lo, static_cast<uint32_t>(word * kWave + __builtin_ctzll(__ballot(hit) | (1ull << (kWave - 1))))};
+}
+
 template <bool SELECT, bool DISPATCH, int NT>
 __global__ __launch_bounds__(NT) void plan_fast_kernel(
     const float* topk_s, const int32_t* topk_ids, int T, int K, int Kb, int64_t B, int E,
     int32_t* keep_count, int32_t* expert_offsets, int32_t* row_token, int32_t* row_rank,
     int32_t* inv_row, int bm, int32_t* tile_info) {
-    __shared__ FastShared sh;
+    using Sh = FastShared<NT>;
+    __shared__ Sh sh;
     constexpr int NW = NT / kWave;            // waves
-    constexpr int NBINS = 2 * NT;             // histogram bins: two per thread
-    constexpr int NBINS_LOG2 = NT == 1024 ? 11 : 9;
     static_assert(NT == 1024 || NT == 256, "two block sizes");
-    const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+    const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     // Launched as several workgroups (only where nothing else wants the compute units),
     // every workgroup runs the selection and the counting phases redundantly, on its own
     // unit and in its own LDS, with identical results and no exchange between them, and
@@ -399,246 +560,116 @@ __global__ __launch_bounds__(NT) void plan_fast_kernel(
     // scattered stores a single compute unit can issue; workgroup 0 writes the rest.
     const int n_groups = gridDim.x, group = blockIdx.x;
     const bool writer = group == 0;
+    const int P = K - Kb, n_pool = SELECT ? T * P : 0;
+    const int64_t want = B - static_cast<int64_t>(T) * Kb;
+    const bool search = SELECT && want > 0 && want < n_pool;
 
-    // Candidate ids of this wave's batches (lane = token), all loaded up front so that
-    // the loads are in flight together, and kept in registers for both uses in the
-    // dispatch.  The 4-wave kernel (few tokens, one wave per SIMD, registers to spare)
-    // issues them before the selection, whose result they do not depend on; the 16-wave
-    // kernel after it.  Wider candidate rows than kIdsK fall back to loading them where
-    // they are used.
-    constexpr int kIdsK = 8;
-    constexpr int kMaxBatches = (NT == 1024 ? kFastMaxT : 1024) / kWave / NW;
-    const bool ids_held = DISPATCH && K <= kIdsK;
-    int held[kMaxBatches][kIdsK];
-    auto load_held = [&]() {
-        if (!ids_held) return;
+    // ---- all loads first: the pool's scores, then the candidate ids
+    float score[kFastMaxKeys];
+    if (search) {
+        const uint32_t inv_p = 0xFFFFFFFFu / static_cast<uint32_t>(P) + 1u;   // p / P = p inv_p >> 32 (P = 1: 0)
+        for_entries<NT>(n_pool, [&](auto q_const) {
+            constexpr int q = decltype(q_const)::value;
+            const int i = min(q * NT + tid, n_pool - 1);
+            const int t = P == 1 ? i : static_cast<int>(__umulhi(static_cast<uint32_t>(i), inv_p));
+            score[q] = topk_s[static_cast<size_t>(t) * K + Kb + (i - t * P)];
+        });
+        for (int i = tid; i < kMaxPasses << Sh::kBinsLog2; i += NT) (&sh.hist[0][0])[i] = 0;
+        if (tid == 0) sh.n_collected = 0;
+    }
+    const bool ids_held = DISPATCH && T * K <= Sh::kIds;
+    if (ids_held) {
+        // (four to a word, whatever the number of candidates; the last word may be partly filled)
+        const int n = T * K, quads = n / 4;
+        typedef int32_t i32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+        constexpr int kBatch = 6;
+        for (int i0 = tid; i0 < quads; i0 += kBatch * NT) {
+            i32x4_any v[kBatch];
 #pragma unroll
-        for (int bi = 0; bi < kMaxBatches; ++bi) {
-            const int t = (wave + bi * NW) * kWave + lane;
+            for (int u = 0; u < kBatch; ++u)
+                v[u] = *reinterpret_cast<const i32x4_any*>(topk_ids + 4 * static_cast<size_t>(min(i0 + u * NT, quads - 1)));
 #pragma unroll
-            for (int j = 0; j < kIdsK; ++j)
-                held[bi][j] = (t < T && j < K) ? topk_ids[static_cast<size_t>(t) * K + j] : 0;
+            for (int u = 0; u < kBatch; ++u)
+                if (i0 + u * NT < quads)
+                    sh.ids[i0 + u * NT] = static_cast<uint32_t>((v[u][0] & 255) | ((v[u][1] & 255) << 8) |
+                                                                ((v[u][2] & 255) << 16) | (v[u][3] << 24));
+        }
+        if (tid < n % 4) reinterpret_cast<uint8_t*>(sh.ids)[4 * quads + tid] = static_cast<uint8_t>(topk_ids[4 * quads + tid]);
+    }
+    if (search) {
+        uint32_t key[kFastMaxKeys];
+        for_entries<NT>(n_pool, [&](auto q_const) {
+            constexpr int q = decltype(q_const)::value;
+            key[q] = q * NT + tid < n_pool ? ordered_key(score[q]) : 0u;
+        });
+        const Threshold last = find_threshold<NT>(sh, key, n_pool, static_cast<uint32_t>(want));
+        uint64_t word = 0;   // lane q: the ballot over the wave's q-th entries
+        for_entries<NT>(n_pool, [&](auto q_const) {
+            constexpr int q = decltype(q_const)::value;
+            const uint64_t kept = __ballot(key[q] > last.key || (key[q] == last.key && static_cast<uint32_t>(q * NT + tid) <= last.index));
+            word = lane == q ? kept : word;
+        });
+        if (lane * NT < n_pool) sh.bits[lane * NW + wave] = word;
+    }
+    __syncthreads();
+    // keep count of token t: its bits of the map
+    auto count_of = [&](int t) -> int {
+        if (!SELECT) return max(0, min(K, keep_count[t]));
+        if (!search) return want <= 0 ? Kb : K;
+        const uint32_t* w = reinterpret_cast<const uint32_t*>(sh.bits) + (static_cast<uint32_t>(t * P) >> 5);
+        const uint64_t two = w[0] | (static_cast<uint64_t>(w[1]) << 32);
+        return Kb + __popc(static_cast<uint32_t>(two >> ((t * P) & 31)) & ((1u << P) - 1u));
+    };
+    if (!DISPATCH) {
+        for (int t = tid; t < T; t += NT) keep_count[t] = count_of(t);
+        return;
+    }
+    // candidate ids of token t, one byte each: NJ (8 or 16) of them, those past K meaningless
+    auto load_ids = [&](int t, auto& ids) {
+        constexpr int NJ = 4 * (sizeof(ids) / sizeof(ids[0]));
+        if (ids_held) {
+            const uint32_t at = static_cast<uint32_t>(t * K), *w = sh.ids + at / 4;
+            uint32_t x[NJ / 4 + 1];
+#pragma unroll
+            for (int i = 0; i <= NJ / 4; ++i) x[i] = w[i];
+#pragma unroll
+            for (int i = 0; i < NJ / 4; ++i) ids[i] = __builtin_amdgcn_alignbyte(x[i + 1], x[i], at % 4);
+        } else {
+            uint32_t x[NJ];
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) x[j] = static_cast<uint32_t>(topk_ids[static_cast<size_t>(t) * K + min(j, K - 1)]) & 255u;
+#pragma unroll
+            for (int i = 0; i < NJ / 4; ++i) ids[i] = x[4 * i] | (x[4 * i + 1] << 8) | (x[4 * i + 2] << 16) | (x[4 * i + 3] << 24);
         }
     };
-    if (NT == 256) load_held();
-
-    if (SELECT) {
-        const int P = K - Kb;
-        const int n_pool = T * P;
-        const int64_t want = B - static_cast<int64_t>(T) * Kb;
-        if (want <= 0 || want >= n_pool) {
-            const int c = want <= 0 ? Kb : K;
-            for (int t = tid; t < T; t += NT) sh.cnt[t] = c;
-        } else if (n_pool <= kDirectPool) {
-            // Small pool (decode-shaped calls): every pool entry counts the entries that
-            // precede it in the order (score descending, token ascending, rank
-            // ascending) and is kept iff fewer than B' do.
-            // The order as one unsigned number per entry: key, then the complement of the
-            // pool index (equal keys: the lower index is the larger number).  A wave keeps
-            // 64 entries of the pool at a time in a register pair and broadcasts them one
-            // by one through scalar registers, so the inner loop touches no memory.
-            static_assert(kDirectPool <= 256 && kDirectPool <= NT, "one entry per thread, 8-bit index");
-            for (int t = tid; t < T; t += NT) sh.cnt[t] = Kb;
-            for (int i = tid; i < kDirectPool; i += NT)
-                sh.hist[i] = i < n_pool
-                                 ? ordered_key(topk_s[static_cast<size_t>(i / P) * K + Kb + i % P])
-                                 : 0u;   // below every real key (no finite score maps to 0)
-            __syncthreads();
-            if (wave * kWave < n_pool) {   // uniform per wave
-                const uint64_t mine = (static_cast<uint64_t>(sh.hist[tid]) << 8) | (255u - tid);
-                int before = 0;
-                for (int c = 0; c * kWave < n_pool; ++c) {
-                    const int o = c * kWave + lane;
-                    const uint64_t theirs = (static_cast<uint64_t>(sh.hist[o]) << 8) | (255u - o);
-                    const int lo = static_cast<int>(static_cast<uint32_t>(theirs));
-                    const int hi = static_cast<int>(static_cast<uint32_t>(theirs >> 32));
-#pragma unroll
-                    for (int l = 0; l < kWave; ++l) {
-                        const uint64_t other =
-                            static_cast<uint32_t>(__builtin_amdgcn_readlane(lo, l)) |
-                            (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(hi, l))) << 32);
-                        before += other > mine ? 1 : 0;
-                    }
-                }
-                if (tid < n_pool && before < want) atomicAdd(&sh.cnt[tid / P], 1);   // integer adds: order-free
-            }
-        } else {
-            for (int t = tid; t < T; t += NT) sh.cnt[t] = Kb;
-            // ---- this thread's slice of the pool, in (token, rank) order
-            const int C = (n_pool + NT - 1) / NT;   // <= kFastMaxKeys
-            const int n0 = min(n_pool, tid * C), n_mine = min(n_pool, n0 + C) - n0;
-            const int t_first = n0 / P, j_first = n0 % P;
-            uint32_t key[kFastMaxKeys];
-            // A thread's slice is strided in memory (lane stride = C scores), so where the
-            // whole [T,K] score matrix fits the staging area it is copied to LDS with
-            // coalesced loads and the slices are read from there.
-            const bool staged = T * K <= kStageFloats;
-            if (staged) {
-                const int n_all = T * K;
-                if ((n_all & 3) == 0 && (reinterpret_cast<uintptr_t>(topk_s) & 15) == 0) {
-                    const float4* src = reinterpret_cast<const float4*>(topk_s);
-                    float4* dst = reinterpret_cast<float4*>(sh.stage);
-                    for (int i = tid; i < n_all / 4; i += NT) dst[i] = src[i];
-                } else {
-                    for (int i = tid; i < n_all; i += NT) sh.stage[i] = topk_s[i];
-                }
-                __syncthreads();
-            }
-            {
-                int t = t_first, j = j_first;
-#pragma unroll
-                for (int q = 0; q < kFastMaxKeys; ++q) {
-                    key[q] = 0;
-                    if (q < n_mine) {
-                        const size_t at = static_cast<size_t>(t) * K + Kb + j;
-                        key[q] = ordered_key(staged ? sh.stage[at] : topk_s[at]);
-                        if (++j == P) { j = 0; ++t; }
-                    }
-                }
-            }
-            if (staged) __syncthreads();   // the staging area is the dispatch arrays' from here on
-            // ---- range of the keys
-            uint32_t lo = 0xFFFFFFFFu, hi = 0u;
-#pragma unroll
-            for (int q = 0; q < kFastMaxKeys; ++q) {
-                if (q >= C) continue;
-                if (q < n_mine) {
-                    lo = min(lo, key[q]);
-                    hi = max(hi, key[q]);
-                }
-            }
-            lo = wave_min_u32(lo);
-            hi = wave_max_u32(hi);
-            if (lane == 0) {
-                sh.red_lo[wave] = lo;
-                sh.red_hi[wave] = hi;
-            }
-            if (tid == 0) {
-                sh.pick_bin = 0;
-                sh.pick_rank = 1;
-                sh.pick_count = 1;
-            }
-            __syncthreads();
-            lo = 0xFFFFFFFFu;
-            hi = 0u;
-            for (int w = 0; w < NW; ++w) {
-                lo = min(lo, sh.red_lo[w]);
-                hi = max(hi, sh.red_hi[w]);
-            }
-            // ---- narrowing passes (see select_phase)
-            uint32_t r = static_cast<uint32_t>(want);
-            uint32_t in_range = static_cast<uint32_t>(n_pool);
-            while (lo < hi) {
-                const uint32_t width_m1 = hi - lo;
-                const int bits = 32 - __builtin_clz(width_m1);
-                const int shift = bits > NBINS_LOG2 ? bits - NBINS_LOG2 : 0;
-                for (int b = tid; b < NBINS; b += NT) sh.hist[b] = 0;
-                __syncthreads();
-#pragma unroll
-                for (int q = 0; q < kFastMaxKeys; ++q) {
-                    if (q >= C) continue;
-                    if (q < n_mine && key[q] >= lo && key[q] <= hi)
-                        atomicAdd(&sh.hist[(key[q] - lo) >> shift], 1u);
-                }
-                __syncthreads();
-                const int b_first = NBINS - 1 - 2 * tid, b_second = b_first - 1;
-                const uint32_t c_first = sh.hist[b_first], c_second = sh.hist[b_second];
-                const uint32_t above = block_scan_excl<NW>(c_first + c_second, sh.wave_tot, nullptr);
-                if (above < r && r <= above + c_first) {
-                    sh.pick_bin = b_first;
-                    sh.pick_rank = r - above;
-                    sh.pick_count = c_first;
-                } else if (above + c_first < r && r <= above + c_first + c_second) {
-                    sh.pick_bin = b_second;
-                    sh.pick_rank = r - above - c_first;
-                    sh.pick_count = c_second;
-                }
-                __syncthreads();
-                const uint32_t pb = sh.pick_bin;
-                r = sh.pick_rank;
-                in_range = sh.pick_count;
-                const uint32_t new_lo = lo + (pb << shift);
-                const uint32_t span_m1 = (shift == 0) ? 0u : ((1u << shift) - 1u);
-                hi = (hi - new_lo < span_m1) ? hi : new_lo + span_m1;
-                lo = new_lo;
-                __syncthreads();
-            }
-            const uint32_t vstar = lo, n_equal = in_range, R = r;
-            // ---- equal keys that precede this thread's slice (only if a tie is split)
-            uint32_t before = 0;
-            if (R != n_equal) {   // uniform
-                uint32_t eq = 0;
-#pragma unroll
-                for (int q = 0; q < kFastMaxKeys; ++q) {
-                    if (q >= C) continue;
-                    if (q < n_mine) eq += key[q] == vstar ? 1u : 0u;
-                }
-                before = block_scan_excl<NW>(eq, sh.wave_tot, nullptr);
-            }
-            // ---- kept entries per token (a token's slice may straddle two threads:
-            // integer adds in LDS, order-independent)
-            {
-                int t = t_first, j = j_first, run = 0;
-#pragma unroll
-                for (int q = 0; q < kFastMaxKeys; ++q) {
-                    if (q >= C) continue;
-                    if (q < n_mine) {
-                        bool keep = key[q] > vstar;
-                        if (key[q] == vstar) {
-                            keep = R == n_equal || before < R;
-                            ++before;
-                        }
-                        run += keep ? 1 : 0;
-                        if (++j == P || q == n_mine - 1) {
-                            if (run) atomicAdd(&sh.cnt[t], run);
-                            run = 0;
-                            j = 0;
-                            ++t;
-                        }
-                    }
-                }
-            }
-        }
-        __syncthreads();
-        if (writer)
-            for (int t = tid; t < T; t += NT) keep_count[t] = sh.cnt[t];
-    } else {
-        for (int t = tid; t < T; t += NT) sh.cnt[t] = keep_count[t];
-        __syncthreads();
-    }
-    if (!DISPATCH) return;
-
     const int n_batch = (T + kWave - 1) / kWave;
-    if (NT != 256) load_held();
     // ---- A: ballot words by bit-matrix transpose (lane e ends up with expert e's word)
+    auto make_words = [&](auto nj_const) {
+        constexpr int NJ = decltype(nj_const)::value;
+        for (int b = wave; b < n_batch; b += NW) {
+            const int t = b * kWave + lane, tt = min(t, T - 1);
+            const int kt = t < T ? count_of(tt) : 0;
+            uint32_t ids[NJ / 4];
+            load_ids(tt, ids);
+            uint64_t mine = 0;
 #pragma unroll
-    for (int bi = 0; bi < kMaxBatches; ++bi) {
-        const int b = wave + bi * NW;
-        if (b >= n_batch) break;
-        const int t = b * kWave + lane;
-        uint64_t mine = 0;
-        if (t < T) {
-            const int kt = min(K, sh.cnt[t]);
-            if (ids_held) {
-#pragma unroll
-                for (int j = 0; j < kIdsK; ++j)
-                    if (j < kt) mine |= 1ull << (held[bi][j] & (kWave - 1));
-            } else {
-                int ids[kMaxK];   // all loads first, so that they are in flight together
-#pragma unroll
-                for (int j = 0; j < kMaxK; ++j)
-                    ids[j] = j < K ? topk_ids[static_cast<size_t>(t) * K + j] : 0;
-#pragma unroll
-                for (int j = 0; j < kMaxK; ++j)
-                    if (j < kt) mine |= 1ull << (ids[j] & (kWave - 1));
+            for (int j = 0; j < NJ; ++j)
+                mine |= static_cast<uint64_t>(j < kt ? 1u : 0u) << ((ids[j / 4] >> (8 * (j % 4))) & (kWave - 1));
+            if (t < T) {
+                sh.cnt[t] = static_cast<uint8_t>(kt);
+                if (SELECT && writer) keep_count[t] = kt;
             }
+            sh.words[b * kWave + lane] = wave_transpose64(mine);
         }
-        sh.words[b * kWave + lane] = wave_transpose64(mine);
-    }
+    };
+    if (K <= 8)
+        make_words(std::integral_constant<int, 8>{});
+    else
+        make_words(std::integral_constant<int, 16>{});
     __syncthreads();
     // ---- B: per expert, exclusive prefix over batches; offsets over experts
     {
-        const int e = tid % kWave, seg = tid / kWave;
+        const int e = lane, seg = wave;
         const int per_seg = (n_batch + NW - 1) / NW;
         const int b0 = min(n_batch, seg * per_seg), b1 = min(n_batch, b0 + per_seg);
         int local = 0;
@@ -653,7 +684,7 @@ __global__ __launch_bounds__(NT) void plan_fast_kernel(
         }
         int run = base;
         for (int b = b0; b < b1; ++b) {
-            sh.prefix[b * kWave + e] = run;
+            sh.prefix[b * kWave + e] = static_cast<uint16_t>(run);
             run += __popcll(sh.words[b * kWave + e]);
         }
         if (seg == 0) {
@@ -668,58 +699,50 @@ __global__ __launch_bounds__(NT) void plan_fast_kernel(
     // tokens the last wave has no batch of its own)
     if (writer && tile_info != nullptr && wave == NW - 1)
         write_tile_map(sh.expert_off, E, bm, tile_info, static_cast<int>(B));
-    // ---- C: place every pair (token t = lane of batch b, candidate ids in `ids`)
-    auto place = [&](int b, int t, const int (&ids)[kMaxK]) {
-        const int kt = min(K, sh.cnt[t]);
-        const uint64_t below = lanemask_lt();
-#pragma unroll
-        for (int j = 0; j < kMaxK; ++j) {
-            if (j >= K) continue;
-            int row = -1;
-            if (j < kt) {
-                const int e = ids[j] & (kWave - 1);
-                const int idx = b * kWave + e;
-                row = sh.expert_off[e] + sh.prefix[idx] + __popcll(sh.words[idx] & below);
-                if (row < B) {   // holds whenever sum_t keep_count[t] <= budget
-                    row_token[row] = t;
-                    row_rank[row] = j;
-                } else {
-                    row = -1;
-                }
-            }
-            inv_row[static_cast<size_t>(t) * K + j] = row;
-        }
-    };
-    if (n_groups == 1) {
-#pragma unroll
-        for (int bi = 0; bi < kMaxBatches; ++bi) {
-            const int b = wave + bi * NW;
-            if (b >= n_batch) break;
-            const int t = b * kWave + lane;
-            if (t >= T) continue;
-            int ids[kMaxK];
-#pragma unroll
-            for (int j = 0; j < kMaxK; ++j) {
-                if (ids_held)
-                    ids[j] = j < kIdsK ? held[bi][j < kIdsK ? j : 0] : 0;
-                else
-                    ids[j] = j < K ? topk_ids[static_cast<size_t>(t) * K + j] : 0;
-            }
-            place(b, t, ids);
-        }
-    } else {
-        // several workgroups: each has computed the same counts, words and prefixes and
-        // places the batches group, group + n_groups, ..., one per wave at a time
+    // ---- C: place every pair (token t = lane of batch b); several workgroups have computed the
+    // same counts, words and prefixes and share the batches out
+    auto place = [&](auto nj_const) {
+        constexpr int NJ = decltype(nj_const)::value;
         for (int b = group + n_groups * wave; b < n_batch; b += n_groups * NW) {
             const int t = b * kWave + lane;
             if (t >= T) continue;
-            int ids[kMaxK];
+            const int kt = sh.cnt[t];
+            const uint64_t below = lanemask_lt();
+            uint32_t ids[NJ / 4];
+            load_ids(t, ids);
+            int row[NJ];
 #pragma unroll
-            for (int j = 0; j < kMaxK; ++j)
-                ids[j] = j < K ? topk_ids[static_cast<size_t>(t) * K + j] : 0;
-            place(b, t, ids);
+            for (int j = 0; j < NJ; ++j) {   // all LDS reads first
+                const int e = (ids[j / 4] >> (8 * (j % 4))) & (kWave - 1), idx = b * kWave + e;
+                row[j] = sh.expert_off[e] + sh.prefix[idx] + __popcll(sh.words[idx] & below);
+            }
+            int32_t* inv = inv_row + static_cast<size_t>(t) * K;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                // (row < B holds whenever sum_t keep_count[t] <= budget)
+                row[j] = j < kt && row[j] < B ? row[j] : -1;
+                if (row[j] >= 0) {
+                    row_token[row[j]] = t;
+                    row_rank[row[j]] = j;
+                }
+            }
+            typedef int32_t i32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+#pragma unroll
+            for (int j = 0; j < NJ; j += 4) {
+                if (j + 4 <= K) {
+                    *reinterpret_cast<i32x4_any*>(inv + j) = i32x4_any{row[j], row[j + 1], row[j + 2], row[j + 3]};
+                } else {
+#pragma unroll
+                    for (int i = j; i < j + 3; ++i)
+                        if (i < K) inv[i] = row[i];
+                }
+            }
         }
-    }
+    };
+    if (K <= 8)
+        place(std::integral_constant<int, 8>{});
+    else
+        place(std::integral_constant<int, 16>{});
 }
 
 // ---------------------------------------------------------------------------
