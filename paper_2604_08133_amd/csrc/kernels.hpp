@@ -42,16 +42,21 @@ hipError_t launch_topk_from_scores(const float* scores, int T, int E, int K, int
 // candidate scores [T,K]
 hipError_t launch_selector_keys(const float* topk_s, int T, int K, int mode, float* keys,
                                 hipStream_t stream);
-// From kPlanSpreadTokens tokens on, selection and dispatch run as a sequence of launches
-// over many workgroups; the selection then needs plan_spread_bytes(T) bytes of device
-// scratch (`spread`, 256-byte aligned; null: one workgroup does the work, whatever T).
-// Every launch of the sequence costs 5-10 us whatever its size (a chain of dependent
-// memory round trips), five of them 42 us at 8192 tokens and 36 us at 4096, against 82 us
-// and 50 us for the single workgroup; at 2048 tokens both take 32 us.
-// `alone`: nothing else wants the compute units while the plan runs; below the spread
-// size the one launch then has several workgroups that repeat the selection and share
+// Many tokens: selection and dispatch as a sequence of launches over many workgroups; the
+// selection then needs plan_spread_bytes(T) bytes of device scratch (`spread`, 256-byte aligned;
+// null: one workgroup does the work, whatever T).  Every launch of the sequence costs 4-10 us
+// whatever its size (a chain of dependent memory round trips).
+//   selection alone: from kPlanSpreadTokens on.  4200 tokens, K = 6: one workgroup 18.4 us with
+//     Top-K, spread 22.4; 6000: 21.4, 24.5; 8192: 25.7, 26.1; but scores of 64 levels (half the
+//     pool on one histogram count) 69.5 against 32.8 at 6000.
+//   dispatch, alone or behind the selection: from kPlanSpreadDispatchTokens on, or where the
+//     one-launch kernel cannot hold the pool.  Dispatch at 4200 tokens 10.6 us in one launch, 14.2
+//     spread; 6000: 13.1, 14.4; 8192: 16.1, 15.2; layer of 64 experts of 2048 x 1024, K = 8: 4096
+//     tokens 310 us, 330; 6000: 389, 401; K = 6: 7000 tokens 381, 377, 8192: 410, 404.
+// `alone`: nothing else wants the compute units while the plan runs; the one launch then
+// has several workgroups that repeat the selection and share
 // out the placement (beside other work extra workgroups would only queue behind it).
-constexpr int kPlanSpreadTokens = 4096;
+constexpr int kPlanSpreadTokens = 4096, kPlanSpreadDispatchTokens = 6144;
 size_t plan_spread_bytes(int T);
 hipError_t launch_select(const float* topk_s, int T, int K, int Kb, int64_t B,
                          int32_t* keep_count, void* spread, hipStream_t stream);

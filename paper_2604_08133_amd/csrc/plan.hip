@@ -337,9 +337,11 @@ __device__ void tilemap_phase(PlanShared& sh, int E, int bm, int32_t* __restrict
 // transposed with a 6-stage butterfly of lane exchanges instead of 64 ballots.
 //
 // Bound by latency: a chain of loads, barriers and LDS round trips on one compute unit.  Phases
-// of 333 tokens with 8 candidates, us: loads 4.4, range 1.0, passes 6.0, counts 2.6, words and
-// prefixes 1.7, rows 2.0 with thread-contiguous slices of the pool staged through LDS, three
-// passes that ended at a single key and block-wide scans.
+// of 333 tokens with 8 candidates, us: loads 2.0, range 0.6, passes 0.8, last bin and counts 1.5,
+// words and prefixes 1.6, rows 1.2, together 7.6; with thread-contiguous slices of the pool
+// staged through LDS, three passes that ended at a single key and block-wide scans 4.4, 1.0,
+// 6.0, 2.6, 1.7, 2.0.  Whole kernel, then and now: 64 tokens x 6 14.7, 6.2; 777 x 4 21.0, 9.9;
+// 2048 x 4 42, 19; 4096 x 6 60, 33.
 constexpr int kFastMaxT = 8192;
 constexpr int kFastMaxKeys = 48;
 constexpr int kCollect = 64;       // keys of a bin that a wave ranks directly
@@ -349,15 +351,17 @@ constexpr int kMaxPasses = 4;      // 32 key bits, 9 or 10 a pass
 template <int NT>
 struct FastShared {
     static constexpr int kWaves = NT / kWave;
-    static constexpr int kTokens = NT == 1024 ? kFastMaxT : 1024;
+    static constexpr int kTokens = NT == 1024 ? kFastMaxT : 4 * NT;
     static constexpr int kIds = NT == 1024 ? 49152 : kTokens * kMaxK;
     static constexpr int kBinsLog2 = NT == 1024 ? 10 : 9;
     static constexpr int kWords = kFastMaxKeys * kWaves;   // of a bit map over the pool
     union {
         struct {   // selection
-            uint32_t hist[kMaxPasses][1 << kBinsLog2];
+            // (behind the bins and the collected keys a unit per lane, for the entries that are
+            // not in the range: no branch)
+            uint32_t hist[kMaxPasses][(1 << kBinsLog2) + kWave];
             uint64_t equal[kWords];
-            uint64_t collected[kCollect];
+            alignas(16) uint64_t collected[kCollect + kWave];
         };
         uint64_t words[kTokens];       // dispatch: [batch][expert]
     };
@@ -397,14 +401,19 @@ __device__ __forceinline__ uint64_t wave_transpose64(uint64_t x) {
     return x;
 }
 
-// f(q) for every q with entries of the pool (q a compile-time constant: the keys stay in registers)
+// f(q) for every q with entries of the pool (q a compile-time constant: the keys stay in
+// registers), four at a time: a branch costs a wave that is alone on its SIMD as much as several
+// entries (the last four may lie past the end: key 0, not in any range).
 template <int NT, typename F, int... Q>
 __device__ __forceinline__ void for_entries(int n_pool, F f, std::integer_sequence<int, Q...>) {
-    (void)((Q * NT < n_pool && (f(std::integral_constant<int, Q>{}), true)) && ...);
+    (void)((4 * Q * NT < n_pool &&
+            (f(std::integral_constant<int, 4 * Q>{}), f(std::integral_constant<int, 4 * Q + 1>{}),
+             f(std::integral_constant<int, 4 * Q + 2>{}), f(std::integral_constant<int, 4 * Q + 3>{}), true)) && ...);
 }
 template <int NT, typename F>
 __device__ __forceinline__ void for_entries(int n_pool, F f) {
-    for_entries<NT>(n_pool, f, std::make_integer_sequence<int, kFastMaxKeys>{});
+    static_assert(kFastMaxKeys % 4 == 0, "whole groups");
+    for_entries<NT>(n_pool, f, std::make_integer_sequence<int, kFastMaxKeys / 4>{});
 }
 
 // The last pool entry kept: entries are kept iff their key is larger than `key`, or equal and
@@ -469,7 +478,8 @@ __device__ __forceinline__ Threshold find_threshold(FastShared<NT>& sh, const ui
         uint32_t* hist = sh.hist[pass];   // (bins from the top of the range)
         for_entries<NT>(n_pool, [&](auto q_const) {
             constexpr int q = decltype(q_const)::value;
-            if (key[q] >= lo && key[q] <= hi) atomicAdd(&hist[(hi - key[q]) >> shift], 1u);
+            const uint32_t bin = key[q] >= lo && key[q] <= hi ? (hi - key[q]) >> shift : (1u << Sh::kBinsLog2) + lane;
+            atomicAdd(&hist[bin], 1u);
         });
         __syncthreads();
         uint32_t c[kBinsLane], above;
@@ -499,22 +509,25 @@ __device__ __forceinline__ Threshold find_threshold(FastShared<NT>& sh, const ui
         if (__ballot(n != 0u)) {
             for_entries<NT>(n_pool, [&](auto q_const) {
                 constexpr int q = decltype(q_const)::value;
-                if (key[q] >= lo && key[q] <= hi) {
-                    if (slot < kCollect)
-                        sh.collected[slot] = (static_cast<uint64_t>(key[q]) << 32) | ~static_cast<uint32_t>(q * NT + tid);
-                    ++slot;
-                }
+                const bool in = key[q] >= lo && key[q] <= hi;
+                sh.collected[in && slot < kCollect ? slot : kCollect + lane] =
+                    (static_cast<uint64_t>(key[q]) << 32) | ~static_cast<uint32_t>(q * NT + tid);
+                slot += in ? 1u : 0u;
             });
         }
         __syncthreads();
-        const uint64_t mine = lane < static_cast<int>(count) ? sh.collected[lane] : 0ull;
+        const uint64_t mine = sh.collected[lane];   // (cleared where nothing was written)
         const int mine_lo = static_cast<int>(static_cast<uint32_t>(mine)), mine_hi = static_cast<int>(mine >> 32);
         uint32_t before = 0;
-        for (int l = 0; l < static_cast<int>(count); ++l) {
-            const uint64_t other =
-                static_cast<uint32_t>(__builtin_amdgcn_readlane(mine_lo, l)) |
-                (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(mine_hi, l))) << 32);
-            before += other > mine ? 1u : 0u;
+        for (int l = 0; l < static_cast<int>(count); l += 8) {
+            ulonglong2 other[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) other[i] = *reinterpret_cast<const ulonglong2*>(&sh.collected[l + 2 * i]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                before += other[i].x > mine ? 1u : 0u;
+                before += other[i].y > mine ? 1u : 0u;
+            }
         }
         const int last = __builtin_ctzll(__ballot(before == r - 1) | (1ull << (kWave - 1)));
         return {static_cast<uint32_t>(__builtin_amdgcn_readlane(mine_hi, last)),
@@ -551,7 +564,7 @@ __global__ __launch_bounds__(NT) void plan_fast_kernel(
     using Sh = FastShared<NT>;
     __shared__ Sh sh;
     constexpr int NW = NT / kWave;            // waves
-    static_assert(NT == 1024 || NT == 256, "two block sizes");
+    static_assert(NT == 1024 || NT == 512 || NT == 256, "block sizes");
     const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     // Launched as several workgroups (only where nothing else wants the compute units),
     // every workgroup runs the selection and the counting phases redundantly, on its own
@@ -574,7 +587,9 @@ __global__ __launch_bounds__(NT) void plan_fast_kernel(
             const int t = P == 1 ? i : static_cast<int>(__umulhi(static_cast<uint32_t>(i), inv_p));
             score[q] = topk_s[static_cast<size_t>(t) * K + Kb + (i - t * P)];
         });
-        for (int i = tid; i < kMaxPasses << Sh::kBinsLog2; i += NT) (&sh.hist[0][0])[i] = 0;
+        if (n_pool > kCollect)
+            for (int i = tid; i < static_cast<int>(sizeof(sh.hist) / 4); i += NT) (&sh.hist[0][0])[i] = 0;
+        if (tid < kCollect) sh.collected[tid] = 0;
         if (tid == 0) sh.n_collected = 0;
     }
     const bool ids_held = DISPATCH && T * K <= Sh::kIds;
@@ -1016,14 +1031,15 @@ static void launch_spread_select(const float* keys, const int32_t* topk_ids, int
                        0, stream, keys, topk_ids, T, K, Kb, B, hist, G, state, keep_count, words);
 }
 
-// 0: large sizes (generic kernels), 256 / 1024: block size of the fast kernel.
-// Small problems run on 4 waves (one per SIMD): the kernel is a chain of short
-// dependent phases, and fewer waves means each instruction issues sooner.
+// 0: large sizes (generic kernels), else the block size of the fast kernel.
+// A thread costs the barriers and the redundant searches little and the phases that walk batches
+// of 64 tokens a wave much: 333 tokens x 8 candidates 8.6 us with 256 threads, 7.3 with 512, 8.1
+// with 1024; 500 x 4 8.6, 7.2, 8.5; 777 x 4 12.2 with 512, 9.8 with 1024; 64 x 6 5.7 with 256.
 inline int fast_path_threads(int T, int K, int Kb) {
     const int64_t n_pool = static_cast<int64_t>(T) * (K - Kb);
-    if (T > kFastMaxT) return 0;
-    if (T <= 1024 && (n_pool + 255) / 256 <= kFastMaxKeys) return 256;
-    return (n_pool + kPlanThreads - 1) / kPlanThreads <= kFastMaxKeys ? kPlanThreads : 0;
+    for (int nt : {256, 512, 1024})
+        if (T <= (nt == 1024 ? kFastMaxT : nt) && n_pool <= static_cast<int64_t>(nt) * kFastMaxKeys) return nt;
+    return 0;
 }
 
 // Workgroups of the fast kernel's launch: one beside other work (more would queue behind
@@ -1034,21 +1050,22 @@ inline int fast_path_groups(int T, bool alone) {
     return std::max(1, std::min(16, n_batch / 2));
 }
 
+template <bool SELECT, bool DISPATCH, typename... Args>
+void enqueue_fast(int nt, int groups, hipStream_t stream, Args... args) {
+    const dim3 grid(groups), block(nt);
+    if (nt == 256)
+        hipLaunchKernelGGL((plan_fast_kernel<SELECT, DISPATCH, 256>), grid, block, 0, stream, args...);
+    else if (nt == 512)
+        hipLaunchKernelGGL((plan_fast_kernel<SELECT, DISPATCH, 512>), grid, block, 0, stream, args...);
+    else
+        hipLaunchKernelGGL((plan_fast_kernel<SELECT, DISPATCH, 1024>), grid, block, 0, stream, args...);
+}
+
 __global__ __launch_bounds__(kPlanThreads) void select_kernel(const float* topk_s, int T, int K,
                                                               int Kb, int64_t B,
                                                               int32_t* keep_count) {
     __shared__ PlanShared sh;
     select_phase(sh, topk_s, T, K, Kb, B, keep_count);
-}
-
-__global__ __launch_bounds__(kPlanThreads) void dispatch_kernel(
-    const int32_t* topk_ids, const int32_t* keep_count, int T, int K, int E, int64_t B,
-    int32_t* expert_offsets, int32_t* row_token, int32_t* row_rank, int32_t* inv_row,
-    uint64_t* words, int32_t* prefix, int bm, int32_t* tile_info) {
-    __shared__ PlanShared sh;
-    dispatch_phase(sh, topk_ids, keep_count, T, K, E, B, expert_offsets, row_token, row_rank,
-                   inv_row, words, prefix);
-    if (tile_info != nullptr) tilemap_phase(sh, E, bm, tile_info, static_cast<int>(B));
 }
 
 __global__ __launch_bounds__(kPlanThreads) void plan_kernel(
@@ -1095,19 +1112,14 @@ hipError_t launch_selector_keys(const float* topk_s, int T, int K, int mode, flo
 
 hipError_t launch_select(const float* topk_s, int T, int K, int Kb, int64_t B,
                          int32_t* keep_count, void* spread, hipStream_t stream) {
-    if (spread != nullptr && T >= kPlanSpreadTokens) {
+    const int nt = fast_path_threads(T, K, Kb);
+    if ((nt == 0 || T >= kPlanSpreadTokens) && spread != nullptr && plan_spread_bytes(T) > 0) {
         launch_spread_select(topk_s, nullptr, T, K, Kb, B, spread, keep_count, nullptr, stream);
         return hipGetLastError();
     }
-    const int nt = fast_path_threads(T, K, Kb);
-    if (nt == 256)
-        hipLaunchKernelGGL((plan_fast_kernel<true, false, 256>), dim3(1), dim3(256), 0, stream,
-                           topk_s, nullptr, T, K, Kb, B, 0, keep_count, nullptr, nullptr, nullptr,
-                           nullptr, 0, nullptr);
-    else if (nt == 1024)
-        hipLaunchKernelGGL((plan_fast_kernel<true, false, 1024>), dim3(1), dim3(1024), 0, stream,
-                           topk_s, nullptr, T, K, Kb, B, 0, keep_count, nullptr, nullptr, nullptr,
-                           nullptr, 0, nullptr);
+    int32_t* const none = nullptr;
+    if (nt != 0)
+        enqueue_fast<true, false>(nt, 1, stream, topk_s, none, T, K, Kb, B, 0, keep_count, none, none, none, none, 0, none);
     else
         hipLaunchKernelGGL(select_kernel, dim3(1), dim3(kPlanThreads), 0, stream, topk_s, T, K, Kb,
                            B, keep_count);
@@ -1118,7 +1130,8 @@ hipError_t launch_dispatch(const int32_t* topk_ids, const int32_t* keep_count, i
                            int E, int64_t B, int32_t* expert_offsets, int32_t* row_token,
                            int32_t* row_rank, int32_t* inv_row, uint64_t* words, int32_t* prefix,
                            int bm, int32_t* tile_info, bool alone, hipStream_t stream) {
-    if (T >= kPlanSpreadTokens) {
+    const int nt = fast_path_threads(T, K, K);
+    if (nt == 0 || T >= kPlanSpreadDispatchTokens) {
         const dim3 grid((T + kSpreadThreads - 1) / kSpreadThreads), block(kSpreadThreads);
         hipLaunchKernelGGL(spread_keep_kernel<false>, grid, block, 0, stream, nullptr, topk_ids, T, K,
                            0, B, nullptr, 0, nullptr, const_cast<int32_t*>(keep_count), words);
@@ -1126,20 +1139,9 @@ hipError_t launch_dispatch(const int32_t* topk_ids, const int32_t* keep_count, i
                            B, words, expert_offsets, row_token, row_rank, inv_row, bm, tile_info);
         return hipGetLastError();
     }
-    const int nt = fast_path_threads(T, K, K);
-    const dim3 groups(fast_path_groups(T, alone));
-    if (nt == 256)
-        hipLaunchKernelGGL((plan_fast_kernel<false, true, 256>), groups, dim3(256), 0, stream,
-                           nullptr, topk_ids, T, K, 0, B, E, const_cast<int32_t*>(keep_count),
-                           expert_offsets, row_token, row_rank, inv_row, bm, tile_info);
-    else if (nt == 1024)
-        hipLaunchKernelGGL((plan_fast_kernel<false, true, 1024>), groups, dim3(1024), 0, stream,
-                           nullptr, topk_ids, T, K, 0, B, E, const_cast<int32_t*>(keep_count),
-                           expert_offsets, row_token, row_rank, inv_row, bm, tile_info);
-    else
-        hipLaunchKernelGGL(dispatch_kernel, dim3(1), dim3(kPlanThreads), 0, stream, topk_ids,
-                           keep_count, T, K, E, B, expert_offsets, row_token, row_rank, inv_row,
-                           words, prefix, bm, tile_info);
+    enqueue_fast<false, true>(nt, fast_path_groups(T, alone), stream, static_cast<const float*>(nullptr), topk_ids, T, K,
+                              0, B, E, const_cast<int32_t*>(keep_count), expert_offsets, row_token, row_rank, inv_row,
+                              bm, tile_info);
     return hipGetLastError();
 }
 
@@ -1148,23 +1150,17 @@ hipError_t launch_plan(const float* topk_s, const int32_t* topk_ids, int T, int 
                        int32_t* row_token, int32_t* row_rank, int32_t* inv_row, uint64_t* words,
                        int32_t* prefix, int bm, int32_t* tile_info, void* spread, bool alone,
                        hipStream_t stream) {
-    if (spread != nullptr && T >= kPlanSpreadTokens) {
+    const int nt = fast_path_threads(T, K, Kb);
+    if ((nt == 0 || T >= kPlanSpreadDispatchTokens) && spread != nullptr && plan_spread_bytes(T) > 0) {
         launch_spread_select(topk_s, topk_ids, T, K, Kb, B, spread, keep_count, words, stream);
         const dim3 grid((T + kSpreadThreads - 1) / kSpreadThreads), block(kSpreadThreads);
         hipLaunchKernelGGL(spread_place_kernel, grid, block, 0, stream, topk_ids, keep_count, T, K, E,
                            B, words, expert_offsets, row_token, row_rank, inv_row, bm, tile_info);
         return hipGetLastError();
     }
-    const int nt = fast_path_threads(T, K, Kb);
-    const dim3 groups(fast_path_groups(T, alone));
-    if (nt == 256)
-        hipLaunchKernelGGL((plan_fast_kernel<true, true, 256>), groups, dim3(256), 0, stream,
-                           topk_s, topk_ids, T, K, Kb, B, E, keep_count, expert_offsets, row_token,
-                           row_rank, inv_row, bm, tile_info);
-    else if (nt == 1024)
-        hipLaunchKernelGGL((plan_fast_kernel<true, true, 1024>), groups, dim3(1024), 0, stream,
-                           topk_s, topk_ids, T, K, Kb, B, E, keep_count, expert_offsets, row_token,
-                           row_rank, inv_row, bm, tile_info);
+    if (nt != 0)
+        enqueue_fast<true, true>(nt, fast_path_groups(T, alone), stream, topk_s, topk_ids, T, K, Kb, B, E, keep_count,
+                                 expert_offsets, row_token, row_rank, inv_row, bm, tile_info);
     else
         hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kPlanThreads), 0, stream, topk_s, topk_ids,
                            T, K, Kb, B, E, keep_count, expert_offsets, row_token, row_rank,
