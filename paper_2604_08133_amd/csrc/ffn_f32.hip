@@ -12,16 +12,17 @@
 // 16-k steps in turn and meet in LDS at the end, which gives small workgroups (an
 // expert's rows are few, so a launch is some hundred of them for 256 compute units) that
 // still load 10 KB per wave and step.  Operands go straight from global memory to
-// registers in 16-byte loads, one step ahead of the MFMAs: which k a lane's slot means
+// registers in 16-byte loads, three steps ahead of the MFMAs (a ring): which k a lane's slot means
 // and which column is free to choose, so a lane takes 4 consecutive k of its row of A
 // (slot i of step k0: k0 + 4 (lane/16) + i) and 4 consecutive columns of those 4 rows of B
 // (column block j: n0 + 4 (lane%16) + j).  A layer of 500 tokens (d 1000, 16 experts of 700,
-// 1000 pairs, shared expert of 1400; 8.4 GFLOP) takes 181 us, 100 and 54 of them in the two
-// halves; 909 with a 32 x 64 tile on the vector ALUs and scalar loads through LDS (relative
-// error against 64 bits 5.4e-7, then 1.07e-6).  Bound, by counters, by the matrix pipe inside a
-// workgroup (0.77 of the waves' cycles an instruction waits for its unit, 0.13 for loads) and
-// by the rounds of workgroups around it: 864 and 992 of them, two to a unit, keep the units
-// busy 0.68 of a launch and the pipes 0.40 and 0.35.
+// 1000 pairs, shared expert of 1400; 8.4 GFLOP) takes 140 us, 81 and 44 of them in the two
+// halves (one step ahead, with the odd depth's last step masked behind its loads: 173, 100 and
+// 54; a ring of 4: 81 and 52; 909 with a 32 x 64 tile on the vector ALUs and scalar loads through
+// LDS; relative error against 64 bits 5.4e-7 now and then).  Bound by the matrix pipe where two workgroups share a unit (a loop 30 us for two, 16
+// alone, 13.4 at the pipe's rate) and by what is left over: of some 800 workgroups 41 units get four
+// and end at 87 us, the others three, the third one alone, and end at 67.  More of them at a time
+// (32 KB of LDS, 2 to 4 to a unit: 149, 155 and 148 us) or smaller ones (32 columns: 159) are slower.
 #include <algorithm>
 
 #include "common.hpp"
@@ -33,7 +34,7 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 // rows of odd widths are 4-byte aligned only, which a 16-byte global access accepts
 typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
 
-constexpr int kF32BM = kTileRowsSmall, kF32BN = 64, kF32Step = 16, kF32Waves = 4;
+constexpr int kF32BM = kTileRowsSmall, kF32BN = 64, kF32Step = 16, kF32Waves = 4, kF32Ring = 3;
 constexpr int kF32Xcds = 8;
 
 __device__ __forceinline__ f32x4 load4u(const float* p) {
@@ -82,17 +83,19 @@ __device__ __forceinline__ void f32_tile(const F32Group& g, int e, int row0, int
         for (int mt = 0; mt < NM; ++mt)
 #pragma unroll
             for (int i = 0; i < 4; ++i) f.b[mt][i] = load4u(br[mt] + static_cast<size_t>(ks + i) * N);
-        if ((step + 1) * kF32Step > Kd) {   // the last step of an odd depth (uniform)
+    };
+    // the last step of an odd depth: zeros for the k that another lane has as well
+    auto trim = [&](Frag& f, int step) {
+        const int k = step * kF32Step + 4 * kg, ks = min(k, Kd - 4);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const bool own = ks + i >= k;
+        for (int i = 0; i < 4; ++i) {
+            const bool own = ks + i >= k;
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb) f.a[mb][i] = own ? f.a[mb][i] : 0.f;
+            for (int mb = 0; mb < MB; ++mb) f.a[mb][i] = own ? f.a[mb][i] : 0.f;
 #pragma unroll
-                for (int mt = 0; mt < NM; ++mt)
+            for (int mt = 0; mt < NM; ++mt)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) f.b[mt][i][j] = own ? f.b[mt][i][j] : 0.f;
-            }
+                for (int j = 0; j < 4; ++j) f.b[mt][i][j] = own ? f.b[mt][i][j] : 0.f;
         }
     };
     auto multiply = [&](const Frag& f) {
@@ -107,17 +110,28 @@ __device__ __forceinline__ void f32_tile(const F32Group& g, int e, int row0, int
                         acc[mt][mb][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.a[mb][i], f.b[mt][i][j],
                                                                              acc[mt][mb][j], 0, 0, 0);
     };
+    // kF32Ring steps in flight: an entry is loaded again as soon as its products are issued
+    // (past the end: the last step's again, not used)
     const int steps = (Kd + kF32Step - 1) / kF32Step;
-    Frag f0, f1;
+    Frag ring[kF32Ring];
+#pragma unroll
+    for (int r = 0; r < kF32Ring; ++r) load(ring[r], min(wave + r * kF32Waves, steps - 1));
+    const int full = Kd / kF32Step;   // whole steps
     int s = wave;
-    if (s < steps) load(f0, s);
-    for (; s < steps; s += 2 * kF32Waves) {
-        const bool more = s + kF32Waves < steps;
-        if (more) load(f1, s + kF32Waves);
-        multiply(f0);
-        if (!more) break;
-        if (s + 2 * kF32Waves < steps) load(f0, s + 2 * kF32Waves);
-        multiply(f1);
+    for (; s + (kF32Ring - 1) * kF32Waves < full; s += kF32Ring * kF32Waves) {
+#pragma unroll
+        for (int r = 0; r < kF32Ring; ++r) {
+            multiply(ring[r]);
+            load(ring[r], min(s + (r + kF32Ring) * kF32Waves, steps - 1));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < kF32Ring; ++r) {
+        const int step = s + r * kF32Waves;
+        if (step >= steps) break;
+        if (step >= full) trim(ring[r], step);
+        multiply(ring[r]);
     }
 
     // the waves' sums meet in LDS; accumulator register r of lane l holds row 4 (l/16) + r,
