@@ -476,6 +476,8 @@ allocmoe_status forward_impl(const allocmoe_layer_desc* desc, const void* X,
     const bool routed_tiled = choice.routed_tiled, shared_tiled = choice.shared_tiled;
     const int bm = routed_tiled ? kTileRowsLarge : kTileRowsSmall;
     const int64_t max_tiles = max_tiles_for(desc, bm);
+    // half of the tiles that rows beyond the experts' first ones could at most need
+    const int64_t likely_tiles = (std::min<int64_t>(E, B) + max_tiles) / 2;
     // The shared expert depends on nothing but X.  On a stream of its own (large layers where a
     // group uses the tile kernel, smaller ones that are mostly shared expert) its two GEMMs run
     // beside selection and the routed experts' GEMMs, and the streams meet again before the
@@ -580,6 +582,7 @@ allocmoe_status forward_impl(const allocmoe_layer_desc* desc, const void* X,
             r1.A = X; r1.lda = d; r1.row_map = row_token; r1.Bp = pk + p.p13;
             r1.group_stride = 2 * dd * II; r1.Kd = d; r1.N = I; r1.tile_info = tile_info;
             r1.max_tiles = max_tiles; r1.C = H; r1.ldc = I;
+            r1.likely_tiles = r2.likely_tiles = likely_tiles;
             r2.A = H; r2.lda = I; r2.Bp = pk + p.p2; r2.group_stride = II * dd; r2.Kd = I;
             r2.N = d; r2.tile_info = tile_info; r2.max_tiles = max_tiles; r2.C = O; r2.ldc = d;
             if (fp8) {

@@ -157,33 +157,45 @@ __global__ __launch_bounds__(kStreamWaves* kWave) void ffn_bf16_stream_kernel(St
             }
         }
     };
-    // UNROLL steps in flight all the time: an entry is loaded again as soon as it is used.  The
-    // first weights do not wait for the row map.
+    // The first n steps: the weights do not wait for the row map.
+    auto start = [&](auto n_const) {
+        constexpr int n = decltype(n_const)::value;
 #pragma unroll
-    for (int u = 0; u < UNROLL; ++u) load_w(u, u);
-    __builtin_amdgcn_sched_barrier(0);
-    ap = reinterpret_cast<const bf16x8*>(A + static_cast<size_t>(src) * lda * 2) + wave * (kStepK / 8) + kg;
+        for (int u = 0; u < n; ++u) load_w(u, u);
+        __builtin_amdgcn_sched_barrier(0);
+        ap = reinterpret_cast<const bf16x8*>(A + static_cast<size_t>(src) * lda * 2) + wave * (kStepK / 8) + kg;
 #pragma unroll
-    for (int u = 0; u < UNROLL; ++u) load_a(u, u);
-    __builtin_amdgcn_sched_barrier(0);
-    int s = 0;
-    auto pass = [&]() {
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-            multiply(u);
-            load_w(u, s + UNROLL + u);
-            load_a(u, s + UNROLL + u);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        s += UNROLL;
+        for (int u = 0; u < n; ++u) load_a(u, u);
+        __builtin_amdgcn_sched_barrier(0);
     };
-    // (The first pass by itself: its loads stand in another order, and in a loop the compiler
-    // would wait for either.)
-    if (s + UNROLL < steps) pass();
-    while (s + UNROLL < steps) pass();
+    int s = 0;
+    auto finish = [&](auto n_const) {   // the last n steps or fewer, loaded already
 #pragma unroll
-    for (int u = 0; u < UNROLL; ++u)
-        if (s + u < steps) multiply(u);   // uniform
+        for (int u = 0; u < decltype(n_const)::value; ++u)
+            if (s + u < steps) multiply(u);   // uniform
+    };
+    if (steps <= UNROLL / 2) {   // (loads that nothing would use cost a short contraction 2-3 %)
+        start(std::integral_constant<int, UNROLL / 2>{});
+        finish(std::integral_constant<int, UNROLL / 2>{});
+    } else {
+        // UNROLL steps in flight all the time: an entry is loaded again as soon as it is used.
+        start(std::integral_constant<int, UNROLL>{});
+        auto pass = [&]() {
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) {
+                multiply(u);
+                load_w(u, s + UNROLL + u);
+                load_a(u, s + UNROLL + u);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            s += UNROLL;
+        };
+        // (The first pass by itself: its loads stand in another order, and in a loop the
+        // compiler would wait for either.)
+        if (s + UNROLL < steps) pass();
+        while (s + UNROLL < steps) pass();
+        finish(std::integral_constant<int, UNROLL>{});
+    }
 
 #pragma unroll
     for (int r = 0; r < 16; ++r)

@@ -28,8 +28,16 @@ constexpr int kXcds = 8;                // accelerator dies (one L2 each) of an 
 // Where the target is met (short tiles, less than one round) the group also takes the deeper
 // weight rings; above it they crowd the memory system (300 tokens, shared expert of 22528 on
 // 2048, 176 column tiles in the first half: layer 325 us, 332 with them).
-void lay_out_dense(StreamGroup& g, int col_tiles) {
-    constexpr int kTargetWorkgroups = 128;
+//
+// beside: workgroups that the routed experts are expected to have in the same launch.  Where
+// there is room for both in one round, the dense tiles are as high as that takes: 777 tokens, 32
+// experts of 1088 x 704, shared expert of 1408: 99 dense workgroups of 96 rows and 186 routed
+// ones ended at 32 us (a second round of 31), 55 of 160 rows at 26; second half 125 and 155, 31
+// us, now 65 of 64 rows, 21; layer 83.7 us, 74.3.
+void lay_out_dense(StreamGroup& g, int col_tiles, int64_t beside) {
+    constexpr int kUnits = 256, kMostWorkgroups = 128, kFewestWorkgroups = 32;
+    const int64_t room = kUnits - beside;
+    const int64_t kTargetWorkgroups = room >= kFewestWorkgroups ? std::min<int64_t>(kMostWorkgroups, room) : kMostWorkgroups;
     auto workgroups = [&](int h) { return static_cast<int64_t>((g.M_dense + h - 1) / h) * col_tiles; };
     int h = 32;
     while (h < kRows && workgroups(h) > kTargetWorkgroups) h += 32;
@@ -41,8 +49,9 @@ hipError_t launch_ffn_bf16_t256(bool swiglu, StreamGroup routed, StreamGroup sha
                                 hipStream_t stream) {
     const int cols = swiglu ? 128 : 256;
     auto col_tiles = [cols](const StreamGroup& g) { return (g.N + cols - 1) / cols; };
-    if (routed.A != nullptr && routed.tile_info == nullptr) lay_out_dense(routed, col_tiles(routed));
-    if (shared.A != nullptr) lay_out_dense(shared, col_tiles(shared));
+    if (routed.A != nullptr && routed.tile_info == nullptr) lay_out_dense(routed, col_tiles(routed), 0);
+    if (shared.A != nullptr)
+        lay_out_dense(shared, col_tiles(shared), routed.A != nullptr ? routed.likely_tiles * col_tiles(routed) : 0);
     // items per XCD; for the routed group an upper bound (the real tile count is
     // known on the device only)
     int64_t per_xcd = 0;

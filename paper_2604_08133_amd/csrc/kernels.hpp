@@ -102,6 +102,7 @@ struct StreamGroup {
     int Kd = 0, N = 0;
     const int32_t* tile_info = nullptr;
     int64_t max_tiles = 0;
+    int64_t likely_tiles = 0;  // tiles that a batch is likely to have (tile kernel)
     int M_dense = 0;
     void* C = nullptr;
     int ldc = 0;
