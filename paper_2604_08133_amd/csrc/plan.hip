@@ -953,6 +953,13 @@ __global__ __launch_bounds__(kSpreadThreads) void spread_place_kernel(
     const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
     const int n_batch = (T + kWave - 1) / kWave;
     const int b0 = blockIdx.x * kPlanWaves;
+    // (what does not depend on the counts comes first: the wave's own batch)
+    const int b = b0 + wave, t = b * kWave + lane;
+    wd[wave][lane] = b < n_batch ? words[static_cast<size_t>(b) * kWave + lane] : 0ull;
+    const int kept = t < T ? keep_count[t] : 0;
+    int ids[kMaxK];
+#pragma unroll
+    for (int j = 0; j < kMaxK; ++j) ids[j] = j < K ? topk_ids[static_cast<size_t>(min(t, T - 1)) * K + j] : 0;
     {   // lane = expert; the waves split the batches
         const int per_seg = (n_batch + kPlanWaves - 1) / kPlanWaves;
         const int s0 = min(n_batch, wave * per_seg), s1 = min(n_batch, s0 + per_seg);
@@ -983,21 +990,15 @@ __global__ __launch_bounds__(kSpreadThreads) void spread_place_kernel(
         if (tile_info != nullptr && wave == kPlanWaves - 1)
             write_tile_map(expert_off, E, bm, tile_info, static_cast<int>(B));
     }
-    const int b = b0 + wave;
-    if (b < n_batch) {
+    {
         int p = before[lane];
-        for (int bb = b0; bb < b; ++bb) p += __popcll(words[static_cast<size_t>(bb) * kWave + lane]);
+        for (int w = 0; w < wave; ++w) p += __popcll(wd[w][lane]);
         pre[wave][lane] = p;
-        wd[wave][lane] = words[static_cast<size_t>(b) * kWave + lane];
     }
     __syncthreads();
-    const int t = b * kWave + lane;
-    if (b >= n_batch || t >= T) return;
-    const int kt = min(K, keep_count[t]);
+    if (t >= T) return;
+    const int kt = min(K, kept);
     const uint64_t below = lanemask_lt();
-    int ids[kMaxK];
-#pragma unroll
-    for (int j = 0; j < kMaxK; ++j) ids[j] = j < K ? topk_ids[static_cast<size_t>(t) * K + j] : 0;
 #pragma unroll
     for (int j = 0; j < kMaxK; ++j) {
         if (j >= K) continue;

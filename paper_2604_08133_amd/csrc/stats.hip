@@ -123,17 +123,84 @@ __global__ __launch_bounds__(kStatThreads) void load_entropy_kernel(
         token_entropies(scores, wg - E, T, E, H);
 }
 
+// Pearson correlation of two rank vectors from exact integer sums (doubled ranks)
+__device__ __forceinline__ float rank_correlation(long long n, long long sa, long long sb,
+                                                  long long saa, long long sbb, long long sab) {
+    const double va = static_cast<double>(n) * static_cast<double>(saa) -
+                      static_cast<double>(sa) * static_cast<double>(sa);
+    const double vb = static_cast<double>(n) * static_cast<double>(sbb) -
+                      static_cast<double>(sb) * static_cast<double>(sb);
+    const double cov = static_cast<double>(n) * static_cast<double>(sab) -
+                       static_cast<double>(sa) * static_cast<double>(sb);
+    if (va <= 0.0 || vb <= 0.0) return 0.f;   // one side constant
+    return static_cast<float>(cov / sqrt(va * vb));
+}
+
+__device__ __forceinline__ long long wave_sum_int(long long s) {   // (integers: any order)
+    uint64_t v = static_cast<uint64_t>(s);
+    v += lane_xor<32>(v);
+    v += lane_xor<16>(v);
+    v += lane_xor<8>(v);
+    v += lane_xor<4>(v);
+    v += lane_xor<2>(v);
+    v += lane_xor<1>(v);
+    return static_cast<long long>(v);
+}
+
+// the four summary numbers of the experts' loads; one wave, lane = expert
+__device__ __forceinline__ void expert_metrics(const int32_t* __restrict__ load_orig,
+                                               const int32_t* __restrict__ load_kept,
+                                               const float* __restrict__ wload_orig,
+                                               const float* __restrict__ wload_kept, int E,
+                                               float* __restrict__ metrics) {
+    const int lane = lane_id();
+    const bool valid = lane < E;
+    const int lo = valid ? load_orig[lane] : 0, lk = valid ? load_kept[lane] : 0;
+    const float wo = valid ? wload_orig[lane] : 0.f, wk = valid ? wload_kept[lane] : 0.f;
+    int ro = 1, rk = 1;   // doubled average ranks among the E loads
+    for (int o = 0; o < E; ++o) {
+        const int oo = __builtin_amdgcn_readlane(lo, o), ok = __builtin_amdgcn_readlane(lk, o);
+        ro += oo < lo ? 2 : (oo == lo ? 1 : 0);
+        rk += ok < lk ? 2 : (ok == lk ? 1 : 0);
+    }
+    const long long a = valid ? ro : 0, b = valid ? rk : 0;
+    const float rho = rank_correlation(E, wave_sum_int(a), wave_sum_int(b), wave_sum_int(a * a),
+                                       wave_sum_int(b * b), wave_sum_int(a * b));
+    // weighted load distributions
+    const float so = wave_sum(wo), sk = wave_sum(wk);
+    const float p = so > 0.f ? wo / so : 0.f, q = sk > 0.f ? wk / sk : 0.f;
+    const float norm = E > 1 ? 1.f / logf(static_cast<float>(E)) : 0.f;
+    const float ho = wave_sum(p > 0.f ? -p * logf(p) : 0.f) * norm;
+    const float hk = wave_sum(q > 0.f ? -q * logf(q) : 0.f) * norm;
+    const float m = 0.5f * (p + q);
+    const float js = 0.5f * wave_sum((p > 0.f ? p * logf(p / m) : 0.f) +
+                                     (q > 0.f ? q * logf(q / m) : 0.f));
+    if (lane == 0) {
+        metrics[0] = rho;
+        metrics[1] = ho;
+        metrics[2] = hk;
+        metrics[3] = js;
+    }
+}
+
 // Doubled average rank of every token's entropy among all T entropies: 2 #smaller + #equal
 // + 1 = #smaller + #not greater + 1.  All pairs are compared, one compare and one add with
 // carry each: bound by the vector units, so the pairs are spread over all of them: a
 // workgroup ranks 16 tokens (lane % 16), and its 16 waves' 64 groups of 16 lanes take
-// the entropies compared with in turn, four at a time.
+// the entropies compared with in turn, four at a time.  The last workgroup's first wave has the
+// experts' summary numbers instead, which nothing here depends on.
 constexpr int kRankTok = 16;
 constexpr int kRankGroups = kStatThreads / kRankTok;
 constexpr int kRankUnroll = 4;
 
-__global__ __launch_bounds__(kStatThreads) void entropy_rank_kernel(const float* __restrict__ H, int T,
-                                                                    int32_t* __restrict__ rank2) {
+__global__ __launch_bounds__(kStatThreads) void entropy_rank_kernel(
+    const float* __restrict__ H, int T, int32_t* __restrict__ rank2, const int32_t* __restrict__ load_orig,
+    const int32_t* __restrict__ load_kept, const float* __restrict__ wload_orig,
+    const float* __restrict__ wload_kept, int E, float* __restrict__ metrics) {
+    if (blockIdx.x == gridDim.x - 1) {
+        if (threadIdx.x < kWave) expert_metrics(load_orig, load_kept, wload_orig, wload_kept, E, metrics);
+        return;
+    }
     typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));   // H: any 4-byte boundary
     __shared__ int part[kStatWaves][kRankTok];
     const int tid = threadIdx.x, wave = tid / kWave;
@@ -175,131 +242,50 @@ __global__ __launch_bounds__(kStatThreads) void entropy_rank_kernel(const float*
     }
 }
 
-// Pearson correlation of two rank vectors from exact integer sums (doubled ranks)
-__device__ __forceinline__ float rank_correlation(long long n, long long sa, long long sb,
-                                                  long long saa, long long sbb, long long sab) {
-    const double va = static_cast<double>(n) * static_cast<double>(saa) -
-                      static_cast<double>(sa) * static_cast<double>(sa);
-    const double vb = static_cast<double>(n) * static_cast<double>(sbb) -
-                      static_cast<double>(sb) * static_cast<double>(sb);
-    const double cov = static_cast<double>(n) * static_cast<double>(sab) -
-                       static_cast<double>(sa) * static_cast<double>(sb);
-    if (va <= 0.0 || vb <= 0.0) return 0.f;   // one side constant
-    return static_cast<float>(cov / sqrt(va * vb));
-}
-
-// one workgroup: the five summary numbers
+// one workgroup: the correlation of the tokens' entropies with the experts they keep.  A keep
+// count has few values: of the tokens that keep v experts the number n_v and the sum S_v of their
+// entropy ranks are all that is needed beside the sum of squared ranks (b_v being the doubled
+// average rank of v: sum b = sum n_v b_v, sum a b = sum b_v S_v).
 constexpr int kMetricsBatch = 6;
-__global__ __launch_bounds__(kStatThreads) void routing_metrics_kernel(
-    const int32_t* __restrict__ load_orig, const int32_t* __restrict__ load_kept,
-    const float* __restrict__ wload_orig, const float* __restrict__ wload_kept,
+__global__ __launch_bounds__(kStatThreads) void token_metrics_kernel(
     const int32_t* __restrict__ keep_count, const int32_t* __restrict__ entropy_rank2, int T,
-    int E, int K, float* __restrict__ metrics) {
+    float* __restrict__ metrics) {
     constexpr int kValues = 64;   // keep counts counted (0 .. K, K <= 16)
-    constexpr int kSums = 5;
-    __shared__ long long buf[kSums][kStatWaves];
-    __shared__ int32_t k_hist[kValues];
-    __shared__ int32_t k_rank2[kValues];   // doubled average rank of a token that keeps v
-    const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
-    auto isum = [](long long s) {
-        uint64_t v = static_cast<uint64_t>(s);   // (sums of integers: any order)
-        v += lane_xor<32>(v);
-        v += lane_xor<16>(v);
-        v += lane_xor<8>(v);
-        v += lane_xor<4>(v);
-        v += lane_xor<2>(v);
-        v += lane_xor<1>(v);
-        return static_cast<long long>(v);
-    };
-    if (tid < kValues) k_hist[tid] = 0;
-    __syncthreads();
-
-    // ---- expert side, last wave (the others go on to the tokens), lane = expert
-    if (wave == kStatWaves - 1) {
-        const bool valid = lane < E;
-        const int lo = valid ? load_orig[lane] : 0, lk = valid ? load_kept[lane] : 0;
-        int ro = 1, rk = 1;   // doubled average ranks among the E loads
-        for (int o = 0; o < E; ++o) {
-            const int oo = __builtin_amdgcn_readlane(lo, o), ok = __builtin_amdgcn_readlane(lk, o);
-            ro += oo < lo ? 2 : (oo == lo ? 1 : 0);
-            rk += ok < lk ? 2 : (ok == lk ? 1 : 0);
-        }
-        const long long a = valid ? ro : 0, b = valid ? rk : 0;
-        const float rho = rank_correlation(E, isum(a), isum(b), isum(a * a), isum(b * b), isum(a * b));
-        // weighted load distributions
-        const float wo = valid ? wload_orig[lane] : 0.f, wk = valid ? wload_kept[lane] : 0.f;
-        const float so = wave_sum(wo), sk = wave_sum(wk);
-        const float p = so > 0.f ? wo / so : 0.f, q = sk > 0.f ? wk / sk : 0.f;
-        const float norm = E > 1 ? 1.f / logf(static_cast<float>(E)) : 0.f;
-        const float ho = wave_sum(p > 0.f ? -p * logf(p) : 0.f) * norm;
-        const float hk = wave_sum(q > 0.f ? -q * logf(q) : 0.f) * norm;
-        const float m = 0.5f * (p + q);
-        const float js = 0.5f * wave_sum((p > 0.f ? p * logf(p / m) : 0.f) +
-                                         (q > 0.f ? q * logf(q / m) : 0.f));
-        if (lane == 0) {
-            metrics[0] = rho;
-            metrics[1] = ho;
-            metrics[2] = hk;
-            metrics[3] = js;
-        }
-    }
-
-    // ---- token side: doubled ranks of keep_count from its histogram
-    constexpr int kHistThreads = kStatThreads - kWave;
-    if (wave < kStatWaves - 1) {
-        for (int t0 = tid; t0 - lane < T; t0 += kMetricsBatch * kHistThreads) {   // (whole waves)
-            int v[kMetricsBatch];
-#pragma unroll
-            for (int u = 0; u < kMetricsBatch; ++u) {
-                const int t = t0 + u * kHistThreads;
-                v[u] = t < T ? keep_count[t] : -1;
-            }
-            for (int k = 0; k <= K; ++k) {   // one count per wave and value instead of 64 colliding ones
-                int n = 0;
-#pragma unroll
-                for (int u = 0; u < kMetricsBatch; ++u) n += __popcll(__ballot(v[u] == k));
-                if (lane == 0 && n) atomicAdd(&k_hist[k], n);   // integers
-            }
-#pragma unroll
-            for (int u = 0; u < kMetricsBatch; ++u)
-                if (v[u] > K) atomicAdd(&k_hist[v[u]], 1);
-        }
+    __shared__ uint32_t n_of[kValues];
+    __shared__ unsigned long long s_of[kValues], squares;
+    const int tid = threadIdx.x, lane = lane_id();
+    if (tid < kValues) {
+        n_of[tid] = 0;
+        s_of[tid] = 0;
+        if (tid == 0) squares = 0;
     }
     __syncthreads();
-    if (tid < kValues) k_rank2[tid] = 2 * (wave_scan_incl(k_hist[tid]) - k_hist[tid]) + k_hist[tid] + 1;
-    __syncthreads();
-    long long sums[kSums] = {0, 0, 0, 0, 0};   // a, b, a a, b b, a b
+    unsigned long long sq = 0;
     for (int t0 = tid; t0 < T; t0 += kMetricsBatch * kStatThreads) {
         int v[kMetricsBatch], r[kMetricsBatch];
 #pragma unroll
         for (int u = 0; u < kMetricsBatch; ++u) {
             const int t = min(t0 + u * kStatThreads, T - 1);
-            v[u] = keep_count[t];
+            v[u] = keep_count[t] & (kValues - 1);
             r[u] = entropy_rank2[t];
         }
 #pragma unroll
         for (int u = 0; u < kMetricsBatch; ++u) {
             if (t0 + u * kStatThreads >= T) continue;
-            const long long b = k_rank2[v[u]], a = r[u];
-            sums[0] += a;
-            sums[1] += b;
-            sums[2] += a * a;
-            sums[3] += b * b;
-            sums[4] += a * b;
+            atomicAdd(&n_of[v[u]], 1u);   // (integers: any order)
+            atomicAdd(&s_of[v[u]], static_cast<unsigned long long>(r[u]));
+            sq += static_cast<unsigned long long>(r[u]) * r[u];
         }
     }
-#pragma unroll
-    for (int i = 0; i < kSums; ++i) {
-        const long long v = isum(sums[i]);
-        if (lane == 0) buf[i][wave] = v;
-    }
+    sq = static_cast<unsigned long long>(wave_sum_int(static_cast<long long>(sq)));
+    if (lane == 0) atomicAdd(&squares, sq);
     __syncthreads();
-    if (tid == 0) {
-        for (int i = 0; i < kSums; ++i) {
-            sums[i] = 0;
-            for (int w = 0; w < kStatWaves; ++w) sums[i] += buf[i][w];
-        }
-        metrics[4] = rank_correlation(T, sums[0], sums[1], sums[2], sums[3], sums[4]);
+    if (tid < kWave) {   // lane = keep count
+        const int n = static_cast<int>(n_of[lane]);
+        const long long before = wave_scan_incl(n) - n, b = 2 * before + n + 1, s = static_cast<long long>(s_of[lane]);
+        const float rho = rank_correlation(T, wave_sum_int(s), wave_sum_int(n * b), static_cast<long long>(squares),
+                                           wave_sum_int(n * b * b), wave_sum_int(s * b));
+        if (lane == 0) metrics[4] = rho;
     }
 }
 
@@ -313,10 +299,10 @@ hipError_t launch_routing_stats(const float* scores, const int32_t* topk_ids, co
     hipLaunchKernelGGL(load_entropy_kernel, dim3(E + (T + kEntropyWgTok - 1) / kEntropyWgTok),
                        dim3(kStatThreads), 0, stream, scores, topk_ids, topk_s, keep_count, T, E, K,
                        load_orig, load_kept, wload_orig, wload_kept, token_entropy);
-    hipLaunchKernelGGL(entropy_rank_kernel, dim3((T + kRankTok - 1) / kRankTok), dim3(kStatThreads), 0,
-                       stream, token_entropy, T, entropy_rank2);
-    hipLaunchKernelGGL(routing_metrics_kernel, dim3(1), dim3(kStatThreads), 0, stream, load_orig,
-                       load_kept, wload_orig, wload_kept, keep_count, entropy_rank2, T, E, K,
+    hipLaunchKernelGGL(entropy_rank_kernel, dim3((T + kRankTok - 1) / kRankTok + 1), dim3(kStatThreads), 0,
+                       stream, token_entropy, T, entropy_rank2, load_orig, load_kept, wload_orig, wload_kept, E,
+                       metrics);
+    hipLaunchKernelGGL(token_metrics_kernel, dim3(1), dim3(kStatThreads), 0, stream, keep_count, entropy_rank2, T,
                        metrics);
     return hipGetLastError();
 }
