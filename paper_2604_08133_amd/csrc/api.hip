@@ -481,9 +481,8 @@ allocmoe_status forward_impl(const allocmoe_layer_desc* desc, const void* X,
     // The shared expert depends on nothing but X.  On a stream of its own (large layers where a
     // group uses the tile kernel, smaller ones that are mostly shared expert) its two GEMMs run
     // beside selection and the routed experts' GEMMs, and the streams meet again before the
-    // combine: the side stream starts after the routing kernel and the
-    // single-workgroup plan kernel is enqueued first, so that it gets a compute unit
-    // at once.  Decode shapes (both groups on the weight-streaming kernel) keep one
+    // combine: the side stream starts beside or after the routing kernel (below) and the
+    // single-workgroup plan kernel is enqueued first.  Decode shapes (both groups on the weight-streaming kernel) keep one
     // stream and one launch per half for both groups: there the two event waits of a
     // fork and join cost more than the overlap gains.
     const bool overlap = choice.own_stream;
@@ -530,6 +529,19 @@ allocmoe_status forward_impl(const allocmoe_layer_desc* desc, const void* X,
         }
     }
 
+    // The fork point: before the routing kernel, on which the shared expert does not depend (its
+    // kernels are enqueued behind the plan kernel).  An event between the routing and the plan
+    // kernel holds the latter up for 7 us, and the shared expert's kernel starts 13 us after the
+    // routing kernel's end (2048 tokens, 60 experts of 2048 x 1408, shared expert of 5632: layer 349
+    // us, now 333; 64 experts, shared expert of 2816: 130 tokens 211, 201; 2048 311, 301; 4096 452,
+    // 442).  The first round leaves a unit of every die to the plan kernel, which otherwise waits for
+    // the first workgroups to end (4096 tokens: 468).  Long first halves fork behind the routing
+    // kernel: what follows their first round would compete with the routed experts and become the
+    // end of the layer (4096 tokens, shared expert of 5632, 88 workgroups a die: 454 against 432;
+    // 16384 of 2816: 1335 against 1306).
+    const int64_t shared_per_xcd = overlap && shared_tiled ? t256_first_half_per_xcd(s1) : 0;
+    const bool fork_early = overlap && shared_tiled && shared_per_xcd <= 2 * (kUnitsPerXcd - 1);
+    if (fork_early) ALLOCMOE_TRY(hipEventRecord(side->fork, stream));
     // steps 1-2: scores and sorted candidates
     ALLOCMOE_MARK(ALLOCMOE_STAGE_ROUTE);
     if (bf16) {
@@ -541,8 +553,8 @@ allocmoe_status forward_impl(const allocmoe_layer_desc* desc, const void* X,
                                   desc->shared_gate ? w->w_sg : nullptr, T, d, E, K, scores,
                                   topk_ids, topk_s, sgate, stream));
     }
-    if (overlap && shared_tiled) {   // the fork point; the kernels follow the plan kernel
-        ALLOCMOE_TRY(hipEventRecord(side->fork, stream));
+    if (overlap && shared_tiled) {   // (the kernels follow the plan kernel)
+        if (!fork_early) ALLOCMOE_TRY(hipEventRecord(side->fork, stream));
         ALLOCMOE_TRY(hipStreamWaitEvent(side->stream, side->fork, 0));
     }
     // steps 3-4: Alloc-T selection, dispatch, tile map.  Beside the shared expert's GEMMs
@@ -565,7 +577,8 @@ allocmoe_status forward_impl(const allocmoe_layer_desc* desc, const void* X,
     if (overlap && shared_tiled) {
         for (int half = 0; half < 2; ++half) {
             ALLOCMOE_MARK_ON(half == 0 ? kEvSide0 : kEvSide1, side->stream);
-            ALLOCMOE_TRY(launch_ffn_bf16_t256(half == 0, none, half == 0 ? s1 : s2, side->stream));
+            ALLOCMOE_TRY(half == 0 && fork_early ? launch_ffn_bf16_t256_beside(s1, side->stream)
+                                                 : launch_ffn_bf16_t256(half == 0, none, half == 0 ? s1 : s2, side->stream));
         }
         ALLOCMOE_MARK_ON(kEvSide2, side->stream);
         ALLOCMOE_TRY(hipEventRecord(side->join, side->stream));

@@ -45,8 +45,34 @@ void lay_out_dense(StreamGroup& g, int col_tiles, int64_t beside) {
     g.deep_ring = workgroups(h) <= kTargetWorkgroups;
 }
 
-hipError_t launch_ffn_bf16_t256(bool swiglu, StreamGroup routed, StreamGroup shared,
-                                hipStream_t stream) {
+namespace {
+
+// Lays the shared expert's tiles out over the XCDs (StreamGroup::xr); returns the items of the
+// fullest one.
+int64_t spread_dense(bool swiglu, StreamGroup& shared, int64_t ct) {
+    // XCD grid over (row tiles, column tiles): xr x 8/xr, chosen to minimise the
+    // bytes the 8 L2s fetch in total: (8/xr) x activations + xr x weights
+    const int64_t rt = (shared.M_dense + shared.dense_rows - 1) / shared.dense_rows;
+    const double a_bytes = static_cast<double>(shared.M_dense) * shared.Kd;
+    const double b_bytes = static_cast<double>(shared.N) * shared.Kd * (swiglu ? 2 : 1);
+    int best = 1;
+    double best_cost = 0;
+    for (int xr = 1; xr <= kXcds; xr *= 2) {
+        const double cost = (kXcds / xr) * a_bytes + xr * b_bytes;
+        if (xr == 1 || cost < best_cost) {
+            best = xr;
+            best_cost = cost;
+        }
+    }
+    shared.xr = best;
+    const int xc = kXcds / best;
+    return ((rt + best - 1) / best) * ((ct + xc - 1) / xc);
+}
+
+constexpr int kRoundPerXcd = kUnitsPerXcd - 1;
+
+// first_round: as launch_ffn_bf16_t256_beside
+hipError_t launch_t256(bool swiglu, StreamGroup routed, StreamGroup shared, bool first_round, hipStream_t stream) {
     const int cols = swiglu ? 128 : 256;
     auto col_tiles = [cols](const StreamGroup& g) { return (g.N + cols - 1) / cols; };
     if (routed.A != nullptr && routed.tile_info == nullptr) lay_out_dense(routed, col_tiles(routed), 0);
@@ -65,38 +91,48 @@ hipError_t launch_ffn_bf16_t256(bool swiglu, StreamGroup routed, StreamGroup sha
         per_xcd += tiles * col_tiles(routed);
     }
     if (shared.A != nullptr) {
-        // XCD grid over (row tiles, column tiles): xr x 8/xr, chosen to minimise the
-        // bytes the 8 L2s fetch in total: (8/xr) x activations + xr x weights
-        const int64_t rt = (shared.M_dense + shared.dense_rows - 1) / shared.dense_rows, ct = col_tiles(shared);
-        const double a_bytes = static_cast<double>(shared.M_dense) * shared.Kd;
-        const double b_bytes = static_cast<double>(shared.N) * shared.Kd * (swiglu ? 2 : 1);
-        int best = 1;
-        double best_cost = 0;
-        for (int xr = 1; xr <= kXcds; xr *= 2) {
-            const double cost = (kXcds / xr) * a_bytes + xr * b_bytes;
-            if (xr == 1 || cost < best_cost) {
-                best = xr;
-                best_cost = cost;
-            }
-        }
-        shared.xr = best;
-        const int xc = kXcds / best;
-        per_xcd += ((rt + best - 1) / best) * ((ct + xc - 1) / xc);
+        per_xcd += spread_dense(swiglu, shared, col_tiles(shared));
     }
     if (per_xcd <= 0) return hipSuccess;
-    const dim3 grid(static_cast<unsigned>(per_xcd * kXcds));
+    const dim3 whole(static_cast<unsigned>(per_xcd * kXcds));
     const bool fp8 = (routed.A ? routed.scale : shared.scale) != nullptr;
     if (routed.A && shared.A && (routed.scale != nullptr) != (shared.scale != nullptr))
         return hipErrorInvalidValue;   // one weight format per launch
-    if (swiglu && fp8)
-        enqueue_t256<true, true>(grid, routed, shared, stream);
-    else if (swiglu)
-        enqueue_t256<true, false>(grid, routed, shared, stream);
-    else if (fp8)
-        enqueue_t256<false, true>(grid, routed, shared, stream);
-    else
-        enqueue_t256<false, false>(grid, routed, shared, stream);
+    auto enqueue = [&](dim3 grid) {
+        if (swiglu && fp8)
+            enqueue_t256<true, true>(grid, routed, shared, stream);
+        else if (swiglu)
+            enqueue_t256<true, false>(grid, routed, shared, stream);
+        else if (fp8)
+            enqueue_t256<false, true>(grid, routed, shared, stream);
+        else
+            enqueue_t256<false, false>(grid, routed, shared, stream);
+    };
+    if (first_round && per_xcd > kRoundPerXcd) {
+        enqueue(dim3(kRoundPerXcd * kXcds));
+        shared.first_item = kRoundPerXcd;
+        enqueue(dim3(static_cast<unsigned>((per_xcd - kRoundPerXcd) * kXcds)));
+    } else {
+        enqueue(whole);
+    }
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_ffn_bf16_t256(bool swiglu, StreamGroup routed, StreamGroup shared, hipStream_t stream) {
+    return launch_t256(swiglu, routed, shared, false, stream);
+}
+
+hipError_t launch_ffn_bf16_t256_beside(StreamGroup shared, hipStream_t stream) {
+    return launch_t256(true, StreamGroup{}, shared, true, stream);
+}
+
+int64_t t256_first_half_per_xcd(const StreamGroup& group) {
+    StreamGroup shared = group;
+    const int col_tiles = (shared.N + 127) / 128;
+    lay_out_dense(shared, col_tiles, 0);
+    return spread_dense(true, shared, col_tiles);
 }
 
 }  // namespace allocmoe

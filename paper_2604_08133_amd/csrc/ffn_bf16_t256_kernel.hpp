@@ -517,7 +517,7 @@ __global__ __launch_bounds__(kWaves* kWave, 1) void ffn_bf16_t256_kernel(StreamG
     //    pass over the weight stream; the column tiles that share the gathered
     //    activation rows follow within a few items.
     constexpr int kColsPerTile = SWIGLU ? 128 : 256;
-    const int xcd = blockIdx.x % kXcds, idx = blockIdx.x / kXcds;
+    const int xcd = blockIdx.x % kXcds, idx = g1.first_item + blockIdx.x / kXcds;
     const int nt0 = g0.A ? (g0.N + kColsPerTile - 1) / kColsPerTile : 1;
     const int nt1 = g1.A ? (g1.N + kColsPerTile - 1) / kColsPerTile : 1;
     int S = 0, s_rows = 1;     // dense group: items and row tiles of this XCD

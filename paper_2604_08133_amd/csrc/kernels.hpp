@@ -109,6 +109,7 @@ struct StreamGroup {
     int64_t n_wg = 0;          // filled by the launcher
     int xr = 1;                // dense group: XCDs along the row tiles (filled by the launcher)
     int dense_rows = 256;      // dense group, tile kernel: rows per tile (filled by the launcher)
+    int first_item = 0;        // dense group, tile kernel: first of an XCD's items in this launch (filled by the launcher)
     bool deep_ring = false;    // the same: few workgroups, weights further ahead (filled by the launcher)
     // 8-bit weights: Bp holds E4M3 codes, one byte per element
     // (group_stride in bytes), and scale[g][stream][n] the fp32 scale of every output
@@ -125,6 +126,12 @@ hipError_t launch_ffn_bf16_stream(bool swiglu, StreamGroup routed, StreamGroup s
 constexpr int kTileRowsLarge = 256;
 hipError_t launch_ffn_bf16_t256(bool swiglu, StreamGroup routed, StreamGroup shared,
                                 hipStream_t stream);
+// The shared expert's first half, starting beside the routing kernel: the first round of its
+// workgroups as a launch of its own that leaves a compute unit of every die to the plan kernel.
+hipError_t launch_ffn_bf16_t256_beside(StreamGroup shared, hipStream_t stream);
+// compute units of a die, and how many workgroups the shared expert's first half has for it
+constexpr int kUnitsPerXcd = 32;
+int64_t t256_first_half_per_xcd(const StreamGroup& shared);
 
 // ---- pack.hip : row-major [G][Kd][N] bf16 -> MFMA fragment order
 // the gate matrix and the shared expert's gate vector (may be null), re-tiled in the same launch
