@@ -231,8 +231,9 @@ typedef enum {
     ALLOCMOE_STAGE_COMBINE = 4, /* step 6: Eq. (2)                                           */
     ALLOCMOE_STAGE_SHARED_FFN1 = 5, /* the shared expert's first GEMM on the library's stream */
     ALLOCMOE_STAGE_SHARED_FFN2 = 6, /* its second GEMM there (both 0 if that stream was idle) */
-    ALLOCMOE_STAGE_EXPERT_SPAN = 7, /* start of PLAN to start of COMBINE: the region in which */
-                                /* every expert GEMM of the layer runs, on either stream     */
+    ALLOCMOE_STAGE_EXPERT_SPAN = 7, /* start of PLAN, or of SHARED_FFN1 where that is earlier, */
+                                /* to start of COMBINE: the region in which every expert     */
+                                /* GEMM of the layer runs, on either stream                  */
     ALLOCMOE_STAGE_TOTAL = 8,   /* start of ROUTE to the end of COMBINE                      */
     ALLOCMOE_N_STAGES = 9
 } allocmoe_stage;

@@ -736,6 +736,11 @@ allocmoe_status allocmoe_moe_forward_timed(const allocmoe_layer_desc* desc, cons
     ALLOCMOE_TRY(hipEventElapsedTime(&stage_ms[ALLOCMOE_STAGE_SHARED_FFN2], ev[kEvSide1], ev[kEvSide2]));
     ALLOCMOE_TRY(hipEventElapsedTime(&stage_ms[ALLOCMOE_STAGE_EXPERT_SPAN], ev[ALLOCMOE_STAGE_PLAN],
                                      ev[ALLOCMOE_STAGE_COMBINE]));
+    // (the shared expert may start beside the routing kernel; with one stream its marks stand at
+    // the end and the interval is negative)
+    float from_shared = 0.f;
+    ALLOCMOE_TRY(hipEventElapsedTime(&from_shared, ev[kEvSide0], ev[ALLOCMOE_STAGE_COMBINE]));
+    stage_ms[ALLOCMOE_STAGE_EXPERT_SPAN] = std::max(stage_ms[ALLOCMOE_STAGE_EXPERT_SPAN], from_shared);
     ALLOCMOE_TRY(hipEventElapsedTime(&stage_ms[ALLOCMOE_STAGE_TOTAL], ev[0], ev[5]));
     return ALLOCMOE_OK;
 }
