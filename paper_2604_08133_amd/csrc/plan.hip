@@ -500,20 +500,25 @@ __device__ __forceinline__ Threshold find_threshold(FastShared<NT>& sh, const ui
     }
     if (count <= kCollect) {
         // ---- rank the bin's keys directly
-        uint32_t n = 0;
-        for_entries<NT>(n_pool, [&](auto q_const) {
-            constexpr int q = decltype(q_const)::value;
-            n += key[q] >= lo && key[q] <= hi ? 1u : 0u;
-        });
-        uint32_t slot = n ? atomicAdd(&sh.n_collected, n) : 0u;   // (the order does not matter)
-        if (__ballot(n != 0u)) {
+        if (n_pool <= kCollect) {   // (the whole pool: it sits in the first lanes)
+            if (tid < n_pool)
+                sh.collected[tid] = (static_cast<uint64_t>(key[0]) << 32) | ~static_cast<uint32_t>(tid);
+        } else {
+            uint32_t n = 0;
             for_entries<NT>(n_pool, [&](auto q_const) {
                 constexpr int q = decltype(q_const)::value;
-                const bool in = key[q] >= lo && key[q] <= hi;
-                sh.collected[in && slot < kCollect ? slot : kCollect + lane] =
-                    (static_cast<uint64_t>(key[q]) << 32) | ~static_cast<uint32_t>(q * NT + tid);
-                slot += in ? 1u : 0u;
+                n += key[q] >= lo && key[q] <= hi ? 1u : 0u;
             });
+            uint32_t slot = n ? atomicAdd(&sh.n_collected, n) : 0u;   // (the order does not matter)
+            if (__ballot(n != 0u)) {
+                for_entries<NT>(n_pool, [&](auto q_const) {
+                    constexpr int q = decltype(q_const)::value;
+                    const bool in = key[q] >= lo && key[q] <= hi;
+                    sh.collected[in && slot < kCollect ? slot : kCollect + lane] =
+                        (static_cast<uint64_t>(key[q]) << 32) | ~static_cast<uint32_t>(q * NT + tid);
+                    slot += in ? 1u : 0u;
+                });
+            }
         }
         __syncthreads();
         const uint64_t mine = sh.collected[lane];   // (cleared where nothing was written)
