@@ -317,8 +317,8 @@ class Bench:
             # prefill shapes: the tile kernel runs the routed rows on the caller's stream and
             # the shared expert on the library's stream beside them (two launches each).  The
             # figure is the summed work of those launches over the wall-clock region in which
-            # they run: from the start of the plan stage (the shared expert's first GEMM starts
-            # there) to the start of the combine.
+            # they run: from the start of the plan stage, or of the shared expert's first GEMM
+            # where that is earlier, to the start of the combine.
             flops = pairs * 6 * d * I + nL * T * 6 * d * Is
             nbytes = (n_active * 3 * d * I * wb + pairs * (d * 2 + 2 * I * 2 + d * 2)
                       + nL * (3 * d * Is * wb + T * (d * 2 + 2 * Is * 2 + d * 2) if Is else 0))
@@ -341,7 +341,7 @@ class Bench:
                 "kernel": "ffn_bf16_t256_kernel" + targs + " and " + targs.replace("true,", "false,", 1)
                           + f": the {launches} launches of a layer (selected rows on the caller's "
                           "stream, shared expert on the library's stream), timed as one region "
-                          "from the start of the plan stage to the start of the combine",
+                          "from the start of the plan stage, or of the shared expert where that is earlier, to the start of the combine",
                 "kernel_ms": ms / nL, "launches_per_step": nL * launches,
                 "algorithmic_flops": flops / nL, "algorithmic_bytes": nbytes / nL,
                 "per_launch_ms": {k: round(stages[k] / nL, 5)
