@@ -116,8 +116,9 @@ __global__ __launch_bounds__(kStreamWaves* kWave) void ffn_bf16_stream_kernel(St
     }
     // packed B: for this expert and column block, KB fragments of 64 x 16 bytes (the W1 stream,
     // then for SWIGLU the W3 stream, else the next column block's; a stream holds Kd * 32
-    // elements: 2 bytes each, or 1 with FP8).  Through buffer loads: scalar base and step
-    // offset, and a step past the end reads zeros.
+    // elements: 2 bytes each, or 1 with FP8).  Through buffer loads: a scalar base and the step in
+    // the lane's offset.  That offset is what the range check looks at (a scalar offset beside
+    // it is documented as left out), so a step past the end reads zeros and touches no memory.
     const uint32_t stream_bytes = static_cast<uint32_t>(KB) * 1024u;
     const char* b0 = Bp + (static_cast<size_t>(e) * group_stride +
                            static_cast<size_t>(nb) * (static_cast<size_t>(STREAMS) * Kd * 32)) * (FP8 ? 1 : 2);
@@ -133,7 +134,7 @@ __global__ __launch_bounds__(kStreamWaves* kWave) void ffn_bf16_stream_kernel(St
     auto load_w = [&](int u, int step) {
 #pragma unroll
         for (int j = 0; j < STREAMS; ++j)
-            w[u][j] = __builtin_amdgcn_raw_buffer_load_b128(rs[j], lane * 16, (step * kStreamWaves + wave) * 1024, kNonTemporal);
+            w[u][j] = __builtin_amdgcn_raw_buffer_load_b128(rs[j], (step * kStreamWaves + wave) * 1024 + lane * 16, 0, kNonTemporal);
     };
     const bf16x8* ap;
     auto load_a = [&](int u, int step) {   // (past the end: the last step's again)
