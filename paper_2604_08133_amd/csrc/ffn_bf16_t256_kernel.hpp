@@ -170,11 +170,11 @@ __device__ __forceinline__ void t256_body(char* lds, const bf16_t* A, size_t lda
     const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds0 + wave * 1024);
     typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4;
     // Weight fragments come through buffer loads: a scalar descriptor per stream
-    // (base, size), the lane's offset in a VGPR and the k16 step's offset in an SGPR,
-    // so a load costs no address arithmetic on the vector unit; a step past the end
-    // of the stream reads zeros instead of faulting.  Weights that no other tile
-    // reads are marked non-temporal: they need not displace what the caches hold
-    // for tiles that share theirs.
+    // (base, size) and the step in the lane's offset, one addition for the loads of a 32-k
+    // step.  That offset is what the range check looks at (a scalar offset beside it is
+    // documented as left out), so a step past the end of the stream reads zeros and touches no
+    // memory.  Weights that no other tile reads are marked non-temporal: they need not displace
+    // what the caches hold for tiles that share theirs.
     const int stream_bytes = live ? KT * kStepK * 32 * (FP8 ? 1 : 2) : 0;
     const __amdgpu_buffer_rsrc_t rs0 = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<void*>(b0), 0, stream_bytes, 0x00020000);
@@ -186,8 +186,8 @@ __device__ __forceinline__ void t256_body(char* lds, const bf16_t* A, size_t lda
     constexpr int NH = FP8 ? 1 : 2;
     i32x4 ring[NR][2][NH];
     auto load_b = [&](int r, int j, int h, int d) {   // entry r <- 32-k step d
-        ring[r][j][h] = __builtin_amdgcn_raw_buffer_load_b128(j == 0 ? rs0 : rs1, lane_off,
-                                                              (d * NH + h) * 1024, kAux);
+        ring[r][j][h] = __builtin_amdgcn_raw_buffer_load_b128(j == 0 ? rs0 : rs1, lane_off + (d * NH + h) * 1024,
+                                                              0, kAux);
     };
     // The matrix instruction is 16x16x32: its operand holds row (or column) l%16 in lane l,
     // and lane group l/16 supplies 8 of the 32 k.  Which k the groups take is free as long as

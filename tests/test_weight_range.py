@@ -9,8 +9,22 @@ import pytest
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2604_08133_amd", "csrc")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-SOURCES = {
+TILE = """
+#include "ffn_bf16_t256_kernel.hpp"
+namespace allocmoe {
+__global__ void probe(const bf16_t* A, const int32_t* row_map, const char* b, const float* sc, int KT, void* C) {
+    __shared__ __attribute__((aligned(1024))) char lds[kSlots * kSlotBytes];
+    t256_body<BODY>(lds, A, KT * kStepK, row_map, b, b + KT * 4096, sc, sc + 32, KT, threadIdx.x / kWave, lane_id(),
+                    0, 33, 0, true, C, 64);
+}
+}
+"""
+SOURCES = {   # tile kernel: SwiGLU, 16-row blocks, weights read once, 8-bit, steps held
     "streaming kernel": '#include "ffn_bf16.hip"',
+    "tile kernel, 4 steps": TILE.replace("BODY", "true, 3, true, false, 4"),
+    "tile kernel, 8 steps": TILE.replace("BODY", "false, 3, false, false, 8"),
+    "tile kernel, 12 steps": TILE.replace("BODY", "true, 3, false, false, 12"),
+    "tile kernel, 8-bit": TILE.replace("BODY", "false, 3, true, true, 8"),
 }
 
 
