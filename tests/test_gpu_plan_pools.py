@@ -14,6 +14,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("T,E,K,Kb,levels", [
     (1, 8, 2, 1, 0), (16, 16, 5, 1, 0), (13, 16, 5, 0, 0), (64, 64, 2, 1, 4),       # pools of 1, 64, 65, 64
+    (85, 20, 4, 1, 0), (64, 20, 5, 1, 0), (64, 20, 5, 1, 3), (256, 20, 2, 1, 0),     # 255, 256: an entry a thread
     (86, 20, 4, 1, 0), (86, 20, 4, 1, 2),                                          # 258: a second entry for some
     (333, 64, 8, 1, 0), (333, 64, 8, 1, 64), (1000, 64, 6, 0, 3),
     (768, 33, 16, 0, 0), (1024, 40, 12, 0, 256),                                   # 48 entries a thread
