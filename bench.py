@@ -315,16 +315,18 @@ class Bench:
                 roof["measured_peak"] = measured["hbm_read"]["non_temporal"]["gbs"]
         else:
             # prefill shapes: the tile kernel runs the routed rows on the caller's stream and
-            # the shared expert on the library's stream beside them (two launches each).  The
-            # figure is the summed work of those launches over the wall-clock region in which
-            # they run: from the start of the plan stage, or of the shared expert's first GEMM
+            # the shared expert on the library's stream beside them (two launches each; its first
+            # half takes two where it starts beside the routing kernel and is more than a round of
+            # workgroups).  The figure is the summed work of those launches over the wall-clock
+            # region in which they run: from the start of the plan stage, or of the shared expert's first GEMM
             # where that is earlier, to the start of the combine.
             flops = pairs * 6 * d * I + nL * T * 6 * d * Is
             nbytes = (n_active * 3 * d * I * wb + pairs * (d * 2 + 2 * I * 2 + d * 2)
                       + nL * (3 * d * Is * wb + T * (d * 2 + 2 * Is * 2 + d * 2) if Is else 0))
             ms = stages["expert_span"]
             attainable = min(MFMA_BF16_PEAK_TFLOPS, flops / nbytes * HBM_PEAK_GBS / 1e3)
-            launches = (2 if pairs else 0) + (2 if Is else 0)
+            per_layer = [self.B.allocmoe_expert_launches(dc) for dc in self.descs]
+            launches = "/".join(map(str, sorted(set(per_layer))))
             if attainable < MFMA_BF16_PEAK_TFLOPS * 0.6:
                 # weight-bound: below the ridge the HBM side of the roofline is the binding one
                 roof = {"bound": "hbm", "achieved": nbytes / (ms * 1e-3) / 1e9,
@@ -342,7 +344,7 @@ class Bench:
                           + f": the {launches} launches of a layer (selected rows on the caller's "
                           "stream, shared expert on the library's stream), timed as one region "
                           "from the start of the plan stage, or of the shared expert where that is earlier, to the start of the combine",
-                "kernel_ms": ms / nL, "launches_per_step": nL * launches,
+                "kernel_ms": ms / nL, "launches_per_step": sum(per_layer),
                 "algorithmic_flops": flops / nL, "algorithmic_bytes": nbytes / nL,
                 "per_launch_ms": {k: round(stages[k] / nL, 5)
                                   for k in ("ffn1", "ffn2", "shared_ffn1", "shared_ffn2")},

@@ -252,6 +252,10 @@ allocmoe_status allocmoe_moe_forward_timed(const allocmoe_layer_desc *desc, cons
                                            size_t ws_bytes, allocmoe_stream stream,
                                            float *stage_ms);
 
+/* Number of kernel launches in which allocmoe_moe_forward runs the expert networks of a bf16
+ * layer (routed and shared, both GEMMs).  Host arithmetic; for descriptions of a benchmark. */
+allocmoe_status allocmoe_expert_launches(const allocmoe_layer_desc *desc, int32_t *launches);
+
 /* Ceiling probes (measurement utilities, not on the layer's path; both WAIT for their
  * kernels and copy a few bytes back).  The rooflines of the layer's kernels are quoted
  * against the published peaks; these re-measure what the device at hand sustains.

@@ -22,6 +22,7 @@ EXPORTS = [
     "allocmoe_workspace_bytes", "allocmoe_workspace_layout", "allocmoe_packed_bytes",
     "allocmoe_pack_weights", "allocmoe_route", "allocmoe_route_from_scores",
     "allocmoe_dispatch", "allocmoe_dispatch_static", "allocmoe_moe_forward", "allocmoe_moe_forward_timed",
+    "allocmoe_expert_launches",
     "allocmoe_alloc_l", "allocmoe_layer_schedule", "allocmoe_routing_stats",
     "allocmoe_probe_mfma_operand_bytes", "allocmoe_probe_sink_bytes", "allocmoe_probe_mfma",
     "allocmoe_probe_hbm_read",
@@ -147,6 +148,13 @@ def allocmoe_packed_bytes(desc: LayerDesc) -> int:
     n = ctypes.c_size_t(0)
     _check(load().allocmoe_packed_bytes(ctypes.byref(desc), ctypes.byref(n)),
            "allocmoe_packed_bytes")
+    return n.value
+
+
+def allocmoe_expert_launches(desc: LayerDesc) -> int:
+    """Kernel launches of the expert networks in one forward pass of a bf16 layer."""
+    n = ctypes.c_int32(0)
+    _check(load().allocmoe_expert_launches(ctypes.byref(desc), ctypes.byref(n)), "allocmoe_expert_launches")
     return n.value
 
 

@@ -438,6 +438,28 @@ allocmoe_status validate_forward(const allocmoe_layer_desc* desc, const void* X,
     return ALLOCMOE_OK;
 }
 
+// Whether the shared expert, which does not depend on the routing kernel, starts beside it.
+// An event between the routing and the plan kernel holds the latter up for 7 us, and the
+// shared expert's kernel starts 13 us after the routing kernel's end (2048 tokens, 60 experts of 2048 x 1408, shared expert of 5632: layer 349
+// us, now 333; 64 experts, shared expert of 2816: 130 tokens 211, 201; 2048 311, 301; 4096 452,
+// 442).  The first round leaves a unit of every die to the plan kernel, which otherwise waits for
+// the first workgroups to end (4096 tokens: 468).  Long first halves fork behind the routing
+// kernel: what follows their first round would compete with the routed experts and become the
+// end of the layer (4096 tokens, shared expert of 5632, 88 workgroups a die: 454 against 432;
+// 16384 of 2816: 1335 against 1306).
+bool forks_early(const FfnChoice& c, const StreamGroup& first_half) {
+    return c.own_stream && c.shared_tiled && t256_first_half_per_xcd(first_half) <= 2 * kRoundPerXcd;
+}
+
+// Kernel launches of the expert networks: two for either group, or for both groups where they share
+// them; the shared expert's first half takes two where it starts early and is more than a round.
+int expert_launches(const FfnChoice& c, bool routed, const StreamGroup& first_half) {
+    const bool shared = first_half.N > 0;
+    if (!c.own_stream && c.routed_tiled == c.shared_tiled) return routed || shared ? 2 : 0;
+    const bool split = shared && forks_early(c, first_half) && t256_first_half_per_xcd(first_half) > kRoundPerXcd;
+    return (routed ? 2 : 0) + (shared ? 2 : 0) + (split ? 1 : 0);
+}
+
 // (state.lock held)
 allocmoe_status forward_impl(const allocmoe_layer_desc* desc, const void* X,
                              const allocmoe_weights* w, void* Y, void* ws, size_t ws_bytes,
@@ -529,18 +551,9 @@ allocmoe_status forward_impl(const allocmoe_layer_desc* desc, const void* X,
         }
     }
 
-    // The fork point: before the routing kernel, on which the shared expert does not depend (its
-    // kernels are enqueued behind the plan kernel).  An event between the routing and the plan
-    // kernel holds the latter up for 7 us, and the shared expert's kernel starts 13 us after the
-    // routing kernel's end (2048 tokens, 60 experts of 2048 x 1408, shared expert of 5632: layer 349
-    // us, now 333; 64 experts, shared expert of 2816: 130 tokens 211, 201; 2048 311, 301; 4096 452,
-    // 442).  The first round leaves a unit of every die to the plan kernel, which otherwise waits for
-    // the first workgroups to end (4096 tokens: 468).  Long first halves fork behind the routing
-    // kernel: what follows their first round would compete with the routed experts and become the
-    // end of the layer (4096 tokens, shared expert of 5632, 88 workgroups a die: 454 against 432;
-    // 16384 of 2816: 1335 against 1306).
-    const int64_t shared_per_xcd = overlap && shared_tiled ? t256_first_half_per_xcd(s1) : 0;
-    const bool fork_early = overlap && shared_tiled && shared_per_xcd <= 2 * (kUnitsPerXcd - 1);
+    // The fork point: before or behind the routing kernel (forks_early); the shared expert's
+    // kernels are enqueued behind the plan kernel.
+    const bool fork_early = forks_early(choice, s1);
     if (fork_early) ALLOCMOE_TRY(hipEventRecord(side->fork, stream));
     // steps 1-2: scores and sorted candidates
     ALLOCMOE_MARK(ALLOCMOE_STAGE_ROUTE);
@@ -693,6 +706,18 @@ allocmoe_status allocmoe_dispatch_static(const allocmoe_layer_desc* desc, const 
                                  expert_offsets, row_token, row_rank, inv_row,
                                  at<uint64_t>(base, s.words), at<int32_t>(base, s.prefix),
                                  kTileRowsSmall, nullptr, true, stream));
+    return ALLOCMOE_OK;
+}
+
+allocmoe_status allocmoe_expert_launches(const allocmoe_layer_desc* desc, int32_t* launches) {
+    if (launches == nullptr) return ALLOCMOE_EINVAL;
+    const allocmoe_status st = check_desc(desc);
+    if (st != ALLOCMOE_OK) return st;
+    if (desc->dtype != ALLOCMOE_BF16) return ALLOCMOE_EINVAL;
+    StreamGroup s1;   // the shared expert's first half, as far as the rules look at it
+    s1.Kd = desc->d; s1.N = desc->I_shared; s1.M_dense = desc->T;
+    *launches = expert_launches(choose_ffn(desc->T, desc->d, desc->E, desc->I, desc->I_shared, desc->budget),
+                                desc->budget > 0, s1);
     return ALLOCMOE_OK;
 }
 

@@ -69,8 +69,6 @@ int64_t spread_dense(bool swiglu, StreamGroup& shared, int64_t ct) {
     return ((rt + best - 1) / best) * ((ct + xc - 1) / xc);
 }
 
-constexpr int kRoundPerXcd = kUnitsPerXcd - 1;
-
 // first_round: as launch_ffn_bf16_t256_beside
 hipError_t launch_t256(bool swiglu, StreamGroup routed, StreamGroup shared, bool first_round, hipStream_t stream) {
     const int cols = swiglu ? 128 : 256;

@@ -129,8 +129,9 @@ hipError_t launch_ffn_bf16_t256(bool swiglu, StreamGroup routed, StreamGroup sha
 // The shared expert's first half, starting beside the routing kernel: the first round of its
 // workgroups as a launch of its own that leaves a compute unit of every die to the plan kernel.
 hipError_t launch_ffn_bf16_t256_beside(StreamGroup shared, hipStream_t stream);
-// compute units of a die, and how many workgroups the shared expert's first half has for it
-constexpr int kUnitsPerXcd = 32;
+// compute units of a die, those that the first round takes, and how many workgroups the shared expert's
+// first half has for a die
+constexpr int kUnitsPerXcd = 32, kRoundPerXcd = kUnitsPerXcd - 1;
 int64_t t256_first_half_per_xcd(const StreamGroup& shared);
 
 // ---- pack.hip : row-major [G][Kd][N] bf16 -> MFMA fragment order
