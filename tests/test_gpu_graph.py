@@ -26,6 +26,21 @@ def test_forward_replays_from_a_graph(kind):
         w = synth.Workload("graph_prefill", T=300, d=256, E=8, I=128, K=3, K_base=1, budget=500,
                            dtype="bf16", I_shared=128, I_shared_each=128, bias_kind="normal")
     assert choice_of(w) == (kind == "large",) * 3
+    check_replays(w, kind)
+
+
+def test_split_first_half_replays_from_a_graph():
+    # the shared expert beside the routing kernel, its first half in two launches (48 workgroups a die):
+    # in the graph routing and the shared expert are both roots
+    w = synth.Workload("graph_split", T=4096, d=1024, E=8, I=256, K=2, K_base=1, budget=6000, dtype="bf16",
+                       I_shared=2816, I_shared_each=2816, bias_kind="normal")
+    assert choice_of(w) == (True, True, True)
+    desc = B.make_desc(w.T, w.d, w.E, w.I, w.K, w.K_base, w.budget, w.dtype, w.I_shared)
+    assert B.allocmoe_expert_launches(desc) == 5
+    check_replays(w, "split")
+
+
+def check_replays(w, kind):
     layer = synth.make_layer(w, seed=81)
     dev = DeviceLayer(w, layer)
     desc = dev.desc()

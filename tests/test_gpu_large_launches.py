@@ -42,7 +42,7 @@ def test_bf16_packing_of_a_very_large_layer():
 
 
 def test_8bit_packing_of_a_very_wide_layer():
-    # 4.19e6 strips of 64 columns, 1024 threads each: every expert as it is packed alone
+    # 8.39e6 strips of 32 columns, 512 threads each, in two launches: every expert as it is packed alone
     need(95)
     E, d, I = 64, 128, 2 ** 21 + 128
     W = torch.empty(E * d * I, dtype=torch.int16, device="cuda").random_()

@@ -14,7 +14,7 @@ DEV = "cuda:0"
 
 def gpu_route_dispatch(scores_cpu, K, Kb, budget, select_ws=True):
     """select_ws: hand the selection a workspace, with which it runs on many workgroups
-    from 2048 tokens on; without, one workgroup selects whatever the size."""
+    from 4096 tokens on; without, one workgroup selects whatever the size."""
     T, E = scores_cpu.shape
     desc = B.make_desc(T, 64, E, 64, K, Kb, budget, "f32")
     s = scores_cpu.to(DEV)
