@@ -336,8 +336,7 @@ allocmoe_status allocmoe_dispatch(const allocmoe_layer_desc* desc, const int32_t
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     ALLOCMOE_TRY(launch_dispatch(topk_ids, keep_count, desc->T, desc->K, desc->E, desc->budget,
                                  expert_offsets, row_token, row_rank, inv_row,
-                                 at<uint64_t>(ws, s.words), at<int32_t>(ws, s.prefix),
-                                 kTileRowsSmall, nullptr, true, stream));
+                                 at<uint64_t>(ws, s.words), kTileRowsSmall, nullptr, true, stream));
     return ALLOCMOE_OK;
 }
 
@@ -704,8 +703,7 @@ allocmoe_status allocmoe_dispatch_static(const allocmoe_layer_desc* desc, const 
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     ALLOCMOE_TRY(launch_dispatch(topk_ids, keep_count, desc->T, desc->K, desc->E, desc->budget,
                                  expert_offsets, row_token, row_rank, inv_row,
-                                 at<uint64_t>(base, s.words), at<int32_t>(base, s.prefix),
-                                 kTileRowsSmall, nullptr, true, stream));
+                                 at<uint64_t>(base, s.words), kTileRowsSmall, nullptr, true, stream));
     return ALLOCMOE_OK;
 }
 

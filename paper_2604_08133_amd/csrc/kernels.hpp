@@ -62,7 +62,7 @@ hipError_t launch_select(const float* topk_s, int T, int K, int Kb, int64_t B,
                          int32_t* keep_count, void* spread, hipStream_t stream);
 hipError_t launch_dispatch(const int32_t* topk_ids, const int32_t* keep_count, int T, int K,
                            int E, int64_t B, int32_t* expert_offsets, int32_t* row_token,
-                           int32_t* row_rank, int32_t* inv_row, uint64_t* words, int32_t* prefix,
+                           int32_t* row_rank, int32_t* inv_row, uint64_t* words,
                            int bm, int32_t* tile_info, bool alone, hipStream_t stream);
 hipError_t launch_plan(const float* topk_s, const int32_t* topk_ids, int T, int K, int Kb,
                        int64_t B, int E, int32_t* keep_count, int32_t* expert_offsets,

@@ -47,7 +47,6 @@ struct PlanShared {
 
 // Exclusive block-wide prefix sum of one value per thread, in thread order.
 // Returns the exclusive prefix; *total (optional) receives the block sum.
-template <int NW = kPlanWaves>
 __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t* wave_tot,
                                                     uint32_t* total) {
     const int lane = lane_id(), wave = threadIdx.x / kWave;
@@ -55,7 +54,7 @@ __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t* wave_t
     if (lane == kWave - 1) wave_tot[wave] = incl;
     __syncthreads();
     uint32_t base = 0, sum = 0;
-    for (int w = 0; w < NW; ++w) {
+    for (int w = 0; w < kPlanWaves; ++w) {
         const uint32_t x = wave_tot[w];
         if (w < wave) base += x;
         sum += x;
@@ -319,7 +318,7 @@ __device__ void tilemap_phase(PlanShared& sh, int E, int bm, int32_t* __restrict
 }
 
 // ---------------------------------------------------------------------------
-// Fast path (T <= 8192 and at most 48 pool keys per thread): the same two phases, but
+// Fast path (T <= 8192 and at most 48 pool keys per thread of 1024): the same two phases, but
 // everything is read from global memory once: the pool keys into registers, where they stay
 // for every pass, the candidate ids into LDS (one byte each), where the keep counts, ballot
 // words and prefixes live as well.
@@ -343,7 +342,7 @@ __device__ void tilemap_phase(PlanShared& sh, int E, int bm, int32_t* __restrict
 // 6.0, 2.6, 1.7, 2.0.  Whole kernel, then and now: 64 tokens x 6 14.7, 6.2; 777 x 4 21.0, 9.9;
 // 2048 x 4 42, 19; 4096 x 6 60, 33.
 constexpr int kFastMaxT = 8192;
-constexpr int kFastMaxKeys = 48;
+constexpr int kFastMaxPool = 48 * kPlanThreads;
 constexpr int kCrowd = 8;          // share of the pool in one bin from which on its range is measured
 constexpr int kCollect = 64;       // keys of a bin that a wave ranks directly
 constexpr int kMaxK = 16;          // candidates per token the interface allows
@@ -352,10 +351,12 @@ constexpr int kMaxPasses = 4;      // 32 key bits, 9 or 10 a pass
 template <int NT>
 struct FastShared {
     static constexpr int kWaves = NT / kWave;
-    static constexpr int kTokens = NT == 1024 ? kFastMaxT : 4 * NT;
-    static constexpr int kIds = NT == 1024 ? 49152 : kTokens * kMaxK;
+    // (256 and 512 threads: a token each at most)
+    static constexpr int kTokens = NT == kPlanThreads ? kFastMaxT : NT;
+    static constexpr int kKeys = NT == kPlanThreads ? kFastMaxPool / NT : kMaxK;   // pool entries of a thread
+    static constexpr int kIds = NT == kPlanThreads ? 49152 : kTokens * kMaxK;
     static constexpr int kBinsLog2 = NT == 1024 ? 10 : 9;
-    static constexpr int kWords = kFastMaxKeys * kWaves;   // of a bit map over the pool
+    static constexpr int kWords = kKeys * kWaves;   // of a bit map over the pool
     union {
         struct {   // selection
             // (behind the bins and the collected keys a unit per lane, for the entries that are
@@ -413,13 +414,14 @@ __device__ __forceinline__ void for_entries(int n_pool, F f, std::integer_sequen
 }
 template <int NT, typename F>
 __device__ __forceinline__ void for_entries(int n_pool, F f) {
-    static_assert(kFastMaxKeys % 4 == 0, "whole groups");
+    constexpr int kKeys = FastShared<NT>::kKeys;
+    static_assert(kKeys % 4 == 0, "whole groups");
     // (At most one entry a thread: not three idle ones beside it.  24 tokens with 3 entries each: selection
     // 6.0 us, 5.5 with it; 512 and 1024 threads have larger pools.)
     if (NT == 256 && n_pool <= NT)
         f(std::integral_constant<int, 0>{});
     else
-        for_entries<NT>(n_pool, f, std::make_integer_sequence<int, kFastMaxKeys / 4>{});
+        for_entries<NT>(n_pool, f, std::make_integer_sequence<int, kKeys / 4>{});
 }
 
 // The last pool entry kept: entries are kept iff their key is larger than `key`, or equal and
@@ -450,7 +452,7 @@ __device__ __forceinline__ int wave_find_rank(const uint32_t (&c)[N], uint32_t r
 }
 
 template <int NT>
-__device__ __forceinline__ Threshold find_threshold(FastShared<NT>& sh, const uint32_t (&key)[kFastMaxKeys],
+__device__ __forceinline__ Threshold find_threshold(FastShared<NT>& sh, const uint32_t (&key)[FastShared<NT>::kKeys],
                                                     int n_pool, uint32_t want) {
     using Sh = FastShared<NT>;
     constexpr int NW = NT / kWave, kBinsLane = (1 << Sh::kBinsLog2) / kWave;
@@ -609,7 +611,7 @@ __global__ __launch_bounds__(NT) void plan_fast_kernel(
     const bool search = SELECT && want > 0 && want < n_pool;
 
     // ---- all loads first: the pool's scores, then the candidate ids
-    float score[kFastMaxKeys];
+    float score[Sh::kKeys];
     if (search) {
         const uint32_t inv_p = 0xFFFFFFFFu / static_cast<uint32_t>(P) + 1u;   // p / P = p inv_p >> 32 (P = 1: 0)
         for_entries<NT>(n_pool, [&](auto q_const) {
@@ -643,7 +645,7 @@ __global__ __launch_bounds__(NT) void plan_fast_kernel(
         if (tid < n % 4) reinterpret_cast<uint8_t*>(sh.ids)[4 * quads + tid] = static_cast<uint8_t>(topk_ids[4 * quads + tid]);
     }
     if (search) {
-        uint32_t key[kFastMaxKeys];
+        uint32_t key[Sh::kKeys];
         for_entries<NT>(n_pool, [&](auto q_const) {
             constexpr int q = decltype(q_const)::value;
             key[q] = q * NT + tid < n_pool ? ordered_key(score[q]) : 0u;
@@ -1068,9 +1070,9 @@ static void launch_spread_select(const float* keys, const int32_t* topk_ids, int
 // of 64 tokens a wave much: 333 tokens x 8 candidates 8.6 us with 256 threads, 7.3 with 512, 8.1
 // with 1024; 500 x 4 8.6, 7.2, 8.5; 777 x 4 12.2 with 512, 9.8 with 1024; 64 x 6 5.7 with 256.
 inline int fast_path_threads(int T, int K, int Kb) {
-    const int64_t n_pool = static_cast<int64_t>(T) * (K - Kb);
-    for (int nt : {256, 512, 1024})
-        if (T <= (nt == 1024 ? kFastMaxT : nt) && n_pool <= static_cast<int64_t>(nt) * kFastMaxKeys) return nt;
+    for (int nt : {256, 512})
+        if (T <= nt) return nt;
+    if (T <= kFastMaxT && static_cast<int64_t>(T) * (K - Kb) <= kFastMaxPool) return kPlanThreads;
     return 0;
 }
 
@@ -1160,10 +1162,9 @@ hipError_t launch_select(const float* topk_s, int T, int K, int Kb, int64_t B,
 
 hipError_t launch_dispatch(const int32_t* topk_ids, const int32_t* keep_count, int T, int K,
                            int E, int64_t B, int32_t* expert_offsets, int32_t* row_token,
-                           int32_t* row_rank, int32_t* inv_row, uint64_t* words, int32_t* prefix,
+                           int32_t* row_rank, int32_t* inv_row, uint64_t* words,
                            int bm, int32_t* tile_info, bool alone, hipStream_t stream) {
-    const int nt = fast_path_threads(T, K, K);
-    if (nt == 0 || T >= kPlanSpreadDispatchTokens) {
+    if (T >= kPlanSpreadDispatchTokens) {
         const dim3 grid((T + kSpreadThreads - 1) / kSpreadThreads), block(kSpreadThreads);
         hipLaunchKernelGGL(spread_keep_kernel<false>, grid, block, 0, stream, nullptr, topk_ids, T, K,
                            0, B, nullptr, 0, nullptr, const_cast<int32_t*>(keep_count), words);
@@ -1171,7 +1172,8 @@ hipError_t launch_dispatch(const int32_t* topk_ids, const int32_t* keep_count, i
                            B, words, expert_offsets, row_token, row_rank, inv_row, bm, tile_info);
         return hipGetLastError();
     }
-    enqueue_fast<false, true>(nt, fast_path_groups(T, alone), stream, static_cast<const float*>(nullptr), topk_ids, T, K,
+    static_assert(kPlanSpreadDispatchTokens <= kFastMaxT, "one launch below");
+    enqueue_fast<false, true>(fast_path_threads(T, K, K), fast_path_groups(T, alone), stream, static_cast<const float*>(nullptr), topk_ids, T, K,
                               0, B, E, const_cast<int32_t*>(keep_count), expert_offsets, row_token, row_rank, inv_row,
                               bm, tile_info);
     return hipGetLastError();
