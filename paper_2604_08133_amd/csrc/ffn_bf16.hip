@@ -16,6 +16,7 @@
 // bf16 1 token 35.6, 33.5; from 2 tokens on the bf16 launches stand at 0.9 of the read rate
 // either way).  The A operand (<= 32 activation rows, L2 resident) is gathered per lane.
 // Partial accumulators meet in LDS in a fixed order, so results are bitwise reproducible.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.hpp"
@@ -180,19 +181,9 @@ void ffn_bf16_stream_kernel(StreamGroup g0, StreamGroup g1) {
         for (int u = 0; u < decltype(n_const)::value; ++u)
             if (s + u < steps) multiply(u);   // uniform
     };
-    // Short contractions take a shorter ring: loads that nothing uses cost a layer of 20-30 us up to
-    // 5 % (8-bit weights, 60 tokens, 32 experts of 512 x 384: 25.2 us with rings of 3, 6 and 12,
-    // now 24.1).
-    constexpr int kPart = !FP8 ? UNROLL / 2 : UNROLL == 12 ? 3 : 2;
-    if (steps <= kPart) {
-        start(std::integral_constant<int, kPart>{});
-        finish(std::integral_constant<int, kPart>{});
-    } else if (2 * kPart < UNROLL && steps <= 2 * kPart) {
-        start(std::integral_constant<int, 2 * kPart>{});
-        finish(std::integral_constant<int, 2 * kPart>{});
-    } else if (3 * kPart < UNROLL && steps <= 3 * kPart) {
-        start(std::integral_constant<int, 3 * kPart>{});
-        finish(std::integral_constant<int, 3 * kPart>{});
+    if (steps <= UNROLL / 2) {   // (loads that nothing would use cost a short contraction 2-3 %)
+        start(std::integral_constant<int, UNROLL / 2>{});
+        finish(std::integral_constant<int, UNROLL / 2>{});
     } else {
         // UNROLL steps in flight all the time: an entry is loaded again as soon as it is used.
         start(std::integral_constant<int, UNROLL>{});
@@ -209,8 +200,8 @@ void ffn_bf16_stream_kernel(StreamGroup g0, StreamGroup g1) {
         // bf16: the last pass loads only steps that exist (24 tokens, 32 experts of 640 x 896, ten and
         // fourteen steps a wave: layer 28.3 us without the condition, now 27.4; 60 tokens, 16 of
         // 1472 x 1088: 52.4, 50.1).  8-bit weights: all of an entry's loads, whether the step exists or not:
-        // the condition makes the compiler wait early (64 tokens, 64 experts of 2048 x 1408: 112.0 us,
-        // 110.8).
+        // the condition makes the compiler wait early (64 tokens, 64 experts of 2048 x 1408: 112.0 us
+        // with it, 110.5).
         // (The first pass by itself: its loads stand in another order, and in a loop the
         // compiler would wait for either.)
         constexpr int kWhole = FP8 ? UNROLL + 1 : 2 * UNROLL;
@@ -287,12 +278,22 @@ hipError_t launch_ffn_bf16_stream(bool swiglu, StreamGroup routed, StreamGroup s
     const dim3 grid(static_cast<unsigned>(total)), block(kStreamWaves * kWave);
 #define ALLOCMOE_STREAM_LAUNCH(...) \
     hipLaunchKernelGGL((ffn_bf16_stream_kernel<__VA_ARGS__>), grid, block, 0, stream, routed, shared)
-    if (swiglu && fp8)
+    // 8-bit weights, at most four steps a wave: a ring of that length (loads that nothing uses; 60 tokens, 32
+    // experts of 512 x 384: 24.7 us with the longer rings, 23.4; 40 tokens, 24 of 512 x 512: 24.6, 23.4).
+    // Shorter rings chosen inside the kernel instead make its long loop slower (64 tokens, 64 experts of
+    // 2048 x 1408: 112.2 us, 110.5).
+    const int depth = std::max(routed.A ? routed.Kd : 0, shared.A ? shared.Kd : 0);
+    constexpr int kShort = 4 * 32 * kStreamWaves;
+    if (swiglu && fp8 && depth <= kShort)
+        ALLOCMOE_STREAM_LAUNCH(true, true, 4, 2);
+    else if (swiglu && fp8)
         ALLOCMOE_STREAM_LAUNCH(true, true, 6, 2);
     else if (swiglu)
         ALLOCMOE_STREAM_LAUNCH(true, false, 8, 2);
     else if (pairs)
         ALLOCMOE_STREAM_LAUNCH(false, true, 6, 2);
+    else if (fp8 && depth <= kShort)
+        ALLOCMOE_STREAM_LAUNCH(false, true, 4, 1);
     else if (fp8)
         ALLOCMOE_STREAM_LAUNCH(false, true, 12, 1);
     else

@@ -38,11 +38,11 @@ def test_contractions_and_widths(T, d, E, I, Is, budget, fp8):
 
 
 # every length of the last pass and of the short rings: steps of a wave in the first and in the second
-# half (bf16: rings of 4 and 8; 8-bit: 2, 4, 6 and 3, 6, 9, 12, pairs of column blocks 2, 4, 6)
+# half (bf16: rings of 4 and 8; 8-bit: of 2 and 4 up to four steps, else 3 and 6, second half 6 and 12)
 @pytest.mark.parametrize("first,second,fp8", [
     (1, 16, False), (4, 9, False), (5, 10, False), (7, 11, False), (8, 12, False), (9, 13, False), (10, 14, False),
     (15, 3, False), (17, 24, False), (23, 25, False),
-    (1, 3, True), (2, 4, True), (3, 7, True), (4, 9, True), (5, 10, True), (6, 12, True), (7, 13, True), (9, 17, True),
+    (1, 3, True), (2, 4, True), (3, 1, True), (4, 2, True), (4, 4, True), (3, 7, True), (4, 9, True), (5, 10, True), (6, 12, True), (7, 13, True), (9, 17, True),
     (11, 23, True), (12, 25, True), (13, 6, True),
 ])
 def test_steps_of_a_wave(first, second, fp8):
