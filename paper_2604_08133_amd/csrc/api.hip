@@ -497,7 +497,7 @@ allocmoe_status forward_impl(const allocmoe_layer_desc* desc, const void* X,
     const bool routed_tiled = choice.routed_tiled, shared_tiled = choice.shared_tiled;
     const int bm = routed_tiled ? kTileRowsLarge : kTileRowsSmall;
     const int64_t max_tiles = max_tiles_for(desc, bm);
-    // half of the tiles that rows beyond the experts' first ones could at most need
+    // the experts' first tiles and half of those that further rows could at most need
     const int64_t likely_tiles = (std::min<int64_t>(E, B) + max_tiles) / 2;
     // The shared expert depends on nothing but X.  On a stream of its own (large layers where a
     // group uses the tile kernel, smaller ones that are mostly shared expert) its two GEMMs run
@@ -572,8 +572,8 @@ allocmoe_status forward_impl(const allocmoe_layer_desc* desc, const void* X,
     // steps 3-4: Alloc-T selection, dispatch, tile map.  Beside the shared expert's GEMMs
     // (which hide it, and whose workgroups hold every compute unit for tens of
     // microseconds at a time) one workgroup does it in one launch, enqueued before them;
-    // otherwise, from kPlanSpreadTokens tokens on, a sequence of short launches over many
-    // workgroups.
+    // otherwise, from kPlanSpreadDispatchTokens tokens on (or where one launch cannot hold the
+    // pool), a sequence of short launches over many workgroups.
     const bool spread_plan = plan_spread_bytes(T) > 0 && !overlap;
     ALLOCMOE_MARK(ALLOCMOE_STAGE_PLAN);
     const float* sel_keys = topk_s;   // Alloc-T selects on the scores themselves

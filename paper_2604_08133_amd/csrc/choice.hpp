@@ -20,11 +20,13 @@ struct FfnChoice {
 // expert for the routed group (B = 6E: 174 us a step streaming, 182 tiled; B = 9E: 200
 // against 193; B = 12E: 227 against 201).
 //
-// Smaller layers mostly run both groups on one kernel, in one launch per half: a fork and join
-// of two streams costs 10-20 us there and two launches behind each other 6-20 us (320 x
-// 192, 32 experts, 300 tokens: one launch 33 us streaming, 38 tiled, side stream 51;
-// 1088 x 704, 777 tokens: 117, 82, 83; 1472 x 1344, 64 experts, 300 and 1600 tokens: 174,
-// 161, 170 and 494, 209, 201).  Tiled where the experts see ten rows or more on average
+// Smaller layers mostly run both groups on one kernel, in one launch per half.  A fork and join
+// of two streams costs some of them 5-9 us and gains others as much; two launches behind each other
+// cost 6-20 us.  (Shared expert twice as wide as the experts, two pairs a token: 320 x 192, 32
+// experts, 300 tokens: one launch 26 us streaming, 30 tiled, side stream 37; 1088 x 704, 777 tokens:
+// 123, 77, 83; 1472 x 1344, 64 experts, 300 and 1600 tokens: 177, 144, 154 and 549, 204, 192.  36
+// drawn layers that run tiled in one launch here: 1.5 % longer on two streams in the mean, 13 %
+// shorter to 15 % longer.)  Tiled where the experts see ten rows or more on average
 // (8 rows, 64 experts of 1472 x 1344: 143 us streaming, 149 tiled; 11.5: 172, 163) and the
 // work covers the tile kernel's longer start and end.  With more than 32 rows an expert's
 // weights are streamed more than once, and the tile kernel wins earlier:
@@ -34,16 +36,17 @@ struct FfnChoice {
 // That average says nothing about a shared expert much wider than the routed ones, which then
 // decides by itself:
 //   * enough tokens and work of its own: tiled, however few rows the routed experts see
-//     (1024 x 256, 64 experts, shared 8192, 300 tokens, 75 pairs, 15 GFLOP: 156 us streaming, 99
-//     tiled; shared 4096, 7.7 GFLOP: 87, 71; shared 4096, 130 tokens, 3.3 GFLOP: 59, 69);
+//     (1024 x 256, 64 experts, shared 8192, 300 tokens, 300 pairs, 15 GFLOP: 133 us streaming, 89
+//     tiled; shared 4096, 7.7 GFLOP: 74, 62; shared 4096, 130 tokens, 3.3 GFLOP: 48, 58);
 //   * nearly all of the layer and long enough to hide selection and the routed experts: a stream
 //     of its own (2048 x 1408, 8 experts, shared 22528, 130 tokens: 220 us in one launch per half,
-//     206 beside; 1024 x 512, 32 experts, shared 16384, 300 tokens: 164, 153);
+//     189 beside; 1024 x 512, 32 experts, shared 16384, 300 tokens: 159, 152);
 //   * few tokens and most of the work: streaming (1152 x 1280, 7 experts, shared 2560, 128
 //     tokens: 53 us, tiled 57; 2048 x 1408, 8 experts, shared 45056, 40 tokens: 376, 541).
-// The same limits serve 8-bit weights.  Over 1522 layers (d 256 to 2048, 4 to 64 experts, shared
+// The same limits serve 8-bit weights.  They were chosen while the fork still stood behind the routing
+// kernel (and cost 10-20 us): over 1522 layers (d 256 to 2048, 4 to 64 experts, shared
 // expert 0 to 32 times the expert width, 24 to 8192 tokens, a tenth to all of T K pairs, both
-// formats) the choice is 0.7 % behind the best of the combinations in the mean; the worst cases,
+// formats) the choice was 0.7 % behind the best of the combinations in the mean; the worst cases,
 // 13-15 % behind, lie around 130 to 180 tokens, where all of them are close to each other.
 inline FfnChoice choose_ffn(int T, int d, int E, int I, int Is, int64_t B) {
     constexpr double kLargeWeights = 4e8, kLargeFlops = 4e10;

@@ -12,8 +12,8 @@
 // entry is filled again as soon as its products are issued, so that the same number of them is
 // in flight from the first to the last (batches of 8 steps, the next one issued behind the
 // products of the one before, and the column scales read at the end: 32 tokens, 96 pairs, 64
-// experts of 2048 x 1408 with 8-bit weights 98.3 us a layer, now 92.3; 64 tokens 125.9, 117.0;
-// bf16 1 token 35.6, 33.5; from 2 tokens on the bf16 launches stand at 0.9 of the read rate
+// experts of 2048 x 1408 with 8-bit weights 98.6 us a layer, now 92.0; 64 tokens 124.6, 110.5;
+// bf16 1 token 34.4, 32.3; from 2 tokens on the bf16 launches stand at 0.9 of the read rate
 // either way).  The A operand (<= 32 activation rows, L2 resident) is gathered per lane.
 // Partial accumulators meet in LDS in a fixed order, so results are bitwise reproducible.
 #include <algorithm>

@@ -33,7 +33,8 @@ constexpr int kXcds = 8;                // accelerator dies (one L2 each) of an 
 // there is room for both in one round, the dense tiles are as high as that takes: 777 tokens, 32
 // experts of 1088 x 704, shared expert of 1408: 99 dense workgroups of 96 rows and 186 routed
 // ones ended at 32 us (a second round of 31), 55 of 160 rows at 26; second half 125 and 155, 31
-// us, now 65 of 64 rows, 21; layer 83.7 us, 74.3.
+// us, now 65 of 64 rows, 21; layer 83.7 us, 74.3.  Where not even 256 rows leave room the tiles are
+// 256 rows all the same: of 1065 layers 40, 0.6 % behind the usual heights in the mean (-12 to +6 %).
 void lay_out_dense(StreamGroup& g, int col_tiles, int64_t beside) {
     constexpr int kUnits = 256, kMostWorkgroups = 128, kFewestWorkgroups = 32;
     const int64_t room = kUnits - beside;

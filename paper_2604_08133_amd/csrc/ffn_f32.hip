@@ -16,7 +16,7 @@
 // and which column is free to choose, so a lane takes 4 consecutive k of its row of A
 // (slot i of step k0: k0 + 4 (lane/16) + i) and 4 consecutive columns of those 4 rows of B
 // (column block j: n0 + 4 (lane%16) + j).  A layer of 500 tokens (d 1000, 16 experts of 700,
-// 1000 pairs, shared expert of 1400; 8.4 GFLOP) takes 140 us, 81 and 44 of them in the two
+// 1000 pairs, shared expert of 1400; 8.4 GFLOP) takes 143 us, 81 and 44 of them in the two
 // halves (one step ahead, with the odd depth's last step masked behind its loads: 173, 100 and
 // 54; a ring of 4: 81 and 52; 909 with a 32 x 64 tile on the vector ALUs and scalar loads through
 // LDS; relative error against 64 bits 5.4e-7 now and then).  Bound by the matrix pipe where two workgroups share a unit (a loop 30 us for two, 16

@@ -336,11 +336,12 @@ __device__ void tilemap_phase(PlanShared& sh, int E, int bm, int32_t* __restrict
 // transposed with a 6-stage butterfly of lane exchanges instead of 64 ballots.
 //
 // Bound by latency: a chain of loads, barriers and LDS round trips on one compute unit.  Phases
-// of 333 tokens with 8 candidates, us: loads 2.0, range 0.6, passes 0.8, last bin and counts 1.5,
-// words and prefixes 1.6, rows 1.2, together 7.6; with thread-contiguous slices of the pool
-// staged through LDS, three passes that ended at a single key and block-wide scans 4.4, 1.0,
-// 6.0, 2.6, 1.7, 2.0.  Whole kernel, then and now: 64 tokens x 6 14.7, 6.2; 777 x 4 21.0, 9.9;
-// 2048 x 4 42, 19; 4096 x 6 60, 33.
+// of 333 tokens with 8 candidates by time stamps inside the kernel, us: loads 2.0, range 0.6, passes
+// 0.8, last bin and counts 1.5, words and prefixes 1.6, rows 1.2, together 7.6; with
+// thread-contiguous slices of the pool staged through LDS, three passes that ended at a single
+// key and block-wide scans 4.4, 1.0, 6.0, 2.6, 1.7, 2.0.  Whole kernel by a trace of layers without
+// shared expert, then and now: 64 tokens x 6 14.2, 7.4; 333 x 8 17.3, 9.1; 500 x 4 16.2, 8.3; 777 x 4
+// 18.6, 11.1; 2048 x 4 24.8, 14.4; 4096 x 6 33.8 (five launches), 23.0.
 constexpr int kFastMaxT = 8192;
 constexpr int kFastMaxPool = 48 * kPlanThreads;
 constexpr int kCrowd = 8;          // share of the pool in one bin from which on its range is measured
@@ -794,8 +795,8 @@ __global__ __launch_bounds__(NT) void plan_fast_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// Many tokens (T >= kPlanSpreadTokens): the same selection and dispatch spread over
-// workgroups, as a fixed sequence of short launches, with no global atomics and no
+// Many tokens (selection alone from kPlanSpreadTokens on, with the dispatch from
+// kPlanSpreadDispatchTokens on: kernels.hpp): the same selection and dispatch spread over workgroups, as a fixed sequence of short launches, with no global atomics and no
 // waiting between workgroups (what a later launch needs from all workgroups of an
 // earlier one goes through memory).
 //
@@ -1067,8 +1068,8 @@ static void launch_spread_select(const float* keys, const int32_t* topk_ids, int
 
 // 0: large sizes (generic kernels), else the block size of the fast kernel.
 // A thread costs the barriers and the redundant searches little and the phases that walk batches
-// of 64 tokens a wave much: 333 tokens x 8 candidates 8.6 us with 256 threads, 7.3 with 512, 8.1
-// with 1024; 500 x 4 8.6, 7.2, 8.5; 777 x 4 12.2 with 512, 9.8 with 1024; 64 x 6 5.7 with 256.
+// of 64 tokens a wave much.  Kernel by trace: 64 tokens x 6 candidates 7.4 us with 256 threads, 7.4
+// with 512, 8.9 with 1024; 200 x 6 7.9, 7.7, 9.4; 333 x 8 9.0 with 512, 10.0 with 1024; 500 x 4 8.2, 9.9.
 inline int fast_path_threads(int T, int K, int Kb) {
     for (int nt : {256, 512})
         if (T <= nt) return nt;

@@ -18,7 +18,7 @@ namespace {
 
 // Each kernel is a chain of a few dependent trips to memory, so a workgroup has as many
 // waves as it can hold and a thread's loads go out in batches.  At 6000 tokens, 64 experts
-// and 6 candidates selection, dispatch and the analytics together went from 208 to 65 us (one
+// and 6 candidates selection, dispatch and the analytics together went from 208 to 61 us (one
 // thread per token or expert with serial loads, the ranks on 24 workgroups, before).
 constexpr int kStatThreads = 1024;
 constexpr int kStatWaves = kStatThreads / kWave;
