@@ -12,7 +12,7 @@
 // entry is filled again as soon as its products are issued, so that the same number of them is
 // in flight from the first to the last (batches of 8 steps, the next one issued behind the
 // products of the one before, and the column scales read at the end: 32 tokens, 96 pairs, 64
-// experts of 2048 x 1408 with 8-bit weights 98.6 us a layer, now 92.0; 64 tokens 124.6, 110.5;
+// experts of 2048 x 1408 with 8-bit weights 98.6 us a layer, now 92.0; 64 tokens 124.6, 109.7;
 // bf16 1 token 34.4, 32.3; from 2 tokens on the bf16 launches stand at 0.9 of the read rate
 // either way).  The A operand (<= 32 activation rows, L2 resident) is gathered per lane.
 // Partial accumulators meet in LDS in a fixed order, so results are bitwise reproducible.
@@ -56,11 +56,17 @@ __device__ __forceinline__ bf16x8 fp8x8_to_bf16x8(uint32_t lo, uint32_t hi) {
 // STREAMS: weight streams of a workgroup (SWIGLU: W1 and W3 of a column block; else one or two
 // neighbouring column blocks).
 //
-// bf16: as many workgroups to a unit as the registers allowed anyway, said outright: the compiler then
-// keeps the sums in vector registers (28 layers of 512 to 1024 columns 0.8 % shorter in the mean).
+// Workgroups to a unit, said outright where that makes the compiler keep the sums in vector
+// registers (`free`: left to the registers): bf16, as many as the registers allowed anyway, 28 layers
+// of 512 to 1024 columns 0.8 % shorter in the mean; 8-bit weights, two instead of three, 40 tokens, 24
+// experts of 1280 x 1024 37.5 us a layer, 35.9 with it; 64 tokens, 64 of 2048 x 1408 110.6, 109.7.
+constexpr int stream_workgroups(bool fp8, int unroll, int streams, int free) {
+    return fp8 ? (unroll == 6 ? 2 : free) : streams == 2 ? 2 : 4;
+}
+
 template <bool SWIGLU, bool FP8, int UNROLL, int STREAMS>
 __global__ __launch_bounds__(kStreamWaves* kWave)
-__attribute__((amdgpu_waves_per_eu(FP8 ? 1 : STREAMS == 2 ? 2 : 4, FP8 ? 8 : STREAMS == 2 ? 2 : 4)))
+__attribute__((amdgpu_waves_per_eu(stream_workgroups(FP8, UNROLL, STREAMS, 1), stream_workgroups(FP8, UNROLL, STREAMS, 8))))
 void ffn_bf16_stream_kernel(StreamGroup g0, StreamGroup g1) {
     static_assert(!SWIGLU || STREAMS == 2, "W1 and W3");
     constexpr int kBlocks = SWIGLU ? 1 : STREAMS;   // column blocks of a workgroup
@@ -201,7 +207,7 @@ void ffn_bf16_stream_kernel(StreamGroup g0, StreamGroup g1) {
         // fourteen steps a wave: layer 28.3 us without the condition, now 27.4; 60 tokens, 16 of
         // 1472 x 1088: 52.4, 50.1).  8-bit weights: all of an entry's loads, whether the step exists or not:
         // the condition makes the compiler wait early (64 tokens, 64 experts of 2048 x 1408: 112.0 us
-        // with it, 110.5).
+        // with it, 110.5 then).
         // (The first pass by itself: its loads stand in another order, and in a loop the
         // compiler would wait for either.)
         constexpr int kWhole = FP8 ? UNROLL + 1 : 2 * UNROLL;
