@@ -61,7 +61,7 @@ __device__ __forceinline__ bf16x8 fp8x8_to_bf16x8(uint32_t lo, uint32_t hi) {
 // of 512 to 1024 columns 0.8 % shorter in the mean; 8-bit weights, two instead of three, 40 tokens, 24
 // experts of 1280 x 1024 37.5 us a layer, 35.9 with it; 64 tokens, 64 of 2048 x 1408 110.6, 109.7.
 constexpr int stream_workgroups(bool fp8, int unroll, int streams, int free) {
-    return fp8 ? (unroll == 6 ? 2 : free) : streams == 2 ? 2 : 4;
+    return fp8 ? (unroll == 6 || (unroll == 8 && streams == 2) ? 2 : free) : streams == 2 ? 2 : 4;
 }
 
 template <bool SWIGLU, bool FP8, int UNROLL, int STREAMS>
@@ -284,22 +284,29 @@ hipError_t launch_ffn_bf16_stream(bool swiglu, StreamGroup routed, StreamGroup s
     const dim3 grid(static_cast<unsigned>(total)), block(kStreamWaves * kWave);
 #define ALLOCMOE_STREAM_LAUNCH(...) \
     hipLaunchKernelGGL((ffn_bf16_stream_kernel<__VA_ARGS__>), grid, block, 0, stream, routed, shared)
-    // 8-bit weights, at most four steps a wave: a ring of that length (loads that nothing uses; 60 tokens, 32
-    // experts of 512 x 384: 24.7 us with the longer rings, 23.4; 40 tokens, 24 of 512 x 512: 24.6, 23.4).
-    // Shorter rings chosen inside the kernel instead make its long loop slower (64 tokens, 64 experts of
-    // 2048 x 1408: 112.2 us, 110.5).
-    const int depth = std::max(routed.A ? routed.Kd : 0, shared.A ? shared.Kd : 0);
-    constexpr int kShort = 4 * 32 * kStreamWaves;
-    if (swiglu && fp8 && depth <= kShort)
+    // 8-bit weights, at most four or eight steps a wave: a ring of that length, so that every load is
+    // issued at once and at most three for nothing (up to four: 60 tokens, 32 experts of 512 x 384: 24.7 us
+    // with the longer rings, 23.4; 40 tokens, 24 of 512 x 512: 24.6, 23.4.  Up to eight: 24 tokens, 32
+    // experts of 1024 x 1024: 34.8, 32.6; 640 x 896: 28.6, 27.8; 40 tokens, 24 experts of 1024 x 512:
+    // 31.0, 29.5).  The first half's ring of six holds five and six steps as well.  Shorter rings chosen
+    // inside the kernel instead make its long loop slower (64 tokens, 64 experts of 2048 x 1408: 112.2
+    // us, 110.5).
+    const int steps = (std::max(routed.A ? routed.Kd : 0, shared.A ? shared.Kd : 0) + 32 * kStreamWaves - 1) /
+                      (32 * kStreamWaves);   // of a wave, 8-bit weights
+    if (swiglu && fp8 && steps <= 4)
         ALLOCMOE_STREAM_LAUNCH(true, true, 4, 2);
+    else if (swiglu && fp8 && steps > 6 && steps <= 8)
+        ALLOCMOE_STREAM_LAUNCH(true, true, 8, 2);
     else if (swiglu && fp8)
         ALLOCMOE_STREAM_LAUNCH(true, true, 6, 2);
     else if (swiglu)
         ALLOCMOE_STREAM_LAUNCH(true, false, 8, 2);
     else if (pairs)
         ALLOCMOE_STREAM_LAUNCH(false, true, 6, 2);
-    else if (fp8 && depth <= kShort)
+    else if (fp8 && steps <= 4)
         ALLOCMOE_STREAM_LAUNCH(false, true, 4, 1);
+    else if (fp8 && steps <= 8)
+        ALLOCMOE_STREAM_LAUNCH(false, true, 8, 1);
     else if (fp8)
         ALLOCMOE_STREAM_LAUNCH(false, true, 12, 1);
     else

@@ -13,8 +13,8 @@ from tests.test_gpu_layer import check_layer
 pytestmark = pytest.mark.gpu
 
 
-# a wave's steps: d / 64 and I / 64 (8 in flight), with 8-bit weights d / 128 and I / 128 (6; 12 in
-# the second half with one column block)
+# a wave's steps: d / 64 and I / 64 (8 in flight), with 8-bit weights d / 128 and I / 128 (6, or 8
+# where that is all of them; 12 in the second half with one column block)
 @pytest.mark.parametrize("T,d,E,I,Is,budget,fp8", [
     (5, 64, 8, 64, 64, 9, False),
     (40, 512, 3, 512, 576, 70, False),
@@ -38,12 +38,14 @@ def test_contractions_and_widths(T, d, E, I, Is, budget, fp8):
 
 
 # every length of the last pass and of the short rings: steps of a wave in the first and in the second
-# half (bf16: rings of 4 and 8; 8-bit: of 2 and 4 up to four steps, else 3 and 6, second half 6 and 12)
+# half (bf16: rings of 4 and 8; 8-bit: of 2 and 4 up to four steps, of 4 and 8 up to eight (first half: seven and
+# eight), else 3 and 6, second half 6 and 12)
 @pytest.mark.parametrize("first,second,fp8", [
     (1, 16, False), (4, 9, False), (5, 10, False), (7, 11, False), (8, 12, False), (9, 13, False), (10, 14, False),
     (15, 3, False), (17, 24, False), (23, 25, False),
     (1, 3, True), (2, 4, True), (3, 1, True), (4, 2, True), (4, 4, True), (3, 7, True), (4, 9, True), (5, 10, True), (6, 12, True), (7, 13, True), (9, 17, True),
     (11, 23, True), (12, 25, True), (13, 6, True),
+    (6, 5, True), (7, 8, True), (8, 3, True), (8, 6, True),
 ])
 def test_steps_of_a_wave(first, second, fp8):
     step = 128 if fp8 else 64
