@@ -458,35 +458,29 @@ __device__ __forceinline__ Threshold find_threshold(FastShared<NT>& sh, const ui
     using Sh = FastShared<NT>;
     constexpr int NW = NT / kWave, kBinsLane = (1 << Sh::kBinsLog2) / kWave;
     const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    uint32_t lo = 0xFFFFFFFFu, hi = 0u, r = want, count = n_pool;
-    // the block's smallest and largest key from the threads' own
-    auto range_of = [&](uint32_t first, uint32_t last) {
-        first = wave_min_u32(first);
-        last = wave_max_u32(last);
-        if (lane == 0) {
-            sh.red_lo[wave] = first;
-            sh.red_hi[wave] = last;
-        }
-        __syncthreads();
-        lo = wave_min_u32(sh.red_lo[lane % NW]);
-        hi = wave_max_u32(sh.red_hi[lane % NW]);
-    };
-    if (count > kCollect) {
-        // ---- range of the keys (entries past the end hold 0, below every key)
-        for_entries<NT>(n_pool, [&](auto q_const) {
-            constexpr int q = decltype(q_const)::value;
-            lo = min(lo, key[q] - 1u);
-            hi = max(hi, key[q]);
-        });
-        range_of(lo, hi);
-        lo += 1u;
-    } else {
-        lo = 1u;
-        hi = 0xFFFFFFFFu;
-        __syncthreads();   // (the cleared counters)
-    }
+    uint32_t lo = 1u, hi = 0xFFFFFFFFu, r = want, count = n_pool;
+    if (count <= kCollect) __syncthreads();   // (the cleared counters)
     // ---- narrowing passes: rank r counts from the top of [lo, hi]
+    bool measure = true;
     for (int pass = 0; count > kCollect && lo < hi; ++pass) {
+        if (measure) {   // the range that the keys in [lo, hi] have (entries past the end hold 0, below every key)
+            uint32_t first = 0xFFFFFFFFu, last = 0xFFFFFFFFu;   // (distances: keys outside wrap past all inside)
+            for_entries<NT>(n_pool, [&](auto q_const) {
+                constexpr int q = decltype(q_const)::value;
+                first = min(first, key[q] - lo);
+                last = min(last, hi - key[q]);
+            });
+            first = wave_min_u32(first);
+            last = wave_min_u32(last);
+            if (lane == 0) {
+                sh.red_lo[wave] = first;
+                sh.red_hi[wave] = last;
+            }
+            __syncthreads();
+            lo += wave_min_u32(sh.red_lo[lane % NW]);
+            hi -= wave_min_u32(sh.red_hi[lane % NW]);
+            if (lo == hi) break;
+        }
         const int bits = 32 - __builtin_clz(hi - lo);   // width <= 2^bits
         const int shift = max(0, bits - Sh::kBinsLog2);
         uint32_t* hist = sh.hist[pass];   // (bins from the top of the range)
@@ -514,18 +508,10 @@ __device__ __forceinline__ Threshold find_threshold(FastShared<NT>& sh, const ui
         // Much of the pool in one bin: many equal keys (padding tokens, scores of few levels), which
         // the counter takes one by one, 64 to an instruction, in every pass that is left.  Their
         // own range ends the search at once.  6000 tokens, 3 of 4 padding, 64 experts of 512 x 256,
-        // 6 candidates: layer 147 us without this, now 103 (the sequence of launches 105); no
-        // padding: 90.9, 91.2.
-        if (count > kCollect && count > static_cast<uint32_t>(n_pool) / kCrowd && lo < hi) {
-            uint32_t first = 0xFFFFFFFFu, last = 0u;
-            for_entries<NT>(n_pool, [&](auto q_const) {
-                constexpr int q = decltype(q_const)::value;
-                const bool in = key[q] >= lo && key[q] <= hi;
-                first = min(first, in ? key[q] : 0xFFFFFFFFu);
-                last = max(last, in ? key[q] : 0u);
-            });
-            range_of(first, last);
-        }
+        // 6 candidates: layer 140 us without this, now 102 (the sequence of launches 105); no
+        // padding: 87.7, 87.8.  (The measuring code stands in the loop once for both uses: with a copy
+        // here the kernel grew by 2 KB, 777 tokens of a layer with a shared expert 12.4 us, now 11.7.)
+        measure = count > static_cast<uint32_t>(n_pool) / kCrowd;
     }
     if (count <= kCollect) {
         // ---- rank the bin's keys directly
