@@ -409,20 +409,23 @@ __device__ __forceinline__ uint64_t wave_transpose64(uint64_t x) {
 // entries (the last four may lie past the end: key 0, not in any range).
 template <int NT, typename F, int... Q>
 __device__ __forceinline__ void for_entries(int n_pool, F f, std::integer_sequence<int, Q...>) {
-    (void)((4 * Q * NT < n_pool &&
-            (f(std::integral_constant<int, 4 * Q>{}), f(std::integral_constant<int, 4 * Q + 1>{}),
-             f(std::integral_constant<int, 4 * Q + 2>{}), f(std::integral_constant<int, 4 * Q + 3>{}), true)) && ...);
+    f(std::integral_constant<int, 0>{});
+    // (At most one entry a thread: not three idle ones beside it.  24 tokens with 3 entries each: selection
+    // 5.95 us, 5.5 with it; 200 with 6: 7.2, 7.3 (7.5 with the one entry's code beside the four's); 512
+    // and 1024 threads have larger pools.)
+    if (NT == 256 && n_pool <= NT) return;
+    f(std::integral_constant<int, 1>{});
+    f(std::integral_constant<int, 2>{});
+    f(std::integral_constant<int, 3>{});
+    (void)((4 * (Q + 1) * NT < n_pool &&
+            (f(std::integral_constant<int, 4 * Q + 4>{}), f(std::integral_constant<int, 4 * Q + 5>{}),
+             f(std::integral_constant<int, 4 * Q + 6>{}), f(std::integral_constant<int, 4 * Q + 7>{}), true)) && ...);
 }
 template <int NT, typename F>
 __device__ __forceinline__ void for_entries(int n_pool, F f) {
     constexpr int kKeys = FastShared<NT>::kKeys;
     static_assert(kKeys % 4 == 0, "whole groups");
-    // (At most one entry a thread: not three idle ones beside it.  24 tokens with 3 entries each: selection
-    // 6.0 us, 5.5 with it; 512 and 1024 threads have larger pools.)
-    if (NT == 256 && n_pool <= NT)
-        f(std::integral_constant<int, 0>{});
-    else
-        for_entries<NT>(n_pool, f, std::make_integer_sequence<int, kKeys / 4>{});
+    for_entries<NT>(n_pool, f, std::make_integer_sequence<int, kKeys / 4 - 1>{});
 }
 
 // The last pool entry kept: entries are kept iff their key is larger than `key`, or equal and
