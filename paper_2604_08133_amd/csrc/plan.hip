@@ -515,35 +515,34 @@ __device__ __forceinline__ Threshold find_threshold(FastShared<NT>& sh, const ui
     return {lo, static_cast<uint32_t>(word * kWave + __builtin_ctzll(__ballot(hit) | (1ull << (kWave - 1))))};
 }
 
-// Whether two of the first K bytes of ids, mod 64, are equal.  Four bytes at a time: byte differences, at most 127, plus 127
-// have their top bit set unless they are 0 (24 instructions for eight bytes; a mask of 64 bits takes twice as many).
-template <int NJ>
-__device__ __forceinline__ bool repeats_id(const uint32_t (&ids)[NJ / 4], int K) {
-    constexpr int NW = NJ / 4;
-    uint32_t x[NW], rot[NW][4], all = ~0u;
+// Whether two of the first n of eight bytes, mod 64, are equal.  Four bytes at a time: byte differences, at most 127, plus
+// 127 have their top bit set unless they are 0 (24 instructions; a mask of 64 bits takes twice as many).
+__device__ __forceinline__ bool repeats_id(const uint32_t (&ids)[2], int n) {
+    uint32_t x[2], rot[2][4], all = ~0u;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        // bytes from K on: 64 + position, which equals no other byte
-        const int held = min(max(K - 4 * w, 0), 4);
+    for (int w = 0; w < 2; ++w) {
+        // bytes from n on: 64 + position, which equals no other byte
+        const int held = min(max(n - 4 * w, 0), 4);
         const uint32_t mask = held == 4 ? ~0u : (1u << (8 * held)) - 1;
         x[w] = (ids[w] & (mask & 0x3f3f3f3fu)) | (~mask & (0x43424140u + 0x04040404u * w));
 #pragma unroll
         for (int r = 0; r < 4; ++r) rot[w][r] = __builtin_amdgcn_alignbyte(x[w], x[w], r);
 #pragma unroll
         for (int r = 1; r < 3; ++r) all &= (x[w] ^ rot[w][r]) + 0x7f7f7f7fu;
-#pragma unroll
-        for (int v = 0; v < w; ++v)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) all &= (x[v] ^ rot[w][r]) + 0x7f7f7f7fu;
     }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) all &= (x[0] ^ rot[1][r]) + 0x7f7f7f7fu;
     return (~all & 0x80808080u) != 0;
 }
 
 // SPLIT (several workgroups of 1024 threads, fast_path_runs): a workgroup owns a run of batches and forms words only
 // for those; of the other batches it needs how many pairs of every expert lie before and behind its own, which LDS
-// counters of its waves tell (integers: any order).  Bound by vector instructions: with every workgroup transposing all
-// batches the dispatch of 6000 x 6 candidates by 64 experts took 14.2 us (94 transposes in each of 16 workgroups), with
-// runs 12.3; without the test for repeated ids 11.6.
+// counters of its waves tell (integers: any order).  A wave has kCopies of them and its lanes take the copies in turn:
+// additions of one instruction to one address come one behind the other, and a popular expert is in most tokens.
+// Bound by vector instructions: with every workgroup transposing all
+// batches the dispatch of 6000 x 6 candidates by 64 experts takes 13.1 us (94 transposes in each of 16 workgroups), with
+// runs 11.0, whatever the skew (with one counter an expert 11.0 with even experts, 14.4 with one in every
+// token, 16.2 with popularities of rank^-2.2).
 template <bool SELECT, bool DISPATCH, int NT, bool SPLIT>
 __global__ __launch_bounds__(NT) void plan_fast_kernel(
     const float* topk_s, const int32_t* topk_ids, int T, int K, int Kb, int64_t B, int E,
@@ -556,9 +555,10 @@ __global__ __launch_bounds__(NT) void plan_fast_kernel(
     const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     // Launched as several workgroups (only where nothing else wants the compute units),
     // every workgroup runs the selection and the counting phases redundantly, on its own
-    // unit and in its own LDS, with identical results and no exchange between them, and
-    // then writes its share of the placement, the one phase that is bound by the number of
-    // scattered stores a single compute unit can issue; workgroup 0 writes the rest.
+    // unit and in its own LDS, with identical results and no exchange between them (SPLIT: the
+    // words of its own run of batches only), and then writes its share of the placement, the one phase that
+    // is bound by the number of scattered stores a single compute unit can issue (SPLIT: and of the keep
+    // counts); workgroup 0 writes the rest.
     const int n_groups = gridDim.x, group = blockIdx.x;
     const bool writer = group == 0;
     const int P = K - Kb, n_pool = SELECT ? T * P : 0;
@@ -646,15 +646,19 @@ __global__ __launch_bounds__(NT) void plan_fast_kernel(
         }
     };
     const int n_batch = (T + kWave - 1) / kWave;
-    // SPLIT: the batches of this workgroup and, behind their words, the waves' counters of pairs before and behind them
-    constexpr int kOwn = kFastMaxT / kWave / kPlanMaxGroups;
+    // SPLIT: the batches of this workgroup and, behind their words, the waves' counters of pairs before (low half) and
+    // behind them (high half); an expert has at most kFastMaxT pairs
+    constexpr int kOwn = kFastMaxT / kWave / kPlanMaxGroups, kCopies = 8;
+    static_assert(kFastMaxT < 1 << 16, "halves");
     const int per_group = SPLIT ? (n_batch + n_groups - 1) / n_groups : n_batch;
     const int own0 = SPLIT ? min(n_batch, group * per_group) : 0, own1 = SPLIT ? min(n_batch, own0 + per_group) : n_batch;
-    auto counters = reinterpret_cast<uint32_t(*)[2][kWave]>(sh.words + kOwn * kWave);   // [wave][behind][expert]
+    // [wave][copy][expert], an expert's copies in different banks; copy 0 in the end the sum of all
+    typedef uint32_t Counters[kCopies][kWave + kWave / kCopies];
+    Counters& counters = reinterpret_cast<Counters*>(sh.words + kOwn * kWave)[wave];
     if constexpr (SPLIT) {
-        static_assert(NT == kPlanThreads && kOwn * kWave + NW * kWave <= Sh::kTokens && kOwn <= NW, "room");
-        counters[wave][0][lane] = 0;
-        counters[wave][1][lane] = 0;
+        static_assert(NT == kPlanThreads && kOwn * kWave * 8 + NW * sizeof(Counters) <= sizeof(sh.words) && kOwn <= NW, "room");
+#pragma unroll
+        for (int c = 0; c < kCopies; ++c) counters[c][lane] = 0;
     }
     // ---- A: ballot words by bit-matrix transpose (lane e ends up with expert e's word)
     auto make_words = [&](auto nj_const) {
@@ -664,24 +668,27 @@ __global__ __launch_bounds__(NT) void plan_fast_kernel(
             const int kt = t < T ? count_of(tt) : 0;
             uint32_t ids[NJ / 4];
             load_ids(tt, ids);
-            if (SPLIT && (b < own0 || b >= own1)) {   // uniform
-                auto expert = [&](int j) { return (ids[j / 4] >> (8 * (j % 4))) & (kWave - 1); };
-                uint32_t* counter = counters[wave][b < own0 ? 0 : 1];
-                if (__ballot(repeats_id<NJ>(ids, K)) == 0) {
+            if constexpr (SPLIT) {
+                if (b < own0 || b >= own1) {   // uniform
+                    auto expert = [&](int j) { return (ids[j / 4] >> (8 * (j % 4))) & (kWave - 1); };
+                    uint32_t* counter = counters[lane % kCopies];
+                    const uint32_t one = b < own0 ? 1u : 1u << 16;
+                    if (__ballot(repeats_id(ids, kt)) == 0) {
 #pragma unroll
-                    for (int j = 0; j < NJ; ++j)
-                        if (j < kt) atomicAdd(&counter[expert(j)], 1u);
-                } else {   // an id that a token repeats counts once, as its bit in a word does
-                    uint64_t seen = 0;
-                    for (int j = 0; j < kt; ++j) {
-                        uint32_t e = 0;
+                        for (int j = 0; j < NJ; ++j)
+                            if (j < kt) atomicAdd(&counter[expert(j)], one);
+                    } else {   // an id that a token repeats counts once, as its bit in a word does
+                        uint64_t seen = 0;
+                        for (int j = 0; j < kt; ++j) {
+                            uint32_t e = 0;
 #pragma unroll
-                        for (int i = 0; i < NJ; ++i) e = i == j ? expert(i) : e;
-                        if (!(seen >> e & 1)) atomicAdd(&counter[e], 1u);
-                        seen |= uint64_t{1} << e;
+                            for (int i = 0; i < NJ; ++i) e = i == j ? expert(i) : e;
+                            if (!(seen >> e & 1)) atomicAdd(&counter[e], one);
+                            seen |= uint64_t{1} << e;
+                        }
                     }
+                    continue;
                 }
-                continue;
             }
             uint64_t mine = 0;
 #pragma unroll
@@ -694,19 +701,27 @@ __global__ __launch_bounds__(NT) void plan_fast_kernel(
             sh.words[(b - own0) * kWave + lane] = wave_transpose64(mine);
         }
     };
-    if (K <= 8)
+    if constexpr (SPLIT)
+        make_words(std::integral_constant<int, 8>{});
+    else if (K <= 8)
         make_words(std::integral_constant<int, 8>{});
     else
         make_words(std::integral_constant<int, 16>{});
+    if constexpr (SPLIT) {   // (the wave's own counters)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        uint32_t sum = 0;
+#pragma unroll
+        for (int c = 0; c < kCopies; ++c) sum += counters[c][lane];
+        counters[0][lane] = sum;
+    }
     __syncthreads();
     // ---- B: per expert, exclusive prefix over batches; offsets over experts
     if constexpr (SPLIT) {
-        int before = 0, total = 0, own[kOwn];
+        int own[kOwn];
+        uint32_t sum = 0;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            before += counters[w][0][lane];
-            total += counters[w][1][lane];
-        }
+        for (int w = 0; w < NW; ++w) sum += reinterpret_cast<Counters*>(sh.words + kOwn * kWave)[w][0][lane];
+        int before = static_cast<int>(sum & 0xFFFFu), total = static_cast<int>(sum >> 16);
 #pragma unroll
         for (int i = 0; i < kOwn; ++i) own[i] = i < own1 - own0 ? __popcll(sh.words[i * kWave + lane]) : 0;
         total += before;
@@ -794,7 +809,9 @@ __global__ __launch_bounds__(NT) void plan_fast_kernel(
             }
         }
     };
-    if (K <= 8)
+    if constexpr (SPLIT)
+        place(std::integral_constant<int, 8>{});
+    else if (K <= 8)
         place(std::integral_constant<int, 8>{});
     else
         place(std::integral_constant<int, 16>{});
@@ -1133,8 +1150,12 @@ inline int fast_path_groups(int T, bool alone) {
 
 // Whether those workgroups own runs of batches (SPLIT).  As long as a wave has one batch, or few have a second, forming
 // all words costs less than counting the other batches: layer's plan kernel of 64 experts, K = 6, all words and runs:
-// 600 tokens 10.7 us, 11.0; 1000: 12.5, 12.8; 1300: 12.6, 12.9; 2000: 15.3, 14.7; 2000 of 16 experts, K = 2: 8.1, 7.3.
-inline bool fast_path_runs(int T, int nt, int groups) { return nt == kPlanThreads && groups > 1 && T > 3 * kPlanThreads / 2; }
+// 600 tokens 10.7 us, 11.0; 1000: 12.5, 12.8; 1300: 12.6, 12.9; 2000: 15.3, 14.7.  A pair costs an addition there
+// and little in a word, so with many candidates a token words are the shorter way: dispatch of 2500 tokens by 64
+// experts, even and skewed: K = 6 7.7 us, 6.9; 8: 7.8, 7.1; 12: 9.6, 9.9; 16 (of 16): 10.0, 10.5.
+inline bool fast_path_runs(int T, int K, int nt, int groups) {
+    return nt == kPlanThreads && groups > 1 && T > 3 * kPlanThreads / 2 && K <= 8;
+}
 
 template <bool SELECT, bool DISPATCH, typename... Args>
 void enqueue_fast(int nt, int groups, bool runs, hipStream_t stream, Args... args) {
@@ -1199,7 +1220,7 @@ hipError_t launch_dispatch(const int32_t* topk_ids, const int32_t* keep_count, i
     }
     static_assert(kPlanSpreadDispatchTokens <= kFastMaxT, "one launch below");
     const int nt = fast_path_threads(T, K, K), groups = fast_path_groups(T, alone);
-    enqueue_fast<false, true>(nt, groups, fast_path_runs(T, nt, groups), stream, static_cast<const float*>(nullptr), topk_ids, T, K,
+    enqueue_fast<false, true>(nt, groups, fast_path_runs(T, K, nt, groups), stream, static_cast<const float*>(nullptr), topk_ids, T, K,
                               0, B, E, const_cast<int32_t*>(keep_count), expert_offsets, row_token, row_rank, inv_row,
                               bm, tile_info);
     return hipGetLastError();
@@ -1220,7 +1241,7 @@ hipError_t launch_plan(const float* topk_s, const int32_t* topk_ids, int T, int 
     }
     const int groups = fast_path_groups(T, alone);
     if (nt != 0)
-        enqueue_fast<true, true>(nt, groups, fast_path_runs(T, nt, groups), stream, topk_s, topk_ids, T, K, Kb, B, E, keep_count,
+        enqueue_fast<true, true>(nt, groups, fast_path_runs(T, K, nt, groups), stream, topk_s, topk_ids, T, K, Kb, B, E, keep_count,
                                  expert_offsets, row_token, row_rank, inv_row, bm, tile_info);
     else
         hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kPlanThreads), 0, stream, topk_s, topk_ids,

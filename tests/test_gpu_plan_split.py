@@ -1,6 +1,7 @@
 """Dispatch on several workgroups of one launch: above 1536 tokens each forms words for a run of 64-token batches and counts
-the pairs of the others, so runs that end inside a batch, workgroups without one, tokens that keep nothing, one expert that takes all,
-and an id that a token repeats (one row, as in a word).  Whole numbers, so bit for bit."""
+the pairs of the others (up to 8 candidates a token), so runs that end inside a batch, workgroups without one, tokens that keep nothing,
+one expert that takes all or is in every token, an id that a token repeats (one row, as in a word), and one that fills
+the places behind the kept candidates.  Whole numbers, so bit for bit."""
 import pytest
 import torch
 
@@ -42,7 +43,8 @@ def in_order(ids, cnt, E):
 
 
 @pytest.mark.parametrize("T", [513, 1025, 1536, 1537, 1600, 1601, 2047, 2049, 3000, 6143])
-@pytest.mark.parametrize("E,K,kind", [(64, 8, "counts"), (64, 16, "counts"), (33, 5, "sparse"), (5, 3, "one"), (9, 7, "repeats")])
+@pytest.mark.parametrize("E,K,kind", [(64, 8, "counts"), (64, 16, "counts"), (33, 5, "sparse"), (5, 3, "one"), (9, 7, "repeats"),
+                                      (64, 8, "hot"), (33, 6, "filled"), (64, 9, "hot")])
 def test_runs_of_batches(T, E, K, kind):
     gen = torch.Generator().manual_seed(T * 131 + E)
     if kind == "repeats":
@@ -52,6 +54,13 @@ def test_runs_of_batches(T, E, K, kind):
     cnt = torch.randint(0, K + 1, (T,), generator=gen, dtype=torch.int32)
     if kind == "sparse":
         cnt[torch.rand(T, generator=gen) < 0.97] = 0
+    if kind == "hot":   # expert 3 is every token's first
+        at = (ids == 3).int().argmax(1)
+        ids[torch.arange(T), at] = ids[:, 0]
+        ids[:, 0] = 3
+        cnt.clamp_(min=1)
+    if kind == "filled":
+        ids = torch.where(torch.arange(K)[None, :] < cnt[:, None], ids, torch.full_like(ids, E - 1))
     if kind == "one":
         ids[:, 0] = 2
         ids[:, 1:] = torch.tensor([0, 4], dtype=torch.int32)
