@@ -831,18 +831,20 @@ __global__ __launch_bounds__(NT) void plan_fast_kernel(
 // does this redundantly, workgroup 0 records digit and remaining rank for the launches
 // after it).  After three passes the key v* and the number R of keys equal to v* that
 // are kept are known.  keep: thread = token; ties at v* are split in (token, rank) order:
-// a workgroup counts the equal keys of all earlier tokens itself (only when a tie is
-// split).  The same launch forms the ballot words of its batches of 64 tokens.
+// a workgroup takes the equal keys of earlier tokens from the last pass's partial histograms and
+// counts those of the group that it begins in itself (only when a tie is split).  The same launch forms the ballot words of its batches of 64 tokens.
 // place: a workgroup owns 16 batches; per expert (lane) the counts of all batches and of
 // the batches before its own come from popcounts of the ballot words; then the rows.
 constexpr int kSpreadThreads = 1024;   // (kPlanSpreadTokens: kernels.hpp)
 constexpr int kSpreadMaxGroups = 16;
 constexpr int kSpreadBins = 2048;
 
-// Tokens of a group's histogram: whole workgroups of the keep kernel, so that up to 16384 tokens a
-// workgroup there finds the equal keys of all earlier ones in the last pass's partial histograms.
+// Tokens of a group's histogram.  Up to 16384 those of a workgroup of the keep kernel, which then finds the equal keys
+// of all earlier ones in the last pass's partial histograms.  Beyond, equal shares: in whole workgroups the largest
+// share is up to twice the mean (selection of 16385 tokens, 8 candidates, with the loads of that time 49.1 us, equal
+// shares 39.5; 33000 63.5, 53.9).
 __host__ __device__ inline int spread_group_tokens(int T, int G) {
-    return ((T + kSpreadThreads - 1) / kSpreadThreads + G - 1) / G * kSpreadThreads;
+    return T <= kSpreadMaxGroups * kSpreadThreads ? kSpreadThreads : (T + G - 1) / G;
 }
 
 struct SpreadState {
@@ -898,17 +900,32 @@ __device__ __forceinline__ void spread_find_bin(const uint32_t* __restrict__ par
     __syncthreads();
 }
 
-// f(key) for token t's pool entries, four loads in flight
+// f(key) for token t's pool entries, eight in flight: two 16-byte loads (of any 4-byte boundary; the last of a row ends
+// with it), since single loads of lanes that lie K apart ask for the same lines again and again while they
+// are on their way (selection of 4096 tokens, 8 candidates, 22.6 us: one load behind the other 30.9, four or eight at once 32.4)
 template <typename F>
 __device__ __forceinline__ void for_keys(const float* __restrict__ keys, int t, int K, int Kb, F f) {
+    typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
     const float* row = keys + static_cast<size_t>(t) * K;
-    for (int j0 = Kb; j0 < K; j0 += 4) {
-        float v[4];
+    if (K - Kb < 4) {   // uniform, as all conditions here
+        float v[3];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = row[min(j0 + i, K - 1)];
+        for (int i = 0; i < 3; ++i) v[i] = row[min(Kb + i, K - 1)];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (j0 + i < K) f(ordered_key(v[i]));
+        for (int i = 0; i < 3; ++i)
+            if (Kb + i < K) f(ordered_key(v[i]));
+        return;
+    }
+    for (int j0 = Kb; j0 < K; j0 += 8) {
+        const int at[2] = {min(j0, K - 4), min(j0 + 4, K - 4)};
+        f32x4_any v[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) v[q] = *reinterpret_cast<const f32x4_any*>(row + at[q]);
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (at[q] + i >= j0 + 4 * q) f(ordered_key(v[q][i]));
     }
 }
 
