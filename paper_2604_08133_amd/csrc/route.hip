@@ -17,7 +17,7 @@
 namespace allocmoe {
 
 constexpr int kRouteTok = 4;    // tokens per workgroup
-constexpr int kRouteBatch = 16;   // rows of the gate matrix under one condition
+constexpr int kRouteBatch = 16;   // rows of the gate matrix loaded together
 
 // Where the selection is not on the scores themselves (include/allocmoe.h, allocmoe_selector): the
 // candidates' keys [T,K], fp32, formed while the candidates are found (as a launch of their own behind it: 1
@@ -143,22 +143,27 @@ __global__ __launch_bounds__(WAVES* kWave) void route_kernel(
         };
         const int n = min(kWave, d - h0);
         const TIn* wp = Wg + static_cast<size_t>(h0) * E + (lane_is_expert ? lane : 0);
-        // All rows of the chunk in flight at once (past the last one: zeros, as the token's values there).  One 16 behind
-        // the other, and the rows past the last whole 16 one by one: layer of 500 tokens, d 1000, 112 us, 110.5 now;
-        // 17, d 1132: 62.5, 58.8; 2000, d 2048: 110.4, 99.4; routing of 66000, d 1024: 453, 408; d 200: 122, 114 (133
-        // with loads for all 64 rows of the last chunk as well).
-        float wv[kWave];
+        // The next 16 rows are on their way while 16 are used (past the last one: its own again, times the token's zeros
+        // there).  That fits 64 registers: eight waves a SIMD.  One 16 behind the other with the rows past the last whole
+        // 16 one by one (before), all 64 of a chunk at once (98 registers), this; routing and selection, us:
+        // fp32, 500 tokens, d 1132 19.4, 18.3, 18.1; 8192, d 1132 84.4, 103.6, 78.9; 30000, d 2048 401, 435, 372; 66000, d
+        // 200 128, 123, 123; bf16, 500, d 2048 26.3, 23.3, 21.5; 30000, d 1024 228, 305, 222.
+        float cur[kRouteBatch], ahead[kRouteBatch];
+        auto load = [&](float (&rows)[kRouteBatch], int i) {
+#pragma unroll
+            for (int u = 0; u < kRouteBatch; ++u) rows[u] = load_f32(wp, static_cast<size_t>(min(i + u, n - 1)) * E);
+        };
+        load(cur, 0);
 #pragma unroll
         for (int i = 0; i < kWave; i += kRouteBatch) {
-            if (i >= n) break;
+            if (i >= n) break;   // uniform
+            if (i + kRouteBatch < kWave) load(ahead, i + kRouteBatch);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int u = i; u < i + kRouteBatch; ++u) wv[u] = load_f32(wp, static_cast<size_t>(min(u, n - 1)) * E);
-        }
+            for (int u = 0; u < kRouteBatch; ++u) step(i + u, i + u < n ? cur[u] : 0.f);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < kWave; i += kRouteBatch) {
-            if (i >= n) break;
-#pragma unroll
-            for (int u = i; u < i + kRouteBatch; ++u) step(u, u < n ? wv[u] : 0.f);
+            for (int u = 0; u < kRouteBatch; ++u) cur[u] = ahead[u];
         }
     }
 #pragma unroll

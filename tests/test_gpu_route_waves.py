@@ -49,6 +49,18 @@ def test_both_wave_counts(T, d, dtype):
     check(X, Wg, 5, rows)
 
 
+@pytest.mark.parametrize("d", [2, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 65, 80, 81, 1000, 1132])
+def test_rows_of_a_chunk(d):
+    """Gate rows come 16 at a time, the next ones ahead: chunks of 64 that end before, at and behind each step, and
+    experts whose rows lie next to memory that holds no number."""
+    T, E = 6, 61
+    g = torch.Generator(device="cuda").manual_seed(d)
+    X = torch.randn((T, d), generator=g, device="cuda")
+    room = torch.full((d + 128, E), float("nan"), device="cuda")
+    room[64:64 + d] = torch.randn((d, E), generator=g, device="cuda") / d ** 0.5
+    check(X, room[64:64 + d], 5, torch.arange(T, device="cuda"))
+
+
 def test_more_tokens_than_sixteen_waves_can_launch():
     T, d, E = 2 ** 24 + 5, 257, 3
     torch.cuda.empty_cache()
