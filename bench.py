@@ -28,6 +28,12 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16, published
 METRIC = "budgeted MoE-layer tokens/s at 0.5x budget"
 
 
+def first_half_beside_route(T, d, Is, budget, fp8):
+    """Decode shapes: whether the shared expert's first half is part of the routing launch, not of the
+    experts' (the library's rule)."""
+    return T <= 16 and Is > 0 and budget > 0 and Is // 32 < 256 and d >= (512 if fp8 else 256)
+
+
 def parse_args():
     p = argparse.ArgumentParser()
     p.add_argument("--gpus", type=int, default=1)
@@ -300,13 +306,12 @@ class Bench:
         targs = "<true, true>" if fp8 else "<true, false>"
         if not tiled_routed and not tiled_shared:
             # decode shapes: one launch per half holds the routed rows and the shared expert;
-            # the dominant kernel is the first half (W1, W3: two thirds of the weight bytes).  (Up to 16
-            # tokens the shared expert's first half is part of the routing launch, unless it is very wide.)
-            with_shared = Is > 0 and (T > 16 or Is >= 8192)
+            # the dominant kernel is the first half (W1, W3: two thirds of the weight bytes)
+            n_shared = sum(Is > 0 and not first_half_beside_route(T, d, Is, dc.budget, fp8) for dc in self.descs)
             nbytes = (n_active * 2 * d * I * wb + pairs * (d * 2 + I * 2)
-                      + nL * (2 * d * Is * wb + T * (d * 2 + Is * 2) if with_shared else 0))
+                      + n_shared * (2 * d * Is * wb + T * (d * 2 + Is * 2)))
             if fp8:
-                nbytes += n_active * 2 * I * 4 + (nL * 2 * Is * 4 if with_shared else 0)
+                nbytes += n_active * 2 * I * 4 + n_shared * 2 * Is * 4
             ms = stages["ffn1"]
             roof = {"bound": "hbm", "achieved": nbytes / (ms * 1e-3) / 1e9, "peak": HBM_PEAK_GBS,
                     "unit": "GB/s", "kernel": "ffn_bf16_stream_kernel" + targs,

@@ -499,8 +499,8 @@ allocmoe_status forward_impl(const allocmoe_layer_desc* desc, const void* X,
     // beside selection and the routed experts' GEMMs, and the streams meet again before the
     // combine: the side stream starts beside or after the routing kernel (below) and the
     // single-workgroup plan kernel is enqueued first.  Decode shapes (both groups on the weight-streaming kernel) keep one
-    // stream and one launch per half for both groups: there the two event waits of a
-    // fork and join cost more than the overlap gains.
+    // stream and one launch per half for both groups (up to 16 tokens the shared expert's first half is in the
+    // routing launch): there the two event waits of a fork and join cost more than the overlap gains.
     const bool overlap = choice.own_stream;
     struct { hipStream_t stream; hipEvent_t fork, join; } side_{}, *side = &side_;
     StreamGroup s1, s2;   // the shared expert's two GEMMs
@@ -556,7 +556,7 @@ allocmoe_status forward_impl(const allocmoe_layer_desc* desc, const void* X,
     // Few tokens: the one workgroup that routes them selects and dispatches as well, and where both groups are on the
     // streaming kernel the shared expert's first half runs beside it.
     const bool route_few = bf16 && !overlap && T <= kRoutePlanTokens;
-    const bool beside = route_few && Is > 0 && B > 0 && !routed_tiled && !shared_tiled && streams_beside_route(s1);
+    const bool beside = route_few && first_half_beside_route(choice, T, d, Is, B, fp8);
     ALLOCMOE_MARK(ALLOCMOE_STAGE_ROUTE);
     if (route_few) {
         ALLOCMOE_TRY(launch_route_few(X, packed_gate(desc, w->packed), w->gate_bias, desc->shared_gate != 0, T, d, E,

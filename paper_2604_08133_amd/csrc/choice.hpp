@@ -77,6 +77,17 @@ inline FfnChoice choose_ffn(int T, int d, int E, int I, int Is, int64_t B) {
     return {tiled, tiled, false};
 }
 
+// Tokens (one fragment of the gate GEMM's matrix instruction) that one workgroup routes, selects and dispatches
+// (route.hip), and whether the shared expert's first half runs beside it in the same launch: on the
+// streaming kernel, one round of workgroups with the routing one (32 columns each), and a step of the
+// contraction, 16 or with 8-bit weights 32 deep, for each of a workgroup's 16 waves.
+constexpr int kRoutePlanTokens = 16;
+inline bool first_half_beside_route(const FfnChoice& c, int T, int d, int Is, int64_t B, bool fp8) {
+    constexpr int kUnits = 256, kWaves = 16;
+    return T <= kRoutePlanTokens && !c.own_stream && !c.routed_tiled && !c.shared_tiled && Is > 0 && B > 0 &&
+           Is / 32 < kUnits && d >= kWaves * (fp8 ? 32 : 16);
+}
+
 // Most workgroups of a dense group on the tile kernel below which its tiles stay lower than 256 rows
 // (ffn_bf16_t256.hip), for the second half of a shared expert on its own stream.
 //

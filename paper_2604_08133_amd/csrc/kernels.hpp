@@ -118,11 +118,8 @@ struct StreamGroup {
     // column (stream: W1, W3 for the SwiGLU half; one for the plain half)
     const float* scale = nullptr;
 };
-// Routing, selection, dispatch and tile map of at most kRoutePlanTokens tokens (one fragment of the gate GEMM's
-// matrix instruction) in one launch (route.hip), by one workgroup; shared: a group that streams_beside_route, whose
-// first half runs beside it in the same launch, or none.
-constexpr int kRoutePlanTokens = 16;
-bool streams_beside_route(const StreamGroup& shared);
+// Routing, selection, dispatch and tile map of at most kRoutePlanTokens tokens in one launch (route.hip), by one
+// workgroup; shared: a group whose first half runs beside it (choice.hpp, first_half_beside_route), or none.
 hipError_t launch_route_few(const void* X, const void* gate_packed, const float* bias, bool with_gate, int T,
                             int d, int E, int K, int Kb, int64_t B, float* scores, int32_t* topk_ids, float* topk_s,
                             float* sgate, int sel_mode, float* sel_keys, int32_t* keep_count,

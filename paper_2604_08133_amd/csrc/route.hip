@@ -9,6 +9,7 @@
 
 #include <algorithm>
 
+#include "choice.hpp"
 #include "common.hpp"
 #include "ffn_bf16_stream.hpp"
 #include "kernels.hpp"
@@ -582,11 +583,6 @@ hipError_t launch_route_mfma(const void* X, const void* gate_packed, const float
         ALLOCMOE_ROUTE_LAUNCH(false, 1);
 #undef ALLOCMOE_ROUTE_LAUNCH
     return hipGetLastError();
-}
-
-bool streams_beside_route(const StreamGroup& shared) {
-    constexpr int kUnits = 256;   // one round with the routing workgroup; every wave has a step
-    return shared.N > 0 && shared.N / 32 < kUnits && shared.Kd >= kRmWaves * (shared.scale != nullptr ? 32 : 16);
 }
 
 hipError_t launch_route_few(const void* X, const void* gate_packed, const float* bias, bool with_gate, int T,

@@ -16,6 +16,9 @@ extern "C" int choose(int T, int d, int E, int I, int Is, long long B) {
 extern "C" int second_half(int T, int d, int E, int I, int Is, long long B, int weight_bytes) {
     return allocmoe::side_second_half_workgroups(T, d, E, I, Is, B, weight_bytes);
 }
+extern "C" int beside_route(int T, int d, int E, int I, int Is, long long B, int fp8) {
+    return allocmoe::first_half_beside_route(allocmoe::choose_ffn(T, d, E, I, Is, B), T, d, Is, B, fp8);
+}
 extern "C" int tile_rows(long long rows, int col_tiles, long long most) {
     return allocmoe::dense_tile_rows(rows, col_tiles, most);
 }
@@ -43,6 +46,11 @@ def choose(T, d, E, I, Is, B):
 def second_half_workgroups(T, d, E, I, Is, B, weight_bytes):
     """Limit of the workgroups of the second half of a shared expert on its own stream."""
     return _library().second_half(T, d, E, I, Is, ctypes.c_longlong(B), weight_bytes)
+
+
+def first_half_beside_route(T, d, E, I, Is, B, fp8):
+    """Whether the shared expert's first half is part of the routing launch."""
+    return bool(_library().beside_route(T, d, E, I, Is, ctypes.c_longlong(B), int(fp8)))
 
 
 def dense_tile_rows(rows, col_tiles, most):

@@ -1,7 +1,8 @@
 """Kernel and stream of the bf16 expert networks: both sides of every limit of the rule."""
 import pytest
 
-from tests.ffn_choice import choose, dense_tile_rows, second_half_workgroups
+import bench
+from tests.ffn_choice import choose, dense_tile_rows, first_half_beside_route, second_half_workgroups
 
 STREAMING, TILED = (False, False, False), (True, True, False)
 BESIDE, BESIDE_TILED, BESIDE_STREAMING = (False, True, True), (True, True, True), (True, False, True)
@@ -57,3 +58,24 @@ def test_second_half_ends_before_the_routed_experts():
     assert second_half_workgroups(600, 2048, 60, 1408, 5632, 1200, 2) == 64
     # few of the experts can have rows: 59 us against 2.9 an expert
     assert [second_half_workgroups(600, 2048, 64, 1408, 2816, b, 2) for b in (20, 21)] == [128, 64]
+
+
+@pytest.mark.parametrize("T,d,Is,B,fp8,beside", [(16, 256, 2816, 48, False, True), (17, 256, 2816, 48, False, False),
+                                                 (16, 255, 2816, 48, False, False), (16, 512, 2816, 48, True, True),
+                                                 (16, 511, 2816, 48, True, False), (16, 2048, 8160, 48, False, True),
+                                                 (16, 2048, 8192, 48, False, False), (1, 2048, 2816, 0, False, False),
+                                                 (1, 2048, 0, 3, False, False)])
+def test_shared_first_half_beside_the_routing(T, d, Is, B, fp8, beside):
+    assert first_half_beside_route(T, d, 64, 1408, Is, B, fp8) == beside
+
+
+def test_benchmark_counts_the_bytes_of_the_launch_it_times():
+    """Decode shapes: the benchmark's own statement of the rule, for its count of the first half's bytes."""
+    for T in (1, 8, 16, 17, 32):
+        for d in (64, 192, 256, 448, 512, 2048):
+            for Is in (0, 64, 2816, 8128, 8192, 22528):
+                for B in (0, T, 4 * T):
+                    for fp8 in (False, True):
+                        if not any(choose(T, d, 64, 1408, Is, B)):
+                            assert (bench.first_half_beside_route(T, d, Is, B, fp8) ==
+                                    first_half_beside_route(T, d, 64, 1408, Is, B, fp8)), (T, d, Is, B, fp8)
