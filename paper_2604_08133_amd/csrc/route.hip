@@ -494,11 +494,12 @@ __global__ __launch_bounds__(kRmWaves* kWave) void route_plan_kernel(
 // workgroup is a chain of dependent steps with the chip idle (9-10 us at 16 tokens, 11 with the others beside it,
 // whose share of the layer's weights is a third to a tenth).  A unit has one workgroup of 16 waves, which take a
 // column block's steps in turn; four steps in flight a wave are 128 KB a unit.  (Six and eight do not fit the 128
-// registers: 16 tokens 83.5 and 97.4 us.  With 8-bit weights four registers spill; rings of 3 and 2 without spills take
-// the same time.)  Layer of 64 experts of 2048 x 1408, shared expert of 2816, streaming behind the routing workgroup and
+// registers: 16 tokens 83.5 and 97.4 us.  With 8-bit weights three: four registers spill with a ring of four, which takes
+// the same time, 1.000 in the mean of 18 layers of 1 to 16 tokens.)  Layer of 64 experts of 2048 x 1408, shared expert of 2816, streaming behind the routing workgroup and
 // beside it: 1 token 31.1 us, 30.5; 8: 69.5, 65.0; 16: 85.3, 80.8; 60 experts, shared expert of 5632: 1 token 42.1 before
 // either, 34.8.  Beside the routing alone of 17 and more tokens it takes longer than the routing: 32 tokens 147.2, 150.4.
-constexpr int kSharedRing = 4;
+template <bool FP8>
+constexpr int kSharedRing = FP8 ? 3 : 4;
 template <bool GATE, bool FP8>
 __global__ __launch_bounds__(kRmWaves* kWave) void route_shared_kernel(
     const bf16_t* __restrict__ X, const bf16_t* __restrict__ Gp, const float* __restrict__ bias,
@@ -510,7 +511,7 @@ __global__ __launch_bounds__(kRmWaves* kWave) void route_shared_kernel(
         route_mfma_body<GATE, 1, true>(X, Gp, bias, T, d, E, K, scores, topk_ids, topk_s, sgate, sel, plan,
                                        reinterpret_cast<RouteSums<GATE, 1>&>(sums));
     else
-        stream_body<true, FP8, kSharedRing, 2, kRmWaves>(shared, blockIdx.x - 1, reinterpret_cast<StreamSums&>(sums));
+        stream_body<true, FP8, kSharedRing<FP8>, 2, kRmWaves>(shared, blockIdx.x - 1, reinterpret_cast<StreamSums&>(sums));
 }
 
 // Candidates from caller-supplied scores: one wave per token.
