@@ -62,7 +62,7 @@ class AllocMoEError(RuntimeError):
 
 # Pointers are passed as plain numbers: with the argument types declared, ctypes converts them itself
 # (an object per pointer otherwise, 10 to 15 of them a call).
-_P, _I32, _I64, _SIZE = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_size_t
+_P, _SIZE = ctypes.c_void_p, ctypes.c_size_t
 _ARGTYPES = {
     "allocmoe_route": [_P] * 8 + [_SIZE, _P],
     "allocmoe_route_from_scores": [_P] * 6 + [_SIZE, _P],

@@ -45,15 +45,15 @@ hipError_t launch_topk_from_scores(const float* scores, int T, int E, int K, int
 // selection then needs plan_spread_bytes(T) bytes of device scratch (`spread`, 256-byte aligned;
 // null: one workgroup does the work, whatever T).  Every launch of the sequence costs 4-10 us
 // whatever its size (a chain of dependent memory round trips).
-//   selection alone: from kPlanSpreadTokens on.  4200 tokens, K = 6: one workgroup 17.4 us with
-//     Top-K, spread 21.5; 6000: 20.7, 22.8; 8192: 24.7, 24.9; but scores of 64 levels (half the
-//     pool on one histogram count) 30.1, 28.4; 38.9, 31.8; 49.3, 36.0.
+//   selection alone: from kPlanSpreadTokens on.  4200 tokens, K = 6: one workgroup 19.5 us with
+//     Top-K, spread 20.7; 6000: 22.4, 21.2; 8192: 27.7, 21.6; scores of 64 levels (half the
+//     pool on one histogram count) 33.1, 26.3; 42.8, 26.7; 55.1, 27.2; K = 2, no levels: 4096 10.6, 17.7.
 //   dispatch, alone or behind the selection: from kPlanSpreadDispatchTokens on, or where the
-//     one-launch kernel cannot hold the pool.  Dispatch at 4200 tokens 10.6 us in one launch, 14.2
-//     spread; 6000: 13.1, 14.4; 8192: 16.1, 15.2; layer of 64 experts of 2048 x 1024, K = 8: 4096
-//     tokens 310 us, 330; 6000: 389, 401; K = 6: 7000 tokens 381, 377, 8192: 410, 404.  Tied scores,
-//     layer of 64 experts of 512 x 256: repeated tokens 79 us, 99 at 4096 (K = 8), 98, 123 at 6000; 3 of
-//     4 tokens padding 85, 97 and 103, 105 (K = 6); 9 of 10 at 6000 110, 107.
+//     one-launch kernel cannot hold the pool.  Dispatch at 4200 tokens 8.9 us in one launch, 12.5
+//     spread; 6000: 11.1, 12.6; 7000: 12.2, 12.6; 8191: 13.3, 12.6; layer of 64 experts of 2048 x 1024, K = 8: 4096
+//     tokens 333 us, 350; 6000: 415, 421; K = 6: 7000 tokens 374, 376, 8191: 428, 425.  Tied scores,
+//     layer of 64 experts of 512 x 256: repeated tokens 80 us, 93 at 4096 (K = 8), 97, 100 at 6000; 3 of
+//     4 tokens padding 81, 86 and 100, 93 (K = 6); 9 of 10 at 6000 105, 95.
 // `alone`: nothing else wants the compute units while the plan runs; the one launch then
 // has several workgroups that repeat the selection and share
 // out the placement (beside other work extra workgroups would only queue behind it).

@@ -72,8 +72,10 @@ __device__ __forceinline__ void expert_load(const int32_t* __restrict__ topk_ids
         }
     };
     // The ids of many pairs at once, then one by one what the thread's own pairs of this expert (one in E) need.
-    // (Score and keep count of every pair loaded beside its id: three times the loads, which bound a
-    // unit here; 6000 tokens, 6 candidates 9.5 us the kernel, 16000, 8: 23.)
+    // (Score and keep count of every pair loaded beside its id: three times the loads, which bound a unit here.  The kernel
+    // with them and now, 16000 tokens, 8 candidates: 64 even experts 22.5 us, 10.0; eight of them in every token
+    // 24.1, 14.9; 8 experts 23.8, 14.9; 2 experts, 2 candidates 8.4, 8.9.  6000 x 6, 64 experts of rank^-1.1: 9.7, 7.4.  Own
+    // pairs two at a time: the same; four: up to 2.4 longer.)
     typedef int32_t i32x4_any __attribute__((ext_vector_type(4), aligned(4)));
     const int quads = pairs / 4;
     for (int64_t q0 = tid; q0 < quads; q0 += kLoadQuads * kStatThreads) {
