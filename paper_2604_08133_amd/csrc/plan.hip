@@ -654,11 +654,11 @@ __global__ __launch_bounds__(NT) void plan_fast_kernel(
     const int own0 = SPLIT ? min(n_batch, group * per_group) : 0, own1 = SPLIT ? min(n_batch, own0 + per_group) : n_batch;
     // [wave][copy][expert], an expert's copies in different banks; copy 0 in the end the sum of all
     typedef uint32_t Counters[kCopies][kWave + kWave / kCopies];
-    Counters& counters = reinterpret_cast<Counters*>(sh.words + kOwn * kWave)[wave];
+    auto counters_of = [&](int w) -> Counters& { return reinterpret_cast<Counters*>(sh.words + kOwn * kWave)[w]; };
     if constexpr (SPLIT) {
         static_assert(NT == kPlanThreads && kOwn * kWave * 8 + NW * sizeof(Counters) <= sizeof(sh.words) && kOwn <= NW, "room");
 #pragma unroll
-        for (int c = 0; c < kCopies; ++c) counters[c][lane] = 0;
+        for (int c = 0; c < kCopies; ++c) counters_of(wave)[c][lane] = 0;
     }
     // ---- A: ballot words by bit-matrix transpose (lane e ends up with expert e's word)
     auto make_words = [&](auto nj_const) {
@@ -671,7 +671,7 @@ __global__ __launch_bounds__(NT) void plan_fast_kernel(
             if constexpr (SPLIT) {
                 if (b < own0 || b >= own1) {   // uniform
                     auto expert = [&](int j) { return (ids[j / 4] >> (8 * (j % 4))) & (kWave - 1); };
-                    uint32_t* counter = counters[lane % kCopies];
+                    uint32_t* counter = counters_of(wave)[lane % kCopies];
                     const uint32_t one = b < own0 ? 1u : 1u << 16;
                     if (__ballot(repeats_id(ids, kt)) == 0) {
 #pragma unroll
@@ -711,8 +711,8 @@ __global__ __launch_bounds__(NT) void plan_fast_kernel(
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         uint32_t sum = 0;
 #pragma unroll
-        for (int c = 0; c < kCopies; ++c) sum += counters[c][lane];
-        counters[0][lane] = sum;
+        for (int c = 0; c < kCopies; ++c) sum += counters_of(wave)[c][lane];
+        counters_of(wave)[0][lane] = sum;
     }
     __syncthreads();
     // ---- B: per expert, exclusive prefix over batches; offsets over experts
@@ -720,7 +720,7 @@ __global__ __launch_bounds__(NT) void plan_fast_kernel(
         int own[kOwn];
         uint32_t sum = 0;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) sum += reinterpret_cast<Counters*>(sh.words + kOwn * kWave)[w][0][lane];
+        for (int w = 0; w < NW; ++w) sum += counters_of(w)[0][lane];
         int before = static_cast<int>(sum & 0xFFFFu), total = static_cast<int>(sum >> 16);
 #pragma unroll
         for (int i = 0; i < kOwn; ++i) own[i] = i < own1 - own0 ? __popcll(sh.words[i * kWave + lane]) : 0;

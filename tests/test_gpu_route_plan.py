@@ -53,7 +53,7 @@ def test_selectors(mode, T, K, budget):
 
 
 # the shared expert's first half in the routing launch: one step a wave and uneven numbers of steps, below and
-# above its ring of four; the widest shared expert that takes one round and the first that does not; d too short
+# above its ring of four (8-bit weights three); the widest shared expert that takes one round and the first that does not; d too short
 @pytest.mark.parametrize("T,d,Is,gate,fp8", [(1, 256, 64, False, False), (16, 320, 128, True, False), (5, 192, 64, False, False),
                                              (3, 1088, 192, False, False), (9, 1216, 64, True, False), (16, 2048, 64, False, False),
                                              (2, 256, 8128, False, False), (2, 256, 8192, False, False),
